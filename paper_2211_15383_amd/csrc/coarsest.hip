@@ -1,0 +1,697 @@
+// Fixed-count GMRES of a small coarsest level, every step of it in one launch.
+//
+// A V-cycle ends in m steps of GMRES on the coarsest operator (after the exact solve on the
+// deflation space when one is attached).  As separate launches that is 2 to 6 launches a step
+// and a dozen around them, 2 to 20 us each on vectors of a few KB: launch latency and idle
+// CUs.  Here one workgroup owns one right-hand side: the Krylov vector, the operator's result,
+// the Hessenberg matrix and (where it fits) the basis stay in LDS, and the operator's blocks
+// are streamed from L2, which is what bounds a step (64 bytes per clock and CU).
+//
+//   * operator: a thread per row (column-major blocks, so that a wavefront's loads are
+//     contiguous; the complex-FP32 d = 16 blocks, row-major for the matrix cores, have a
+//     copy by column pairs on levels of this size).  In complex FP64 the contraction is split
+//     over P threads where the rows alone would leave threads idle;
+//   * Gram-Schmidt as in gram.hip: complex FP32 one pass on the unnormalised basis, complex
+//     FP64 two passes on the normalised one; FP64 arithmetic;
+//   * the last wavefront applies the Givens rotations to a step's Hessenberg column before it
+//     joins the next step's operator, whose streaming hides them; one wavefront ends with the
+//     back substitution.
+//
+// The complex-FP32 form without a deflation performs the operations of the separate
+// launches (gram.hip's one-workgroup step, the coarse stencils, the coefficient kernels) in
+// their order, fused multiply-adds included, so its results are theirs to the last bit: the
+// test vectors of a hierarchy come out of solves with it, and a deflation's FP32 vectors
+// magnify a last-bit change of the coarse operators to 1e-8 in the coarsest samples.
+//
+// Measured (MI355X) against the separate launches: 8 steps with 32 deflation vectors, n = 1024,
+// 32 right-hand sides 228 -> 82 us (a step 18.7 kclk: operator 11.5 of its 10.2 floor, dots 4.1,
+// update 1.9); 24 steps, n = 600 with 10 dofs, 5 right-hand sides 920 -> 195 us; the 16^2 FP64
+// estimate 20.7 -> 5.6 ms, the 128^2 mixed one 39.4 -> 23.4 ms.
+#include <algorithm>
+
+#include "coarsest.h"
+#include "wave.h"
+
+namespace {
+
+constexpr int CS_THREADS = 1024;
+constexpr int CS_WAVES = CS_THREADS / 64;
+constexpr int CS_COLS = 16;    // FP32 operator columns whose loads a thread has in flight (half in FP64)
+constexpr int CS_MAX_M = 31;
+constexpr int CS_MAX_K = SMALL_LEVEL_N / 4;  // deflation vectors
+constexpr size_t CS_LDS = 160 * 1024;  // per workgroup
+
+// Krylov basis of a right-hand side: vectors 0 .. kl-1 in LDS, the others in global memory
+template <typename R>
+struct Basis {
+  Cx<R>* lds;
+  Cx<R>* mem;
+  int n, kl;
+  __device__ __forceinline__ Cx<R>* mem_at(int i) const { return mem + (int64_t)(i - kl) * n; }
+};
+
+// f(v_i, i) for i in [i0, i1), the two parts in loops of their own (each with its address space)
+#define BASIS_LOOP(B, i0, i1, UNROLL, BODY)                                     \
+  {                                                                             \
+    const int bl_split = min((i1), max((i0), (B).kl));                          \
+    _Pragma(UNROLL) for (int i = (i0); i < bl_split; ++i) {                     \
+      const auto* v = (B).lds + i * (B).n;                                      \
+      BODY                                                                      \
+    }                                                                           \
+    _Pragma(UNROLL) for (int i = bl_split; i < (i1); ++i) {                     \
+      const auto* v = (B).mem_at(i);                                            \
+      BODY                                                                      \
+    }                                                                           \
+  }
+
+struct SmallArgs {
+  int n, d, Lx, Lt, m, k, P, nrhs;
+  const void* A;
+  const void* b;
+  void* x;
+  const void* W;        // deflation vectors [k][n] (Gamma5 X), or NULL
+  const double* lam;
+  int kl;               // basis vectors 0 .. kl-1 are kept in LDS
+  void* basis;          // the others: [nrhs][m + 1 - kl][n]
+  c128* e0;             // [nrhs][n], the deflation space's part of the solution
+};
+
+// LDS of fixed size: constant addresses (with run-time offsets for all of them the kernel
+// spilled registers).  The deflation coefficients are used before the Hessenberg matrix is.
+struct SmallShared {
+  union {
+    c128 H[(CS_MAX_M + 1) * CS_MAX_M];
+    c128 defl[2][CS_MAX_K];  // W^H b and Lambda^-1 W^H b
+  };
+  double stage[CS_WAVES * 64];
+  c128 cf[CS_MAX_M + 1], cs[CS_MAX_M + 1], g[CS_MAX_M + 1], rs[CS_MAX_M + 1];
+  double sc[CS_MAX_M + 1], rc[CS_MAX_M + 1], red[CS_WAVES];
+};
+
+// LDS sized by the level: u, w (n entries each), the split rows' partial sums, the basis
+// vectors kept in LDS, the operator's blocks
+template <typename R>
+__host__ __device__ inline size_t small_dynamic(int n, int d, int P, int kl, bool blocks) {
+  return sizeof(Cx<R>) * (size_t)n * (2 + (P > 1 ? P : 0) + kl + (blocks ? 5 * d : 0));
+}
+
+__device__ __forceinline__ void site_neighbours(int s, int Lx, int Lt, int* nb) {
+  const int x = s % Lx, t = s / Lx;
+  nb[0] = s;
+  nb[1] = (x + 1 == Lx) ? s - (Lx - 1) : s + 1;
+  nb[2] = (x == 0) ? s + (Lx - 1) : s - 1;
+  nb[3] = (t + 1 == Lt) ? s - (Lt - 1) * Lx : s + Lx;
+  nb[4] = (t == 0) ? s + (Lt - 1) * Lx : s - Lx;
+}
+
+// the eight products of columns 2k' + h, k' = 0..3, of a lane's row in the order of the
+// matrix-core stencil: step t takes dofs t, 4 + t, 8 + t, 12 + t one after the other (h = t / 2,
+// v4 and m4 hold columns 4 k + 2 h and 4 k + 2 h + 1)
+__device__ __forceinline__ void mfma_order(c64& acc, const float4 (&m4)[4], const float4 (&v4)[4]) {
+#pragma unroll
+  for (int t = 0; t < 2; ++t) {
+#pragma unroll
+    for (int k = 0; k < 4; ++k) {
+      const c64 m = t ? cmk(m4[k].z, m4[k].w) : cmk(m4[k].x, m4[k].y);
+      const c64 v = t ? cmk(v4[k].z, v4[k].w) : cmk(v4[k].x, v4[k].y);
+      acc.x = fmaf(m.x, v.x, acc.x);
+      acc.y = fmaf(m.x, v.y, acc.y);
+    }
+#pragma unroll
+    for (int k = 0; k < 4; ++k) {
+      const c64 m = t ? cmk(m4[k].z, m4[k].w) : cmk(m4[k].x, m4[k].y);
+      const c64 v = t ? cmk(v4[k].z, v4[k].w) : cmk(v4[k].x, v4[k].y);
+      acc.x = fmaf(-m.y, v.y, acc.x);
+      acc.y = fmaf(m.y, v.x, acc.y);
+    }
+  }
+}
+
+// w = D u in complex FP32 (u, w in LDS; blocks by column pairs, in LDS or global memory), a
+// thread per row, in the order of the coarse stencils; ends with a barrier
+template <bool D16>
+__device__ void small_op(const SmallArgs& a, const c64* A, const c64* __restrict__ u, c64* __restrict__ w, c64*) {
+  const int d = D16 ? 16 : a.d, pairs = d / 2;
+  for (int row = threadIdx.x; row < a.n; row += CS_THREADS) {
+    const int s = row / d;
+    int nb[5];
+    site_neighbours(s, a.Lx, a.Lt, nb);
+    // lane i of a site reads entries (i, 2 q), (i, 2 q + 1) as 16 bytes
+    const float4* As = reinterpret_cast<const float4*>(A) + (int64_t)s * 5 * d * pairs + (row - s * d);
+    c64 acc = cmk(0.f, 0.f);
+    if constexpr (D16) {
+      // (the next direction's loads ahead of this one's products spilled: slower)
+#pragma unroll 1
+      for (int dir = 0; dir < 5; ++dir) {
+        const int site = dir == 0 ? nb[0] : dir == 1 ? nb[1] : dir == 2 ? nb[2] : dir == 3 ? nb[3] : nb[4];
+        float4 m0[4], m1[4], v4[4];
+#pragma unroll
+        for (int k = 0; k < 4; ++k) {
+          m0[k] = As[dir * 128 + 32 * k];
+          m1[k] = As[dir * 128 + 32 * k + 16];
+        }
+        const float4* ud = reinterpret_cast<const float4*>(u + site * 16);
+#pragma unroll
+        for (int k = 0; k < 4; ++k) v4[k] = ud[2 * k];
+        mfma_order(acc, m0, v4);
+#pragma unroll
+        for (int k = 0; k < 4; ++k) v4[k] = ud[2 * k + 1];
+        mfma_order(acc, m1, v4);
+      }
+    } else {
+#pragma unroll 1
+      for (int dir = 0; dir < 5; ++dir) {
+        const float4* Ad = As + dir * d * pairs;
+        const int site = dir == 0 ? nb[0] : dir == 1 ? nb[1] : dir == 2 ? nb[2] : dir == 3 ? nb[3] : nb[4];
+        const float4* ud = reinterpret_cast<const float4*>(u + site * d);
+#pragma unroll 1
+        for (int q0 = 0; q0 < pairs; q0 += CS_COLS / 2) {
+          float4 m4[CS_COLS / 2];
+#pragma unroll
+          for (int q = 0; q < CS_COLS / 2; ++q)
+            if (q0 + q < pairs) m4[q] = Ad[(q0 + q) * d];
+#pragma unroll
+          for (int q = 0; q < CS_COLS / 2; ++q) {
+            if (q0 + q < pairs) {
+              const float4 v = ud[q0 + q];
+              cfma(acc, cmk(m4[q].x, m4[q].y), cmk(v.x, v.y));
+              cfma(acc, cmk(m4[q].z, m4[q].w), cmk(v.z, v.w));
+            }
+          }
+        }
+      }
+    }
+    w[row] = acc;
+  }
+  __syncthreads();
+}
+
+// The same in complex FP64 (column-major blocks), the 5 d products of a row dealt to P threads
+template <bool D16>
+__device__ void small_op(const SmallArgs& a, const c128* A, const c128* __restrict__ u, c128* __restrict__ w,
+                         c128* __restrict__ part) {
+  const int d = a.d, P = a.P;
+  for (int e = threadIdx.x; e < a.n * P; e += CS_THREADS) {
+    const int row = e % a.n, p0 = e / a.n;  // P > 1 only when n P <= CS_THREADS
+    const int s = row / d;
+    int nb[5];
+    site_neighbours(s, a.Lx, a.Lt, nb);
+    const c128* As = A + (int64_t)s * 5 * d * d + (row - s * d);
+    c128 acc = cmk(0.0, 0.0);
+    for (int q0 = p0; q0 < 5 * d; q0 += CS_COLS / 2 * P) {
+      c128 m[CS_COLS / 2];
+#pragma unroll
+      for (int t = 0; t < CS_COLS / 2; ++t)
+        if (q0 + t * P < 5 * d) m[t] = As[(q0 + t * P) * d];
+#pragma unroll
+      for (int t = 0; t < CS_COLS / 2; ++t) {
+        const int q = q0 + t * P;
+        if (q < 5 * d) {
+          const int dir = (q >= d) + (q >= 2 * d) + (q >= 3 * d) + (q >= 4 * d);
+          const int site = dir == 0 ? nb[0] : dir == 1 ? nb[1] : dir == 2 ? nb[2] : dir == 3 ? nb[3] : nb[4];
+          cfma(acc, m[t], u[site * d + q - dir * d]);
+        }
+      }
+    }
+    if (P > 1)
+      part[e] = acc;
+    else
+      w[row] = acc;
+  }
+  if (P > 1) {
+    __syncthreads();
+    for (int row = threadIdx.x; row < a.n; row += CS_THREADS) {
+      c128 acc = part[row];
+      for (int p = 1; p < P; ++p) acc = acc + part[p * a.n + row];
+      w[row] = acc;
+    }
+  }
+  __syncthreads();
+}
+
+// <v, w> over n entries (n even, w in LDS) by a wavefront, the same value in every lane
+template <typename R>
+__device__ __forceinline__ c128 small_dot(const Cx<R>* v, const Cx<R>* __restrict__ w, int n) {
+  struct __align__(2 * sizeof(Cx<R>)) Two {
+    Cx<R> a, b;
+  };
+  const Two* vp = reinterpret_cast<const Two*>(v);
+  const Two* wp = reinterpret_cast<const Two*>(w);
+  double re = 0.0, im = 0.0;
+#pragma unroll 8
+  for (int p = threadIdx.x & 63; p < n / 2; p += 64) {
+    const Two x = vp[p], y = wp[p];
+    re = fma((double)x.a.x, (double)y.a.x, re);
+    re = fma((double)x.a.y, (double)y.a.y, re);
+    im = fma((double)x.a.x, (double)y.a.y, im);
+    im = fma(-(double)x.a.y, (double)y.a.x, im);
+    re = fma((double)x.b.x, (double)y.b.x, re);
+    re = fma((double)x.b.y, (double)y.b.y, re);
+    im = fma((double)x.b.x, (double)y.b.y, im);
+    im = fma(-(double)x.b.y, (double)y.b.x, im);
+  }
+  return cmk(wave::sum(re), wave::sum(im));
+}
+
+// red[i] = <v_i, w> for i < nb, a wavefront per basis vector; the caller synchronises
+__device__ __forceinline__ void small_dots64(const Basis<double>& V, int nb, const c128* __restrict__ w,
+                                             c128* __restrict__ red) {
+  for (int i = threadIdx.x >> 6; i < nb; i += CS_WAVES) {
+    const c128 d = i < V.kl ? small_dot(V.lds + i * V.n, w, V.n) : small_dot(V.mem_at(i), w, V.n);
+    if ((threadIdx.x & 63) == 0) red[i] = d;
+  }
+}
+
+// Sum of v over the workgroup, in every thread (two barriers)
+__device__ __forceinline__ double small_sum(double v, double* red) {
+  v = wave::sum(v);
+  __syncthreads();
+  if ((threadIdx.x & 63) == 0) red[threadIdx.x >> 6] = v;
+  __syncthreads();
+  double s = 0.0;
+#pragma unroll
+  for (int q = 0; q < CS_WAVES; ++q) s += red[q];
+  return s;
+}
+
+// a b with the roundings of the two-launch kernels' complex products: the first product of
+// each part fused onto the second (IM_HX: which of the imaginary part's products is fused)
+template <bool IM_HX>
+__device__ __forceinline__ c128 cprod(c128 a, c128 b) {
+  const double re = fma(a.x, b.x, -(a.y * b.y));
+  return cmk(re, IM_HX ? fma(a.x, b.y, a.y * b.x) : fma(a.y, b.x, a.x * b.y));
+}
+
+// Applies rotations 0 .. j-1 to column j of H (complex, the subdiagonal entry real), forms
+// rotation j and takes g through it: the operations of hessenberg_update (gram.hip), in every
+// lane of the calling wavefront alike.
+__device__ __forceinline__ void small_rotate(c128* col, double* rc, c128* rs, c128* g, int j) {
+  c128 a = col[0];
+#pragma unroll 4
+  for (int i = 0; i < j; ++i) {
+    const c128 b = col[i + 1], s = rs[i];
+    const double c = rc[i];
+    const c128 sb = cprod<false>(s, b);
+    col[i] = cmk(fma(a.x, c, sb.x), fma(a.y, c, sb.y));
+    a = cmk(fma(c, b.x, -fma(a.x, s.x, a.y * s.y)), fma(c, b.y, -fma(a.y, s.x, -(a.x * s.y))));
+  }
+  const double aa = sqrt(fma(a.x, a.x, a.y * a.y)), beta = col[j + 1].x;
+  const double rho = sqrt(fma(beta, beta, aa * aa));
+  double c = 1.0;
+  c128 s = cmk(0.0, 0.0), diag = cmk(0.0, 0.0);
+  if (rho != 0.0) {
+    if (aa == 0.0) {
+      c = 0.0;
+      s = cmk(1.0, 0.0);
+      diag = cmk(beta, 0.0);
+    } else {
+      const c128 ph = cmk(a.x / aa, a.y / aa);
+      c = aa / rho;
+      s = (beta / rho) * ph;
+      diag = rho * ph;
+    }
+  }
+  const c128 gj = g[j];
+  __builtin_amdgcn_wave_barrier();
+  col[j] = diag;
+  rc[j] = c;
+  rs[j] = s;
+  g[j] = c * gj;
+  g[j + 1] = cmk(-fma(s.x, gj.x, s.y * gj.y), -fma(s.x, gj.y, -(s.y * gj.x)));  // -conj(s) g_j
+}
+
+__device__ __forceinline__ c128 lane_value(c128 v, int lane) {
+  return cmk(__hiloint2double(__builtin_amdgcn_readlane(__double2hiint(v.x), lane),
+                              __builtin_amdgcn_readlane(__double2loint(v.x), lane)),
+             __hiloint2double(__builtin_amdgcn_readlane(__double2hiint(v.y), lane),
+                              __builtin_amdgcn_readlane(__double2loint(v.y), lane)));
+}
+
+// One wavefront: g <- R^-1 g, R the rotated Hessenberg matrix (column c at H + c (m + 1)), by
+// back substitution in backsub_kernel's order (solver.hip); zero pivots give zero coefficients.
+// Lane c holds g_c, then y_c.
+__device__ void small_backsub(const c128* H, c128* g, int m) {
+  const int c = threadIdx.x & 63;
+  const c128* col = H + (c < m ? c : 0) * (m + 1);
+  c128 mine = g[c < m ? c : 0];
+  c128 h = col[m - 1];
+  for (int i = m - 1; i >= 0; --i) {
+    const c128 hi = h;
+    if (i > 0) h = col[i - 1];
+    // lane l > i: R[i][l] y_l; zero beyond the last column, so that four at a time may overrun
+    const c128 term = c < m ? cprod<false>(hi, mine) : cmk(0.0, 0.0);
+    c128 acc = mine;
+    for (int l = i + 1; l < m; l += 4) {
+      const c128 t0 = lane_value(term, l), t1 = lane_value(term, l + 1), t2 = lane_value(term, l + 2),
+                 t3 = lane_value(term, l + 3);
+      acc = ((acc - t0) - t1) - t2;
+      acc = acc - t3;
+    }
+    const double dd = fma(hi.x, hi.x, hi.y * hi.y);
+    if (c == i)
+      mine = dd > 0.0 ? cmk(fma(acc.x, hi.x, acc.y * hi.y) / dd, fma(acc.y, hi.x, -(acc.x * hi.y)) / dd)
+                      : cmk(0.0, 0.0);
+  }
+  if (c < m) g[c] = mine;
+}
+
+// The dots of the one-workgroup step of gram.hip on complex-FP32 vectors of at most 2048
+// entries, in its order: thread t has the pair of entries 2t, 2t + 1, a wavefront tree per
+// basis vector, then the wavefronts one after the other.  raw[i] = <u_i, w>; ends with a
+// barrier.  stage: [CS_WAVES][64] doubles.
+__device__ __forceinline__ void small_dots32(const Basis<float>& V, int nb, const c64* __restrict__ w, int n, double* stage,
+                                             c128* __restrict__ raw) {
+  const int tid = threadIdx.x, lane = tid & 63, wv = tid >> 6;
+  const int np = n / 2, nw = (np + 63) / 64;
+  // wavefronts beyond the nw that cover the vectors take further groups of four basis vectors
+  const int groups = CS_WAVES / nw, t = tid - (wv / nw) * nw * 64;
+  if (wv < groups * nw) {
+    const bool on = t < np;
+    const float4 b = on ? reinterpret_cast<const float4*>(w)[t] : make_float4(0.f, 0.f, 0.f, 0.f);
+    const double bx0 = b.x, by0 = b.y, bx1 = b.z, by1 = b.w;
+    for (int c0 = 4 * (wv / nw); c0 < nb; c0 += 4 * groups) {
+      double acc[8];
+      float4 u[4];
+#pragma unroll
+      for (int i = 0; i < 4; ++i)
+        u[i] = make_float4(0.f, 0.f, 0.f, 0.f);
+      // kl is a multiple of four or past the last vector: a group is in one part of the basis
+      if (c0 < V.kl) {
+#pragma unroll
+        for (int i = 0; i < 4; ++i)
+          if (on && c0 + i < nb) u[i] = reinterpret_cast<const float4*>(V.lds + (c0 + i) * n)[t];
+      } else {
+#pragma unroll
+        for (int i = 0; i < 4; ++i)
+          if (on && c0 + i < nb) u[i] = reinterpret_cast<const float4*>(V.mem_at(c0 + i))[t];
+      }
+#pragma unroll
+      for (int i = 0; i < 4; ++i) {  // products of two floats are exact in FP64
+        acc[2 * i] = (((double)u[i].x * bx0 + (double)u[i].y * by0) + (double)u[i].z * bx1) + (double)u[i].w * by1;
+        acc[2 * i + 1] = (((double)u[i].x * by0 - (double)u[i].y * bx0) + (double)u[i].z * by1) - (double)u[i].w * bx1;
+      }
+      const double s = wave::sum8(acc);
+      if ((lane & 7) == 0) stage[(wv % nw) * 64 + 2 * c0 + (lane >> 3)] = s;
+    }
+  }
+  __syncthreads();
+  if (tid < 2 * nb) {
+    double s = 0.0;
+#pragma unroll
+    for (int k = 0; k < CS_WAVES; ++k)
+      if (k < nw) s += stage[k * 64 + tid];
+    reinterpret_cast<double*>(raw)[tid] = s;
+  }
+  __syncthreads();
+}
+
+// ||v||^2 of a complex-FP32 vector of at most 2048 entries in the order of the two-launch
+// norm (blocks of 256 threads, one per 1024 entries), in every thread; three barriers
+__device__ __forceinline__ double small_norm32(const c64* v, int n, double* red) {
+  const int tid = threadIdx.x;
+  const int G = (n + 1023) / 1024;
+  double s = 0.0;
+  if (tid < 256 * G)
+    for (int p = tid; p < n; p += 256 * G) s += cabs2(v[p]);
+  s = wave::sum(s);
+  __syncthreads();
+  if ((tid & 63) == 0) red[tid >> 6] = s;
+  __syncthreads();
+  double t = 0.0;
+  for (int g = 0; g < G; ++g) {
+    double b = 0.0;
+    for (int k = 0; k < 4; ++k) b += red[4 * g + k];
+    t += b;
+  }
+  __syncthreads();
+  return t;
+}
+
+template <typename R, bool LDSA, bool D16>
+__global__ __launch_bounds__(CS_THREADS) void coarsest_small_kernel(SmallArgs a) {
+  __shared__ __align__(32) SmallShared S;
+  extern __shared__ __align__(32) unsigned char smem[];
+  const int n = a.n, m = a.m, tid = threadIdx.x, r = blockIdx.x;
+  Cx<R>* u = reinterpret_cast<Cx<R>*>(smem);  // the current Krylov vector
+  Cx<R>* w = u + n;
+  Cx<R>* part = w + n;
+  Basis<R> V;
+  V.lds = part + (a.P > 1 ? a.P * n : 0);
+  V.mem = static_cast<Cx<R>*>(a.basis) + (int64_t)r * (m + 1 - a.kl) * n;
+  V.n = n;
+  V.kl = a.kl;
+  Cx<R>* Al = V.lds + a.kl * n;
+  auto store = [&](int i, int p, auto v) {  // entry (or pair) p of basis vector i
+    using T = decltype(v);
+    if (i < V.kl)
+      reinterpret_cast<T*>(V.lds + i * n)[p] = v;
+    else
+      reinterpret_cast<T*>(V.mem_at(i))[p] = v;
+    reinterpret_cast<T*>(u)[p] = v;
+  };
+  const Cx<R>* b = static_cast<const Cx<R>*>(a.b) + (int64_t)r * n;
+  Cx<R>* x = static_cast<Cx<R>*>(a.x) + (int64_t)r * n;
+  const Cx<R>* A = static_cast<const Cx<R>*>(a.A);
+  if constexpr (LDSA) {
+#pragma unroll 4
+    for (int e = tid; e < n * 5 * a.d; e += CS_THREADS) Al[e] = A[e];
+  }
+  constexpr bool F32 = sizeof(R) == 4;
+
+  // the exact solve on the deflation space: c = W^H b, r = b - W c and e0 = X Lambda^-1 c with
+  // X = Gamma5 W, one pass over W for both
+  const Cx<R>* W = static_cast<const Cx<R>*>(a.W);
+  for (int p = tid; p < n; p += CS_THREADS) w[p] = b[p];
+  __syncthreads();
+  if (a.k > 0) {
+    for (int i = tid >> 6; i < a.k; i += CS_WAVES) {
+      const c128 d = small_dot(W + (int64_t)i * n, w, n);
+      if ((tid & 63) == 0) {
+        S.defl[0][i] = d;
+        S.defl[1][i] = (1.0 / a.lam[i]) * d;
+      }
+    }
+    __syncthreads();
+  }
+  double nrm = 0.0;
+  for (int p = tid; p < n; p += CS_THREADS) {
+    c128 v = cmk((double)w[p].x, (double)w[p].y);
+    if (a.k > 0) {
+      c128 e = cmk(0.0, 0.0);
+#pragma unroll 8
+      for (int i = 0; i < a.k; ++i) {
+        const Cx<R> wi = W[(int64_t)i * n + p];
+        const c128 wd = cmk((double)wi.x, (double)wi.y);
+        v = v - S.defl[0][i] * wd;
+        cfma(e, S.defl[1][i], wd);
+      }
+      a.e0[(int64_t)r * n + p] = p % a.d < a.d / 2 ? e : cmk(-e.x, -e.y);
+    }
+    const Cx<R> u0 = ccast<R>(v);
+    if (F32)
+      store(0, p, u0);
+    else
+      u[p] = u0;
+    nrm += cabs2(u0);
+  }
+  if constexpr (F32) {
+    __syncthreads();
+    nrm = small_norm32(u, n, S.red);
+  } else {
+    nrm = small_sum(nrm, S.red);
+  }
+  const double beta0 = sqrt(fmax(nrm, 0.0));
+  const double inv0 = beta0 > 0.0 ? 1.0 / beta0 : 0.0;
+  if (tid == 0) {
+    S.g[0] = cmk(beta0, 0.0);
+    S.sc[0] = F32 ? inv0 : 1.0;
+  }
+  if constexpr (!F32) {  // normalised basis
+    for (int p = tid; p < n; p += CS_THREADS) store(0, p, inv0 * u[p]);
+  }
+  __syncthreads();
+
+  for (int j = 0; j < m; ++j) {
+    const int nb = j + 1;
+    // the last wavefront rotates the previous column while the others stream the operator
+    if (j > 0 && tid >= CS_THREADS - 64) small_rotate(S.H + (j - 1) * (m + 1), S.rc, S.rs, S.g, j - 1);
+    if constexpr (LDSA)
+      small_op<D16>(a, Al, u, w, part);
+    else
+      small_op<D16>(a, A, u, w, part);
+    c128* hcol = S.H + j * (m + 1);
+    double bn;
+    if constexpr (F32) {
+      // h_i = s_j s_i <u_i, w>; u_{j+1} = s_j w - sum_i h_i s_i u_i
+      small_dots32(V, nb, w, n, S.stage, S.cf);
+      const double ws = S.sc[j];
+      if (tid < nb) {
+        const double si = S.sc[tid];
+        const c128 h = cmk(ws * si * S.cf[tid].x, ws * si * S.cf[tid].y);
+        hcol[tid] = h;
+        S.cs[tid] = cmk(h.x * si, h.y * si);
+      }
+      __syncthreads();
+      nrm = 0.0;
+      if (2 * tid < n) {
+        const float4 b0 = reinterpret_cast<const float4*>(w)[tid];
+        c128 v0 = cmk(ws * (double)b0.x, ws * (double)b0.y), v1 = cmk(ws * (double)b0.z, ws * (double)b0.w);
+        BASIS_LOOP(V, 0, nb, "unroll 8", {
+          const float4 q = reinterpret_cast<const float4*>(v)[tid];
+          const c128 h = S.cs[i];
+          v0 = v0 - cprod<true>(h, cmk((double)q.x, (double)q.y));
+          v1 = v1 - cprod<true>(h, cmk((double)q.z, (double)q.w));
+        })
+        const float4 un = make_float4((float)v0.x, (float)v0.y, (float)v1.x, (float)v1.y);
+        store(nb, tid, un);
+        nrm = (((double)un.x * un.x + (double)un.y * un.y) + (double)un.z * un.z) + (double)un.w * un.w;
+      }
+      bn = sqrt(fmax(small_sum(nrm, S.red), 0.0));
+      if (tid == 0) S.sc[nb] = bn > 0.0 ? 1.0 / bn : 0.0;
+    } else {
+      // w' = w - V h1; h2 = V^H w'; beta^2 = ||w'||^2 - |h2|^2; v_{j+1} = (w' - V h2) / beta
+      small_dots64(V, nb, w, S.cf);
+      __syncthreads();
+      if (tid < nb) hcol[tid] = S.cf[tid];
+      nrm = 0.0;
+      for (int p = tid; p < n; p += CS_THREADS) {
+        c128 wp = w[p];
+        BASIS_LOOP(V, 0, nb, "unroll 4", { wp = wp - S.cf[i] * v[p]; })
+        w[p] = wp;
+        nrm += cabs2(wp);
+      }
+      nrm = small_sum(nrm, S.red);  // its barriers also order w' before the dots
+      small_dots64(V, nb, w, S.cs);
+      __syncthreads();
+      double h2n = 0.0;
+      for (int i = 0; i < nb; ++i) h2n += cabs2(S.cs[i]);
+      if (tid < nb) hcol[tid] = hcol[tid] + S.cs[tid];
+      bn = sqrt(fmax(nrm - h2n, 0.0));
+      const double inv = bn > 0.0 ? 1.0 / bn : 0.0;
+      for (int p = tid; p < n; p += CS_THREADS) {
+        c128 wp = w[p];
+        BASIS_LOOP(V, 0, nb, "unroll 4", { wp = wp - S.cs[i] * v[p]; })
+        store(nb, p, inv * wp);
+      }
+      if (tid == 0) S.sc[nb] = 1.0;
+    }
+    if (tid == 0) hcol[nb] = cmk(bn, 0.0);
+    __syncthreads();
+  }
+  if (tid < 64) {
+    small_rotate(S.H + (m - 1) * (m + 1), S.rc, S.rs, S.g, m - 1);
+    __builtin_amdgcn_wave_barrier();
+    small_backsub(S.H, S.g, m);
+  }
+  __syncthreads();
+  if (tid < m) S.cf[tid] = S.sc[tid] * S.g[tid];
+  __syncthreads();
+  for (int p = tid; p < n; p += CS_THREADS) {
+    c128 xp = cmk(0.0, 0.0);
+    BASIS_LOOP(V, 0, m, "unroll 8", { xp = xp + cprod<false>(S.cf[i], cmk((double)v[p].x, (double)v[p].y)); })
+    if (a.k > 0) xp = xp + a.e0[(int64_t)r * n + p];
+    x[p] = ccast<R>(xp);
+  }
+}
+
+// How a level's solve is laid out: threads that share a row's contraction, basis vectors and
+// blocks in LDS
+struct SmallPlan {
+  int P = 1, kl = 0;
+  bool blocks = false, ok = false;
+  size_t shm = 0;
+};
+
+template <typename R>
+SmallPlan small_plan(const Level& L, int m, int k) {
+  SmallPlan p;
+  if (L.fine || m < 1 || m > CS_MAX_M || L.n() > SMALL_LEVEL_N) return p;
+  const int n = (int)L.n(), d = L.dofs;
+  if (sizeof(R) == 8)
+    while (2 * p.P * n <= CS_THREADS && 2 * p.P <= 5 * d) p.P *= 2;
+  if (k > CS_MAX_K) return p;
+  const size_t room = CS_LDS - sizeof(SmallShared);
+  auto bytes = [&](int kl, bool blocks) { return small_dynamic<R>(n, d, p.P, kl, blocks); };
+  if (bytes(0, false) > room) return p;
+  p.ok = true;
+  p.blocks = bytes(m + 1, true) <= room;
+  p.kl = m + 1;
+  if (bytes(p.kl, p.blocks) > room)
+    for (p.kl = m / 4 * 4; bytes(p.kl, false) > room;) p.kl -= 4;
+  p.shm = bytes(p.kl, p.blocks);
+  return p;
+}
+
+// bytes of device scratch for the basis vectors outside LDS
+template <typename R>
+size_t small_scratch_bytes(const SmallPlan& p, int m, int64_t n, int nrhs) {
+  return ((size_t)(m + 1 - p.kl) * nrhs * n * sizeof(Cx<R>) + 15) / 16 * 16;
+}
+
+template <typename R, bool LDSA, bool D16>
+void small_launch(dmlmc_ctx* ctx, const SmallArgs& a, size_t shm) {
+  auto fn = coarsest_small_kernel<R, LDSA, D16>;
+  HIPCHK(hipFuncSetAttribute((const void*)fn, hipFuncAttributeMaxDynamicSharedMemorySize,
+                             (int)(CS_LDS - sizeof(SmallShared))));
+  hipLaunchKernelGGL(fn, dim3(a.nrhs), dim3(CS_THREADS), shm, ctx->stream, a);
+  LAUNCH_CHECK();
+}
+
+}  // namespace
+
+template <typename R>
+bool coarsest_small_ok(const Level& L, int m, int k) {
+  return small_plan<R>(L, m, k).ok;
+}
+
+template <typename R>
+size_t coarsest_small_scratch(const Level& L, int m, int k, int nrhs) {
+  return small_scratch_bytes<R>(small_plan<R>(L, m, k), m, L.n(), nrhs) + (k > 0 ? sizeof(c128) * nrhs * L.n() : 0);
+}
+
+template <typename R>
+void coarsest_small(dmlmc_ctx* ctx, const Level& L, const dmlmc_defl* D, const Cx<R>* b, Cx<R>* x, int nrhs, int m,
+                    void* scratch) {
+  constexpr bool F32 = std::is_same<R, float>::value;
+  const int k = D ? D->k : 0;
+  const SmallPlan p = small_plan<R>(L, m, k);
+  SmallArgs a;
+  a.n = (int)L.n();
+  a.d = L.dofs;
+  a.Lx = L.Lx;
+  a.Lt = L.Lt;
+  a.m = m;
+  a.k = k;
+  a.P = p.P;
+  a.nrhs = nrhs;
+  a.A = F32 ? L.Apair32.p : L.A64.p;
+  a.b = b;
+  a.x = x;
+  a.W = D ? (F32 ? D->W32.p : D->W64.p) : nullptr;
+  a.lam = D ? D->lam_dev.as<double>() : nullptr;
+  a.kl = p.kl;
+  a.basis = scratch;
+  a.e0 = reinterpret_cast<c128*>(static_cast<char*>(scratch) + small_scratch_bytes<R>(p, m, L.n(), nrhs));
+  REQUIRE(p.ok && a.A != nullptr && (scratch != nullptr || (p.kl == m + 1 && k == 0)),
+          "level not laid out for the one-launch coarsest solve");
+  // the operator's blocks once per step and right-hand side
+  KTimer kt(ctx, "coarsest", (double)nrhs * m * 5 * L.dofs * L.n() * sizeof(Cx<R>));
+  if (F32 && L.dofs == 16) {
+    if (p.blocks)
+      small_launch<R, true, F32>(ctx, a, p.shm);
+    else
+      small_launch<R, false, F32>(ctx, a, p.shm);
+  } else if (p.blocks) {
+    small_launch<R, true, false>(ctx, a, p.shm);
+  } else {
+    small_launch<R, false, false>(ctx, a, p.shm);
+  }
+}
+
+#define INST(R)                                                                                              \
+  template bool coarsest_small_ok<R>(const Level&, int, int);                                                \
+  template size_t coarsest_small_scratch<R>(const Level&, int, int, int);                                    \
+  template void coarsest_small<R>(dmlmc_ctx*, const Level&, const dmlmc_defl*, const Cx<R>*, Cx<R>*, int, int, void*);
+INST(float)
+INST(double)
+#undef INST

@@ -223,6 +223,9 @@ struct Level {
   // blocks column-major (entry (i, j) at j * d + i); FP32 blocks the same except at
   // d = 16, where they are row-major (entry (i, j) at i * 16 + j, the matrix-core layout)
   DevBuf A64, A32, Ainv64, Ainv32;
+  // levels of at most SMALL_LEVEL_N entries: FP32 blocks by column pairs as well (entry (i, j)
+  // at (j / 2) * 2 d + 2 i + j % 2; the one-launch coarsest solve has a thread per row)
+  DevBuf Apair32;
   // d = 16: complex-FP16 copies (real part in the low half of a 32-bit word, row-major) of
   // the four hop blocks [site][4][16][16] and of the inverse self blocks, read by the
   // half-precision operands form of the coarse Gauss-Seidel smoother
@@ -235,6 +238,9 @@ struct Level {
   int64_t n() const { return sites() * dofs; }
   int rows_per_block() const { return ax * at * (dofs / 2); }
 };
+
+// Vector length up to which a coarsest solve runs in one launch (coarsest.hip)
+constexpr int64_t SMALL_LEVEL_N = 2048;
 
 struct Workspace;  // per-level scratch for V-cycles and solves (solver.hip)
 

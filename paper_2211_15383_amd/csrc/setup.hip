@@ -217,15 +217,19 @@ int colour_mod(int extent) {
   return extent;
 }
 
-// FP32 copies of coarse blocks (d x d each): row-major at d = 16, the layout of the
-// matrix-core stencil kernels, column-major (as the FP64 source) otherwise.
+// FP32 copies of coarse blocks (d x d each): column-major as the FP64 source, row-major (the
+// layout of the matrix-core stencil kernels, d = 16) or by column pairs (the one-launch
+// coarsest solve).
+enum BlockOrder { BLOCK_COLS = 0, BLOCK_ROWS = 1, BLOCK_PAIRS = 2 };
 __global__ void cast_blocks_kernel(const c128* __restrict__ src, c64* __restrict__ dst, int64_t total, int d,
-                                   int rowmajor) {
+                                   int order) {
   const int64_t dd = (int64_t)d * d;
   for (int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; i < total; i += (int64_t)gridDim.x * blockDim.x) {
     const int64_t blk = i / dd;
     const int e = (int)(i % dd);
-    const int se = rowmajor ? (e % d) * d + e / d : e;
+    int se = e;
+    if (order == BLOCK_ROWS) se = (e % d) * d + e / d;
+    if (order == BLOCK_PAIRS) se = (2 * (e / (2 * d)) + (e & 1)) * d + (e % (2 * d)) / 2;
     dst[i] = ccast<float>(src[blk * dd + se]);
   }
 }
@@ -256,10 +260,10 @@ void half_blocks(dmlmc_ctx* ctx, const c64* src, uint32_t* dst, int64_t nsites, 
   LAUNCH_CHECK();
 }
 
-void cast_blocks(dmlmc_ctx* ctx, const c128* src, c64* dst, int64_t nblocks, int d) {
+void cast_blocks(dmlmc_ctx* ctx, const c128* src, c64* dst, int64_t nblocks, int d, BlockOrder order) {
   const int64_t total = nblocks * d * d;
   const unsigned grid = (unsigned)std::min<int64_t>(ceil_div(total, 256), 8192);
-  hipLaunchKernelGGL(cast_blocks_kernel, dim3(grid), dim3(256), 0, ctx->stream, src, dst, total, d, d == 16 ? 1 : 0);
+  hipLaunchKernelGGL(cast_blocks_kernel, dim3(grid), dim3(256), 0, ctx->stream, src, dst, total, d, (int)order);
   LAUNCH_CHECK();
 }
 
@@ -321,7 +325,11 @@ Level galerkin_level(dmlmc_ctx* ctx, const Level& F) {
     }
   }
   C.A32.alloc(sizeof(c64) * (size_t)Vc * 5 * dc * dc);
-  cast_blocks(ctx, C.A64.as<c128>(), C.A32.as<c64>(), (int64_t)Vc * 5, dc);
+  cast_blocks(ctx, C.A64.as<c128>(), C.A32.as<c64>(), (int64_t)Vc * 5, dc, dc == 16 ? BLOCK_ROWS : BLOCK_COLS);
+  if (nc <= SMALL_LEVEL_N) {
+    C.Apair32.alloc(sizeof(c64) * (size_t)Vc * 5 * dc * dc);
+    cast_blocks(ctx, C.A64.as<c128>(), C.Apair32.as<c64>(), (int64_t)Vc * 5, dc, BLOCK_PAIRS);
+  }
   // inverse self blocks for the block Gauss-Seidel smoother
   C.Ainv64.alloc(sizeof(c128) * (size_t)Vc * dc * dc);
   DevBuf fail(sizeof(int));
@@ -330,7 +338,7 @@ Level galerkin_level(dmlmc_ctx* ctx, const Level& F) {
                      C.A64.as<c128>(), dc, C.Ainv64.as<c128>(), fail.as<int>());
   LAUNCH_CHECK();
   C.Ainv32.alloc(sizeof(c64) * (size_t)Vc * dc * dc);
-  cast_blocks(ctx, C.Ainv64.as<c128>(), C.Ainv32.as<c64>(), (int64_t)Vc, dc);
+  cast_blocks(ctx, C.Ainv64.as<c128>(), C.Ainv32.as<c64>(), (int64_t)Vc, dc, dc == 16 ? BLOCK_ROWS : BLOCK_COLS);
   if (dc == 16) {
     // the half-precision smoother operands exist only when every entry fits FP16
     DevBuf over(sizeof(int));
@@ -392,6 +400,7 @@ Level clone_operator(dmlmc_ctx* ctx, const Level& S) {
   cp(L.U32, S.U32);
   cp(L.A64, S.A64);
   cp(L.A32, S.A32);
+  cp(L.Apair32, S.Apair32);
   cp(L.Ainv64, S.Ainv64);
   cp(L.Ainv32, S.Ainv32);
   cp(L.Ahop16, S.Ahop16);

@@ -2,7 +2,8 @@
 //   * V-cycle: pre-smoothing, restriction P^H, recursion / coarsest solve, prolongation
 //     P, post-smoothing (SAP on the fine level, red/black block Gauss-Seidel on coarse
 //     levels);
-//   * coarsest solve: fixed-count GMRES (no host synchronisation, graph-capturable);
+//   * coarsest solve: fixed-count GMRES (no host synchronisation, graph-capturable), one
+//     launch for small levels (coarsest.hip);
 //   * right-preconditioned FGMRES with per-RHS Krylov spaces, FP64 Arnoldi (classical
 //     Gram-Schmidt with one reorthogonalisation, FP64 dots), Givens on the device;
 //   * outer FP64 refinement: every restart recomputes r = b - D x in FP64, so the mixed
@@ -11,6 +12,7 @@
 #include <algorithm>
 #include <cmath>
 
+#include "coarsest.h"
 #include "defl.h"
 #include "dense.h"
 #include "solver.h"
@@ -287,6 +289,13 @@ void coarsest_gmres(dmlmc_hier* H, int l, const Cx<R>* b_in, Cx<R>* x, int nrhs)
   const dmlmc_defl* D = H->coarse_defl;
   const bool use_defl = D != nullptr && D->level == l;
   const int m = std::max(1, use_defl ? H->coarsest_iters_defl : H->coarsest_iters);
+  // up to 2048 entries (SMALL_LEVEL_N) every step runs in one launch, a workgroup per RHS
+  if (coarsest_small_ok<R>(L, m, use_defl ? D->k : 0)) {
+    const size_t bytes = coarsest_small_scratch<R>(L, m, use_defl ? D->k : 0, nrhs);
+    void* scratch = bytes ? hier_buf(H, f32 ? "cg_V32" : "cg_V64", l, bytes) : nullptr;
+    coarsest_small<R>(ctx, L, use_defl ? D : nullptr, b_in, x, nrhs, m, scratch);
+    return;
+  }
   const Cx<R>* b = b_in;
   c128* e0 = nullptr;
   if (use_defl) {

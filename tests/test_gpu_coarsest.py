@@ -1,0 +1,105 @@
+"""Fixed-count GMRES of small coarsest levels (one launch up to 2048 entries) against numpy.
+
+dmlmc_apply(OP_VCYCLE) at the coarsest level is the coarsest solve alone: x = e0 + GMRES_m(r)
+with r = b - W W^H b, e0 = X Lambda^-1 W^H b for an attached deflation (r = b, e0 = 0
+without).  The reference builds the Krylov space in FP64 with the exported blocks.
+"""
+import numpy as np
+import pytest
+
+pytestmark = pytest.mark.gpu
+
+M, M_DEFL = 24, 8  # default iteration counts without and with a deflation
+
+# lattice, aggregate, test vectors per chirality: sites x dofs of the coarsest level
+SHAPES = {
+    "8x2": ((8, 16), (4, 4), 1),       # 16 entries, the smallest level
+    "16x8": ((16, 16), (4, 4), 4),     # 128: blocks in LDS
+    "60x10": ((24, 40), (4, 4), 5),    # 600: dofs that are no power of two
+    "64x16": ((32, 32), (4, 4), 8),    # 1024: part of the FP32 basis outside LDS
+    "50x24": ((20, 40), (4, 4), 12),   # 1200: more than 16 dofs
+    "128x16": ((64, 32), (4, 4), 8),   # 2048: the largest in one launch
+    "132x16": ((48, 44), (4, 4), 8),   # 2112: the first in separate launches
+}
+
+
+def _blocks_apply(A, Lx, Lt, x):
+    """D x for x [n, nrhs] with blocks A [sites, 5, d, d] (self, +x, -x, +t, -t)."""
+    d = A.shape[-1]
+    f = x.reshape(Lt, Lx, d, -1)
+    nb = [f, np.roll(f, -1, 1), np.roll(f, 1, 1), np.roll(f, -1, 0), np.roll(f, 1, 0)]
+    B = A.reshape(Lt, Lx, 5, d, d)
+    return sum(B[:, :, k] @ nb[k] for k in range(5)).reshape(x.shape)
+
+
+def _gmres(apply, b, m):
+    """x in the m-step Krylov space of b with the least residual (one vector, FP64)."""
+    beta = np.linalg.norm(b)
+    if beta == 0.0:
+        return np.zeros_like(b)
+    V = np.zeros((b.size, m + 1), dtype=np.complex128)
+    H = np.zeros((m + 1, m), dtype=np.complex128)
+    V[:, 0] = b / beta
+    for j in range(m):
+        w = apply(V[:, j : j + 1])[:, 0]
+        for _ in range(2):
+            h = V[:, : j + 1].conj().T @ w
+            w = w - V[:, : j + 1] @ h
+            H[: j + 1, j] += h
+        H[j + 1, j] = np.linalg.norm(w)
+        V[:, j + 1] = w / H[j + 1, j]
+    e1 = np.zeros(m + 1)
+    e1[0] = beta
+    return V[:, :m] @ np.linalg.lstsq(H, e1, rcond=None)[0]
+
+
+@pytest.mark.parametrize("k", [0, 4])
+@pytest.mark.parametrize("prec", ["mixed", "fp64"])
+@pytest.mark.parametrize("shape", sorted(SHAPES))
+def test_coarsest_gmres(shape, prec, k):
+    import torch
+
+    from paper_2211_15383_amd import dmlmc
+
+    (Lx, Lt), agg, ntv = SHAPES[shape]
+    rng = np.random.default_rng(17)
+
+    def cn(*s):
+        return rng.standard_normal(s) + 1j * rng.standard_normal(s)
+
+    H = dmlmc.Hierarchy(dmlmc.Context(0), rng.normal(0.0, 0.3, (2, Lt, Lx)), 0.1, [agg], [ntv],
+                        import_tv=[cn(2 * Lx * Lt, ntv)])
+    lx, lt, d = H.level_info(2)
+    n = H.n(2)
+    A = H.export(2, Dc=True)["Dc"]
+    m = min(M_DEFL if k else M, n // 2)
+    H.solver_params(coarsest_iters=m, coarsest_iters_defl=m)
+    g5 = np.tile(np.repeat([1.0, -1.0], d // 2), n // d)
+    defl = None
+    if k:
+        X = np.linalg.qr(cn(n, k))[0]
+        lam = np.array([0.3, -0.4, 0.5, -0.7])
+        defl = dmlmc.Deflation(H, 2, k, import_X=X, import_lambda=lam)
+        H.set_deflation(defl)
+    b = cn(3, n)
+    b[1] = 0.0
+    mixed = prec == "mixed"
+    dt = torch.complex64 if mixed else torch.complex128
+    bd = torch.as_tensor(b, device="cuda").to(dt)
+    x = H.apply(dmlmc.OP_VCYCLE, 2, bd, torch.full_like(bd, float("nan")),
+                prec=dmlmc.MIXED if mixed else dmlmc.FP64).cpu().numpy().astype(np.complex128)
+    b = bd.cpu().numpy().astype(np.complex128)
+    # FP32: vectors rounded to 6e-8, operator sums of up to 5 d products, m steps, a condition
+    # number of the projected matrix of order 10: 24 * 5e-7 * 10; FP64: 2^-29 of it
+    tol = 2e-4 if mixed else 1e-11
+    for r in range(3):
+        ref, rhs = np.zeros(n, dtype=np.complex128), b[r]
+        if k:
+            W = g5[:, None] * X
+            c = W.conj().T @ rhs
+            ref, rhs = X @ (c / lam), rhs - W @ c
+        ref = ref + _gmres(lambda v: _blocks_apply(A, lx, lt, v), rhs, m)
+        if r == 1:
+            assert np.array_equal(x[r], np.zeros(n))
+        else:
+            assert np.linalg.norm(x[r] - ref) <= tol * np.linalg.norm(ref), (shape, prec, k, r)
