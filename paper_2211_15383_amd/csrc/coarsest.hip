@@ -30,6 +30,7 @@
 #include <algorithm>
 
 #include "coarsest.h"
+#include "givens.h"
 #include "wave.h"
 
 namespace {
@@ -274,87 +275,6 @@ __device__ __forceinline__ double small_sum(double v, double* red) {
   return s;
 }
 
-// a b with the roundings of the two-launch kernels' complex products: the first product of
-// each part fused onto the second (IM_HX: which of the imaginary part's products is fused)
-template <bool IM_HX>
-__device__ __forceinline__ c128 cprod(c128 a, c128 b) {
-  const double re = fma(a.x, b.x, -(a.y * b.y));
-  return cmk(re, IM_HX ? fma(a.x, b.y, a.y * b.x) : fma(a.y, b.x, a.x * b.y));
-}
-
-// Applies rotations 0 .. j-1 to column j of H (complex, the subdiagonal entry real), forms
-// rotation j and takes g through it: the operations of hessenberg_update (gram.hip), in every
-// lane of the calling wavefront alike.
-__device__ __forceinline__ void small_rotate(c128* col, double* rc, c128* rs, c128* g, int j) {
-  c128 a = col[0];
-#pragma unroll 4
-  for (int i = 0; i < j; ++i) {
-    const c128 b = col[i + 1], s = rs[i];
-    const double c = rc[i];
-    const c128 sb = cprod<false>(s, b);
-    col[i] = cmk(fma(a.x, c, sb.x), fma(a.y, c, sb.y));
-    a = cmk(fma(c, b.x, -fma(a.x, s.x, a.y * s.y)), fma(c, b.y, -fma(a.y, s.x, -(a.x * s.y))));
-  }
-  const double aa = sqrt(fma(a.x, a.x, a.y * a.y)), beta = col[j + 1].x;
-  const double rho = sqrt(fma(beta, beta, aa * aa));
-  double c = 1.0;
-  c128 s = cmk(0.0, 0.0), diag = cmk(0.0, 0.0);
-  if (rho != 0.0) {
-    if (aa == 0.0) {
-      c = 0.0;
-      s = cmk(1.0, 0.0);
-      diag = cmk(beta, 0.0);
-    } else {
-      const c128 ph = cmk(a.x / aa, a.y / aa);
-      c = aa / rho;
-      s = (beta / rho) * ph;
-      diag = rho * ph;
-    }
-  }
-  const c128 gj = g[j];
-  __builtin_amdgcn_wave_barrier();
-  col[j] = diag;
-  rc[j] = c;
-  rs[j] = s;
-  g[j] = c * gj;
-  g[j + 1] = cmk(-fma(s.x, gj.x, s.y * gj.y), -fma(s.x, gj.y, -(s.y * gj.x)));  // -conj(s) g_j
-}
-
-__device__ __forceinline__ c128 lane_value(c128 v, int lane) {
-  return cmk(__hiloint2double(__builtin_amdgcn_readlane(__double2hiint(v.x), lane),
-                              __builtin_amdgcn_readlane(__double2loint(v.x), lane)),
-             __hiloint2double(__builtin_amdgcn_readlane(__double2hiint(v.y), lane),
-                              __builtin_amdgcn_readlane(__double2loint(v.y), lane)));
-}
-
-// One wavefront: g <- R^-1 g, R the rotated Hessenberg matrix (column c at H + c (m + 1)), by
-// back substitution in backsub_kernel's order (solver.hip); zero pivots give zero coefficients.
-// Lane c holds g_c, then y_c.
-__device__ void small_backsub(const c128* H, c128* g, int m) {
-  const int c = threadIdx.x & 63;
-  const c128* col = H + (c < m ? c : 0) * (m + 1);
-  c128 mine = g[c < m ? c : 0];
-  c128 h = col[m - 1];
-  for (int i = m - 1; i >= 0; --i) {
-    const c128 hi = h;
-    if (i > 0) h = col[i - 1];
-    // lane l > i: R[i][l] y_l; zero beyond the last column, so that four at a time may overrun
-    const c128 term = c < m ? cprod<false>(hi, mine) : cmk(0.0, 0.0);
-    c128 acc = mine;
-    for (int l = i + 1; l < m; l += 4) {
-      const c128 t0 = lane_value(term, l), t1 = lane_value(term, l + 1), t2 = lane_value(term, l + 2),
-                 t3 = lane_value(term, l + 3);
-      acc = ((acc - t0) - t1) - t2;
-      acc = acc - t3;
-    }
-    const double dd = fma(hi.x, hi.x, hi.y * hi.y);
-    if (c == i)
-      mine = dd > 0.0 ? cmk(fma(acc.x, hi.x, acc.y * hi.y) / dd, fma(acc.y, hi.x, -(acc.x * hi.y)) / dd)
-                      : cmk(0.0, 0.0);
-  }
-  if (c < m) g[c] = mine;
-}
-
 // The dots of the one-workgroup step of gram.hip on complex-FP32 vectors of at most 2048
 // entries, in its order: thread t has the pair of entries 2t, 2t + 1, a wavefront tree per
 // basis vector, then the wavefronts one after the other.  raw[i] = <u_i, w>; ends with a
@@ -514,7 +434,10 @@ __global__ __launch_bounds__(CS_THREADS) void coarsest_small_kernel(SmallArgs a)
   for (int j = 0; j < m; ++j) {
     const int nb = j + 1;
     // the last wavefront rotates the previous column while the others stream the operator
-    if (j > 0 && tid >= CS_THREADS - 64) small_rotate(S.H + (j - 1) * (m + 1), S.rc, S.rs, S.g, j - 1);
+    if (j > 0 && tid >= CS_THREADS - 64) {
+      c128* prev = S.H + (j - 1) * (m + 1);
+      givens_column(prev, prev[j].x, S.rc, S.rs, S.g, j - 1);
+    }
     if constexpr (LDSA)
       small_op<D16>(a, Al, u, w, part);
     else
@@ -579,9 +502,10 @@ __global__ __launch_bounds__(CS_THREADS) void coarsest_small_kernel(SmallArgs a)
     __syncthreads();
   }
   if (tid < 64) {
-    small_rotate(S.H + (m - 1) * (m + 1), S.rc, S.rs, S.g, m - 1);
+    c128* last = S.H + (m - 1) * (m + 1);
+    givens_column(last, last[m].x, S.rc, S.rs, S.g, m - 1);
     __builtin_amdgcn_wave_barrier();
-    small_backsub(S.H, S.g, m);
+    givens_backsub(S.H, m + 1, S.g, m);
   }
   __syncthreads();
   if (tid < m) S.cf[tid] = S.sc[tid] * S.g[tid];

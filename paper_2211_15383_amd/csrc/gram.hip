@@ -9,16 +9,18 @@
 //   A: h_i = s_i <u_i, w>                (read U, w)
 //   B: u_{j+1} = w - sum_i h_i s_i u_i, ||u_{j+1}||^2, Hessenberg column, Givens, s_{j+1}
 //
-// Small vectors (n <= 16384, the coarsest levels) take the single-pass step in one
-// 1024-thread workgroup per RHS: dots, reduction, update, norm and the Givens step in
-// one launch, the basis re-read from L2.
+// Small vectors (n <= 16384, the coarsest levels) take the single-pass step in two launches
+// of 16 single-wavefront workgroups per RHS and a small finish (which a fixed-count solve
+// leaves to the next step's first launch).
 //
 // Reductions: each workgroup reduces in LDS; with one workgroup per RHS the workgroup
 // finishes the pass itself, otherwise it writes partial sums and a small kernel (one
 // workgroup per RHS) adds them in a fixed order.  No atomics or device-scope fences.
 #include <cmath>
 
+#include "givens.h"
 #include "solver.h"
+#include "wave.h"
 
 namespace {
 
@@ -44,12 +46,6 @@ struct Fin {
   double* invb = nullptr;
 };
 
-__device__ __forceinline__ double wave_sum(double v) {
-#pragma unroll
-  for (int off = 32; off > 0; off >>= 1) v += __shfl_xor(v, off, 64);
-  return v;
-}
-
 // acc[0..nv) summed over the 256-thread block into red[0..nv) (LDS); all threads return
 // after red is complete.
 template <int NV>
@@ -58,7 +54,7 @@ __device__ void block_reduce(const double (&acc)[NV], int nv, double* lds /* [4]
 #pragma unroll
   for (int q = 0; q < NV; ++q) {
     if (q < nv) {
-      const double v = wave_sum(acc[q]);
+      const double v = wave::sum(acc[q]);
       if (l == 0) lds[w * NVMAX + q] = v;
     }
   }
@@ -68,83 +64,69 @@ __device__ void block_reduce(const double (&acc)[NV], int nv, double* lds /* [4]
   __syncthreads();
 }
 
-// Hessenberg column j (col rows 0..j hold the Gram-Schmidt coefficients) and beta:
-// previous rotations, a new rotation, g and the residual estimate.
-__device__ void hessenberg_update(const Fin& f, int r, double beta) {
-  const int m = f.m, j = f.j;
-  c128* col = f.H + (int64_t)r * (m + 1) * m + (int64_t)j * (m + 1);
-  for (int i = 0; i < j; ++i) {
-    const double c = f.cs[r * m + i];
-    const c128 s = f.sn[r * m + i];
-    const c128 a = col[i], b = col[i + 1];
-    col[i] = c * a + s * b;
-    col[i + 1] = c * b - conj(s) * a;
+// Shared memory of a step's finish: the Hessenberg column and the rotations before it
+struct ColumnLds {
+  c128 col[NBMAX + 1], rs[NBMAX + 1], g[NBMAX + 2];
+  double rc[NBMAX + 1];
+};
+
+// Completes step j of RHS r from the column in c.col[0..j] and beta (the first wavefront does
+// the work, the whole block calls it): earlier rotations, a new one, g and the residual
+// estimate.  Ends without a barrier.
+__device__ __forceinline__ void complete_column(const Fin& f, int r, ColumnLds& c, double beta) {
+  const int l = threadIdx.x, j = f.j, m = f.m;
+  if (l < j) {
+    c.rc[l] = f.cs[r * m + l];
+    c.rs[l] = f.sn[r * m + l];
   }
-  const c128 a = col[j];
-  const double aa = sqrt(cabs2(a));
-  const double rho = sqrt(aa * aa + beta * beta);
-  double c;
-  c128 s;
-  if (rho == 0.0) {
-    c = 1.0;
-    s = cmk(0.0, 0.0);
-    col[j] = cmk(0.0, 0.0);
-  } else if (aa == 0.0) {
-    c = 0.0;
-    s = cmk(1.0, 0.0);
-    col[j] = cmk(beta, 0.0);
-  } else {
-    const c128 ph = cmk(a.x / aa, a.y / aa);
-    c = aa / rho;
-    s = (beta / rho) * ph;
-    col[j] = rho * ph;
+  if (l == j) c.g[j] = f.g[(int64_t)r * (m + 1) + j];
+  __syncthreads();
+  if (l < 64) givens_column(c.col, beta, c.rc, c.rs, c.g, j);
+  __syncthreads();
+  if (l <= j) f.H[(int64_t)r * (m + 1) * m + (int64_t)j * (m + 1) + l] = c.col[l];
+  if (l == 0) {
+    f.cs[r * m + j] = c.rc[j];
+    f.sn[r * m + j] = c.rs[j];
+    f.g[(int64_t)r * (m + 1) + j] = c.g[j];
+    f.g[(int64_t)r * (m + 1) + j + 1] = c.g[j + 1];
+    f.res[r] = sqrt(fma(c.g[j + 1].x, c.g[j + 1].x, c.g[j + 1].y * c.g[j + 1].y));
   }
-  f.cs[r * m + j] = c;
-  f.sn[r * m + j] = s;
-  c128* gr = f.g + (int64_t)r * (m + 1);
-  const c128 gj = gr[j];
-  gr[j + 1] = cmk(-(s.x * gj.x + s.y * gj.y), -(s.x * gj.y - s.y * gj.x));  // -conj(s) g_j
-  gr[j] = c * gj;
-  f.res[r] = sqrt(cabs2(gr[j + 1]));
 }
 
-// Completes a pass for RHS r from the reduced sums red[0..nv) (whole block calls it).
+// Completes a pass for RHS r from the reduced sums red[0..nv) in LDS (whole block calls it).
 __device__ void finish_pass(const Fin& f, int r, int nv, const double* red) {
-  const int nb = f.j + 1;
+  __shared__ ColumnLds c;
+  const int nb = f.j + 1, l = threadIdx.x;
   switch (f.mode) {
     case FIN_STORE:
-      for (int q = threadIdx.x; q < nv; q += blockDim.x) f.out[(int64_t)r * f.ostride + q] = red[q];
+      for (int q = l; q < nv; q += blockDim.x) f.out[(int64_t)r * f.ostride + q] = red[q];
       break;
     case FIN_SCALED:
-      for (int i = threadIdx.x; i < nb; i += blockDim.x) {
+      for (int i = l; i < nb; i += blockDim.x) {
         const double sc = f.scale[(int64_t)i * f.nrhs + r];
         f.h[(int64_t)r * f.hld + i] = cmk(red[2 * i] * sc, red[2 * i + 1] * sc);
       }
       break;
-    case FIN_CGS2:
-      if (threadIdx.x == 0) {
-        c128* col = f.H + (int64_t)r * (f.m + 1) * f.m + (int64_t)f.j * (f.m + 1);
-        double h2n = 0.0;
-        for (int i = 0; i < nb; ++i) {
-          const c128 b2 = cmk(red[2 * i], red[2 * i + 1]);
-          h2n += b2.x * b2.x + b2.y * b2.y;
-          f.h[(int64_t)r * f.hld + i] = b2;
-          col[i] = f.h1[(int64_t)r * f.hld + i] + b2;
-        }
-        const double beta = sqrt(fmax(f.nrm2[r] - h2n, 0.0));
-        hessenberg_update(f, r, beta);
-        f.invb[r] = beta > 0.0 ? 1.0 / beta : 0.0;
+    case FIN_CGS2: {
+      if (l < nb) {
+        const c128 b2 = cmk(red[2 * l], red[2 * l + 1]);
+        f.h[(int64_t)r * f.hld + l] = b2;
+        c.col[l] = f.h1[(int64_t)r * f.hld + l] + b2;
       }
+      double h2n = 0.0;
+      for (int i = 0; i < nb; ++i) h2n += red[2 * i] * red[2 * i] + red[2 * i + 1] * red[2 * i + 1];
+      const double beta = sqrt(fmax(f.nrm2[r] - h2n, 0.0));
+      complete_column(f, r, c, beta);
+      if (l == 0) f.invb[r] = beta > 0.0 ? 1.0 / beta : 0.0;
       break;
-    case FIN_CGS1:
-      if (threadIdx.x == 0) {
-        const double beta = sqrt(fmax(red[0], 0.0));
-        f.scale[(int64_t)nb * f.nrhs + r] = beta > 0.0 ? 1.0 / beta : 0.0;
-        c128* col = f.H + (int64_t)r * (f.m + 1) * f.m + (int64_t)f.j * (f.m + 1);
-        for (int i = 0; i < nb; ++i) col[i] = f.h1[(int64_t)r * f.hld + i];
-        hessenberg_update(f, r, beta);
-      }
+    }
+    case FIN_CGS1: {
+      const double beta = sqrt(fmax(red[0], 0.0));
+      if (l < nb) c.col[l] = f.h1[(int64_t)r * f.hld + l];
+      complete_column(f, r, c, beta);
+      if (l == 0) f.scale[(int64_t)nb * f.nrhs + r] = beta > 0.0 ? 1.0 / beta : 0.0;
       break;
+    }
   }
 }
 
@@ -161,14 +143,18 @@ __device__ void reduce_or_partial(const double (&acc)[NV], int nv, double* lds, 
   }
 }
 
-// One wavefront per RHS: lane l adds the partials of blocks l, l + 64, ... into four
-// running sums (blocks l + 256 i + 64 u go to sum u, so that four loads are in flight and
-// no add waits on the previous one), then the wavefront sums across lanes.
-__global__ __launch_bounds__(64) void partial_finish_kernel(const double* __restrict__ part, int G, int nv, Fin f) {
+// One workgroup per RHS, value q by wavefront q mod FINISH_WAVES: lane l adds the partials of
+// blocks l, l + 64, ... into four running sums (blocks l + 256 i + 64 u go to sum u, so that
+// four loads are in flight and no add waits on the previous one), then the wavefront sums
+// across lanes.  (One wavefront for all values took 10.6 us at 24 values, 4 blocks.)
+constexpr int FINISH_WAVES = 8;
+
+__global__ __launch_bounds__(64 * FINISH_WAVES) void partial_finish_kernel(const double* __restrict__ part, int G,
+                                                                           int nv, Fin f) {
   __shared__ double red[NVMAX];
-  const int r = blockIdx.x, l = threadIdx.x;
+  const int r = blockIdx.x, l = threadIdx.x & 63;
   const double* base = part + (int64_t)r * G * nv;
-  for (int q = 0; q < nv; ++q) {
+  for (int q = threadIdx.x >> 6; q < nv; q += FINISH_WAVES) {
     double s0 = 0.0, s1 = 0.0, s2 = 0.0, s3 = 0.0;
     int g = l;
     for (; g + 192 < G; g += 256) {
@@ -178,8 +164,7 @@ __global__ __launch_bounds__(64) void partial_finish_kernel(const double* __rest
       s3 += base[(int64_t)(g + 192) * nv + q];
     }
     for (; g < G; g += 64) s0 += base[(int64_t)g * nv + q];
-    double s = (s0 + s1) + (s2 + s3);
-    s = wave_sum(s);
+    const double s = wave::sum((s0 + s1) + (s2 + s3));
     if (l == 0) red[q] = s;
   }
   __syncthreads();
@@ -385,128 +370,166 @@ __global__ __launch_bounds__(256) void gs1_update_kernel(c64* __restrict__ U, in
   reduce_or_partial(acc, 1, lds, red, part, f, r);
 }
 
-// Sums v[0..15] over the 64 lanes of a wavefront by recursive halving: at each exchange a
-// lane keeps half of its values and adds the partner's copy of that half (17 shuffles
-// instead of 96).  Lane l ends with the total of value (l >> 2) & 15 in v[0].
-__device__ __forceinline__ void wave_sum16(double (&v)[16]) {
-  const int lane = threadIdx.x & 63;
+// ---------------------------------------------------------------- single-pass form, n <= 16384
+// The vectors fit a workgroup of 1024 threads (element pair p belongs to thread p % 1024), and
+// the sums are those of such a workgroup: each thread's pairs in order, a tree over each
+// wavefront's lanes, the wavefronts one after the other.  The 16 wavefronts are workgroups of
+// their own (SPLIT_WAVES x RHS of them, so that the basis streams through many CUs): one launch
+// leaves the dots' partial sums, the next adds them up in the fixed order, updates the vector and
+// leaves the norm's, which the step's finish (or the next step's dots launch) adds up.
+// Measured over 24 steps at n = 4096, 20 RHS: the step in one workgroup per RHS took 22 us (one
+// CU's L2 rate), these two launches 4.5 + 5.2 us; at n = 16384, 32 RHS, 15.4 us against 6.0 + 4.9
+// and 4.1 for the finish.
+constexpr int SPLIT_WAVES = 16;
+constexpr int SPLIT_CHUNK = 8;  // basis vectors per workgroup of the dots launch
+
+// beta = ||u_{j+1}|| from the wavefronts' sums, its scale, and column j through the Givens
+// rotations (one wavefront per RHS)
+__device__ __forceinline__ void split_finish(const Fin& f, int r, const double* __restrict__ npart) {
+  __shared__ ColumnLds c;
+  const int l = threadIdx.x, j = f.j;
+  const double part = l < SPLIT_WAVES ? npart[(int64_t)r * SPLIT_WAVES + l] : 0.0;
+  if (l <= j) c.col[l] = f.h[(int64_t)r * f.hld + l];
+  double sum = 0.0;
 #pragma unroll
-  for (int step = 0; step < 4; ++step) {
-    const int half = 8 >> step;
-    const int mask = 32 >> step;
-    const bool hi = (lane & mask) != 0;
-#pragma unroll
-    for (int i = 0; i < 8; ++i) {
-      if (i < half) {
-        const double a = v[i], b = v[half + i];
-        const double send = hi ? a : b;
-        const double recv = __shfl_xor(send, mask, 64);
-        v[i] = (hi ? b : a) + recv;
-      }
-    }
-  }
-  v[0] += __shfl_xor(v[0], 2, 64);
-  v[0] += __shfl_xor(v[0], 1, 64);
+  for (int k = 0; k < SPLIT_WAVES; ++k)
+    sum += __hiloint2double(__builtin_amdgcn_readlane(__double2hiint(part), k),
+                            __builtin_amdgcn_readlane(__double2loint(part), k));
+  const double beta = sqrt(fmax(sum, 0.0));
+  complete_column(f, r, c, beta);
+  if (l == 0) f.scale[(int64_t)(j + 1) * f.nrhs + r] = beta > 0.0 ? 1.0 / beta : 0.0;
 }
 
-// Whole single-pass step for RHS blockIdx.x in one workgroup of 1024 threads; element
-// pair p of the vectors belongs to thread p % 1024 (PPT pairs per thread, n <= 2048 PPT).
-constexpr int FUSED_THREADS = 1024;
-constexpr int FUSED_PPT = 8;
-constexpr int FUSED_CHUNK = 8;  // basis vectors per reduction round (16 doubles: wave_sum16)
-
+// part[(r 16 + wave) 64 + 2 i + (0: re, 1: im)] = the wavefront's sum of <u_i, w>, i in the
+// chunk blockIdx.z.  Blocks x = 16, z = 0 (where launched) complete the previous step (prev)
+// beside.  (A wavefront per 64 pairs meeting in LDS, as in the update: 5.8 us against 4.3 at
+// n = 4096.)
 template <typename RW>
-__global__ __launch_bounds__(FUSED_THREADS) void gs1_fused_kernel(c64* __restrict__ U, int nb,
-                                                                  const Cx<RW>* __restrict__ w, int64_t n,
-                                                                  int64_t vstride, const double* __restrict__ wscale,
-                                                                  Fin f, int64_t ld) {
-  constexpr int NW = FUSED_THREADS / 64;
-  __shared__ double lds[NW][2 * FUSED_CHUNK];
-  __shared__ double red[NVMAX];
-  __shared__ c128 cf[NBMAX];  // h_i s_i, the coefficients of the unnormalised u_i
-  const int r = blockIdx.x;
-  const int tid = threadIdx.x, lane = tid & 63, wv = tid >> 6;
-  const int nrhs = f.nrhs;
-  const double ws = wscale ? wscale[r] : 1.0;
-  const int64_t np = n / 2, vs = vstride / 2;
+__global__ __launch_bounds__(64) void gs1_split_dots_kernel(const c64* __restrict__ U, int nb,
+                                                            const Cx<RW>* __restrict__ w, int64_t n, int64_t vstride,
+                                                            double* __restrict__ part,
+                                                            const double* __restrict__ npart, Fin prev, int64_t ld) {
+  const int r = blockIdx.y, lane = threadIdx.x;
+  if (blockIdx.x == SPLIT_WAVES) {
+    if (blockIdx.z == 0) split_finish(prev, r, npart);
+    return;
+  }
+  const int c0 = SPLIT_CHUNK * blockIdx.z;
   const Pair<RW>* wr = reinterpret_cast<const Pair<RW>*>(w + (int64_t)r * ld);
   const Pair<float>* Ur = reinterpret_cast<const Pair<float>*>(U + (int64_t)r * ld);
-  // h_i = s_i <u_i, ws w>, FUSED_CHUNK basis vectors per reduction round (w is re-read
-  // from L2 per round rather than held in registers)
-  for (int c0 = 0; c0 < nb; c0 += FUSED_CHUNK) {
-    double acc[2 * FUSED_CHUNK];
+  const int64_t np = n / 2, vs = vstride / 2;
+  double acc[2 * SPLIT_CHUNK];
 #pragma unroll
-    for (int q = 0; q < 2 * FUSED_CHUNK; ++q) acc[q] = 0.0;
+  for (int q = 0; q < 2 * SPLIT_CHUNK; ++q) acc[q] = 0.0;
 #pragma unroll 2
-    for (int q = 0; q < FUSED_PPT; ++q) {
-      const int64_t p = tid + (int64_t)q * FUSED_THREADS;
-      if (p < np) {
-        const Pair<RW> b = wr[p];
+  for (int64_t p = 64 * blockIdx.x + lane; p < np; p += 64 * SPLIT_WAVES) {
+    const Pair<RW> b = wr[p];
+    Pair<float> u[SPLIT_CHUNK];
 #pragma unroll
-        for (int i = 0; i < FUSED_CHUNK; ++i) {
-          if (c0 + i < nb) {
-            const Pair<float> u = Ur[(c0 + i) * vs + p];
-            acc[2 * i] += (double)u.a.x * b.a.x + (double)u.a.y * b.a.y + (double)u.b.x * b.b.x +
-                          (double)u.b.y * b.b.y;
-            acc[2 * i + 1] += (double)u.a.x * b.a.y - (double)u.a.y * b.a.x + (double)u.b.x * b.b.y -
-                              (double)u.b.y * b.b.x;
-          }
-        }
+    for (int i = 0; i < SPLIT_CHUNK; ++i)
+      if (c0 + i < nb) u[i] = Ur[(c0 + i) * vs + p];
+#pragma unroll
+    for (int i = 0; i < SPLIT_CHUNK; ++i) {
+      if (c0 + i < nb) {
+        acc[2 * i] += (double)u[i].a.x * b.a.x + (double)u[i].a.y * b.a.y + (double)u[i].b.x * b.b.x +
+                      (double)u[i].b.y * b.b.y;
+        acc[2 * i + 1] += (double)u[i].a.x * b.a.y - (double)u[i].a.y * b.a.x + (double)u[i].b.x * b.b.y -
+                          (double)u[i].b.y * b.b.x;
       }
     }
-    wave_sum16(acc);
-    if ((lane & 3) == 0) lds[wv][(lane >> 2) & 15] = acc[0];
-    __syncthreads();
-    if (tid < 2 * FUSED_CHUNK && c0 + tid / 2 < nb) {
-      double sum = 0.0;
-      for (int k = 0; k < NW; ++k) sum += lds[k][tid];
-      red[2 * c0 + tid] = sum;
-    }
-    __syncthreads();
   }
-  if (tid < nb) {
-    const double sc = f.scale[(int64_t)tid * nrhs + r];
-    const c128 h = cmk(ws * sc * red[2 * tid], ws * sc * red[2 * tid + 1]);
-    f.h[(int64_t)r * f.hld + tid] = h;
-    cf[tid] = cmk(h.x * sc, h.y * sc);
-  }
-  __syncthreads();
-  // u_{j+1} = ws w - sum_i (h_i s_i) u_i, its norm from the stored FP32 values
-  Pair<float>* out = reinterpret_cast<Pair<float>*>(U + (int64_t)nb * vstride + (int64_t)r * ld);
-  double nrm = 0.0;
+  const double s = wave::sum16(acc);
+  if ((lane & 3) == 0) part[((int64_t)r * SPLIT_WAVES + blockIdx.x) * NVMAX + 2 * c0 + (lane >> 2)] = s;
+}
+
+// h_i = s_w s_i <u_i, w> from the partial sums, u_{j+1} = s_w w - sum_i h_i s_i u_i on the
+// wavefront's pairs, npart[r 16 + wave] = their part of ||u_{j+1}||^2 (of the stored values).
+// A wavefront per 64 pairs (q-th of the workgroup: pairs 1024 q + 64 wave ..), the basis loads
+// out before the sums are ready.
+template <typename RW>
+__global__ __launch_bounds__(512) void gs1_split_update_kernel(c64* __restrict__ U, int nb,
+                                                               const Cx<RW>* __restrict__ w, int64_t n,
+                                                               int64_t vstride, const double* __restrict__ wscale,
+                                                               const double* __restrict__ part,
+                                                               double* __restrict__ npart, Fin f, int64_t ld) {
+  constexpr int CH = 16;
+  __shared__ double cf[2 * NBMAX];  // h_i s_i
+  __shared__ double nq[8][64];
+  const int r = blockIdx.y, lane = threadIdx.x & 63, q = threadIdx.x >> 6;
+  const double ws = wscale ? wscale[r] : 1.0;
+  const Pair<RW>* wr = reinterpret_cast<const Pair<RW>*>(w + (int64_t)r * ld);
+  const Pair<float>* Ur = reinterpret_cast<const Pair<float>*>(U + (int64_t)r * ld);
+  const int64_t np = n / 2, vs = vstride / 2, p = 64 * (SPLIT_WAVES * q + blockIdx.x) + lane;
+  const int64_t pl = p < np ? p : 0;  // idle lanes load pair 0
+  const Pair<RW> b = wr[pl];
+  Pair<float> u[CH];
 #pragma unroll
-  for (int q = 0; q < FUSED_PPT; ++q) {
-    const int64_t p = tid + (int64_t)q * FUSED_THREADS;
-    if (p < np) {
-      const Pair<RW> b = wr[p];
-      double v0x = ws * b.a.x, v0y = ws * b.a.y, v1x = ws * b.b.x, v1y = ws * b.b.y;
-      for (int i = 0; i < nb; ++i) {
-        const Pair<float> u = Ur[i * vs + p];
-        const c128 hi = cf[i];
-        v0x -= hi.x * (double)u.a.x - hi.y * (double)u.a.y;
-        v0y -= hi.x * (double)u.a.y + hi.y * (double)u.a.x;
-        v1x -= hi.x * (double)u.b.x - hi.y * (double)u.b.y;
-        v1y -= hi.x * (double)u.b.y + hi.y * (double)u.b.x;
-      }
-      Pair<float> st;
-      st.a = cmk((float)v0x, (float)v0y);
-      st.b = cmk((float)v1x, (float)v1y);
-      out[p] = st;
-      nrm += (double)st.a.x * st.a.x + (double)st.a.y * st.a.y + (double)st.b.x * st.b.x + (double)st.b.y * st.b.y;
-    }
-  }
-  nrm = wave_sum(nrm);
-  if (lane == 0) lds[wv][0] = nrm;
-  __syncthreads();
-  if (tid == 0) {
+  for (int i = 0; i < CH; ++i)
+    if (i < nb) u[i] = Ur[i * vs + pl];
+  if (threadIdx.x < 2 * nb) {
+    const double* pr = part + (int64_t)r * SPLIT_WAVES * NVMAX + lane;
+    double v[SPLIT_WAVES];
+#pragma unroll
+    for (int k = 0; k < SPLIT_WAVES; ++k) v[k] = pr[k * NVMAX];
+    const double sc = f.scale[(int64_t)(lane >> 1) * f.nrhs + r];
     double sum = 0.0;
-    for (int k = 0; k < NW; ++k) sum += lds[k][0];
-    const double beta = sqrt(fmax(sum, 0.0));
-    f.scale[(int64_t)nb * nrhs + r] = beta > 0.0 ? 1.0 / beta : 0.0;
-    c128* col = f.H + (int64_t)r * (f.m + 1) * f.m + (int64_t)f.j * (f.m + 1);
-    for (int i = 0; i < nb; ++i) col[i] = f.h[(int64_t)r * f.hld + i];
-    hessenberg_update(f, r, beta);
+#pragma unroll
+    for (int k = 0; k < SPLIT_WAVES; ++k) sum += v[k];
+    const double h = ws * sc * sum;
+    if (blockIdx.x == 0) reinterpret_cast<double*>(f.h + (int64_t)r * f.hld)[lane] = h;
+    cf[lane] = h * sc;
   }
+  __syncthreads();
+  c128 v0 = cmk(ws * b.a.x, ws * b.a.y), v1 = cmk(ws * b.b.x, ws * b.b.y);
+  for (int c0 = 0; c0 < nb; c0 += CH) {
+    if (c0 > 0) {
+#pragma unroll
+      for (int i = 0; i < CH; ++i)
+        if (c0 + i < nb) u[i] = Ur[(c0 + i) * vs + pl];
+    }
+#pragma unroll
+    for (int i = 0; i < CH; ++i) {
+      if (c0 + i < nb) {
+        const c128 h = cmk(cf[2 * (c0 + i)], cf[2 * (c0 + i) + 1]);
+        v0 = v0 - cprod<true>(h, ccast<double>(u[i].a));
+        v1 = v1 - cprod<true>(h, ccast<double>(u[i].b));
+      }
+    }
+  }
+  Pair<float> st;
+  st.a = ccast<float>(v0);
+  st.b = ccast<float>(v1);
+  if (p < np) reinterpret_cast<Pair<float>*>(U + (int64_t)nb * vstride + (int64_t)r * ld)[p] = st;
+  const double s =
+      (double)st.a.x * st.a.x + (double)st.a.y * st.a.y + (double)st.b.x * st.b.x + (double)st.b.y * st.b.y;
+  nq[q][lane] = p < np ? s : 0.0;
+  __syncthreads();
+  if (q == 0) {  // a lane's pairs in order, then the wavefront's tree
+    double nrm = 0.0;
+    for (int k = 0; k < (int)(blockDim.x >> 6); ++k) nrm += nq[k][lane];
+    nrm = wave::sum(nrm);
+    if (lane == 0) npart[(int64_t)r * SPLIT_WAVES + blockIdx.x] = nrm;
+  }
+}
+
+__global__ __launch_bounds__(64) void gs1_split_finish_kernel(const double* __restrict__ npart, Fin f) {
+  split_finish(f, blockIdx.x, npart);
+}
+
+// y = R^-1 g over the first k columns, times scale[i][r] where given (one wavefront per RHS)
+__global__ __launch_bounds__(64) void solution_kernel(int k, int m, const c128* __restrict__ H,
+                                                      const c128* __restrict__ g, const double* __restrict__ scale,
+                                                      c128* __restrict__ y, int nrhs) {
+  __shared__ c128 Hs[NBMAX * NBMAX], gs[NBMAX];
+  const int r = blockIdx.x, l = threadIdx.x;
+  const c128* Hr = H + (int64_t)r * (m + 1) * m;
+#pragma unroll 4
+  for (int e = l; e < k * k; e += 64) Hs[e] = Hr[(e / k) * (m + 1) + e % k];
+  if (l < k) gs[l] = g[(int64_t)r * (m + 1) + l];
+  __syncthreads();
+  givens_backsub(Hs, k, gs, k);
+  __syncthreads();
+  if (l < k) y[r * m + l] = scale ? scale[(int64_t)l * nrhs + r] * gs[l] : gs[l];
 }
 
 // Workgroups per RHS: about 8 element pairs per thread (two passes of four), at most
@@ -522,7 +545,7 @@ int gs_blocks(int64_t n, int nrhs) {
 
 void launch_partial_finish(dmlmc_ctx* ctx, const double* part, int G, int nv, const Fin& f, int nrhs) {
   if (G <= 1) return;
-  hipLaunchKernelGGL(partial_finish_kernel, dim3(nrhs), dim3(64), 0, ctx->stream, part, G, nv, f);
+  hipLaunchKernelGGL(partial_finish_kernel, dim3(nrhs), dim3(64 * FINISH_WAVES), 0, ctx->stream, part, G, nv, f);
   LAUNCH_CHECK();
 }
 
@@ -596,8 +619,26 @@ void arnoldi_step(dmlmc_ctx* ctx, Cx<RV>* V, c128* w, int j, int64_t n, int nrhs
   }
 }
 
-// One Arnoldi step, single-pass form on an unnormalised complex-FP32 basis.
-int64_t gs_fused_max_n() { return 2 * (int64_t)FUSED_THREADS * FUSED_PPT; }
+// Partial sums of the split single-pass step: [nrhs][SPLIT_WAVES][NVMAX] and [nrhs][SPLIT_WAVES]
+static double* split_partials(dmlmc_ctx* ctx, int nrhs) {
+  ctx->scratch_dots.ensure(sizeof(double) * (size_t)nrhs * SPLIT_WAVES * (NVMAX + 1));
+  return ctx->scratch_dots.as<double>();
+}
+
+void arnoldi_finish_deferred(dmlmc_ctx* ctx, double* scale, int j, int nrhs, const KrylovArrays& k) {
+  Fin f = base_fin(k, j, nrhs);
+  f.h = k.h1;
+  f.scale = scale;
+  hipLaunchKernelGGL(gs1_split_finish_kernel, dim3(nrhs), dim3(64), 0, ctx->stream,
+                     split_partials(ctx, nrhs) + (size_t)nrhs * SPLIT_WAVES * NVMAX, f);
+  LAUNCH_CHECK();
+}
+
+void krylov_solution(dmlmc_ctx* ctx, const KrylovArrays& k, int iters, int nrhs, const double* scale) {
+  REQUIRE(iters >= 1 && iters <= NBMAX, "Krylov basis larger than the Gram-Schmidt limit");
+  hipLaunchKernelGGL(solution_kernel, dim3(nrhs), dim3(64), 0, ctx->stream, iters, k.m, k.H, k.g, scale, k.y, nrhs);
+  LAUNCH_CHECK();
+}
 
 double* gs_partials(dmlmc_ctx* ctx, int64_t n, int nrhs, int extra_G) {
   const int G = std::max(gs_blocks(n, nrhs), extra_G);
@@ -607,23 +648,37 @@ double* gs_partials(dmlmc_ctx* ctx, int64_t n, int nrhs, int extra_G) {
 
 template <typename RW>
 void arnoldi_step_cgs1(dmlmc_ctx* ctx, c64* U, double* scale, const Cx<RW>* w, int j, int64_t n, int nrhs,
-                       const KrylovArrays& k, const double* wscale, int64_t ld, int dots_G) {
+                       const KrylovArrays& k, const double* wscale, int64_t ld, int dots_G, bool deferred) {
   const int nb = j + 1;
   if (nb > NBMAX) throw DmlmcError(DMLMC_EINVAL, "Krylov basis larger than the Gram-Schmidt limit");
   if (ld <= 0) ld = n;
   REQUIRE(ld >= n && ld % 2 == 0, "Gram-Schmidt vectors need an even stride of at least their length");
   const int64_t vstride = (int64_t)nrhs * ld;
-  if (n <= 2 * (int64_t)FUSED_THREADS * FUSED_PPT) {
+  if (n <= GS_SPLIT_MAX_N) {
     Fin f = base_fin(k, j, nrhs);
-    f.mode = FIN_CGS1;
     f.h = k.h1;
     f.scale = scale;
-    KTimer kt(ctx, "gs_fused", (double)nrhs * n * ((2 * nb + 1) * sizeof(c64) + sizeof(Cx<RW>)));
-    hipLaunchKernelGGL((gs1_fused_kernel<RW>), dim3(nrhs), dim3(FUSED_THREADS), 0, ctx->stream, U, nb, w, n, vstride,
-                       wscale, f, ld);
+    Fin prev = f;
+    prev.j = j - 1;
+    const bool chained = deferred && j > 0;  // the previous step's finish rides on the dots launch
+    double* part = split_partials(ctx, nrhs);
+    double* npart = part + (size_t)nrhs * SPLIT_WAVES * NVMAX;
+    const unsigned per_lane = (unsigned)ceil_div(n, 2 * 64 * SPLIT_WAVES);  // pairs, at most 8
+    KTimer kt(ctx, "gs_fused", (double)nrhs * n * ((2 * nb + 1) * sizeof(c64) + 2 * sizeof(Cx<RW>)));
+    const dim3 dgrid(SPLIT_WAVES + (chained ? 1 : 0), nrhs, (unsigned)ceil_div(nb, SPLIT_CHUNK));
+    hipLaunchKernelGGL((gs1_split_dots_kernel<RW>), dgrid, dim3(64), 0, ctx->stream, U, nb, w, n, vstride, part, npart,
+                       prev, ld);
     LAUNCH_CHECK();
+    hipLaunchKernelGGL((gs1_split_update_kernel<RW>), dim3(SPLIT_WAVES, nrhs), dim3(64 * per_lane), 0, ctx->stream, U,
+                       nb, w, n, vstride, wscale, part, npart, f, ld);
+    LAUNCH_CHECK();
+    if (!deferred) {
+      hipLaunchKernelGGL(gs1_split_finish_kernel, dim3(nrhs), dim3(64), 0, ctx->stream, npart, f);
+      LAUNCH_CHECK();
+    }
     return;
   }
+  REQUIRE(!deferred, "the finish of a long vector's Gram-Schmidt step is not deferred");
   const int G = gs_blocks(n, nrhs);
   double* part = gs_partials(ctx, n, nrhs, dots_G);
   dim3 grid(G, nrhs);
@@ -679,6 +734,6 @@ void arnoldi_step_cgs1(dmlmc_ctx* ctx, c64* U, double* scale, const Cx<RW>* w, i
 template void arnoldi_step<double>(dmlmc_ctx*, c128*, c128*, int, int64_t, int, const KrylovArrays&);
 template void arnoldi_step<float>(dmlmc_ctx*, c64*, c128*, int, int64_t, int, const KrylovArrays&);
 template void arnoldi_step_cgs1<float>(dmlmc_ctx*, c64*, double*, const c64*, int, int64_t, int, const KrylovArrays&,
-                                       const double*, int64_t, int);
+                                       const double*, int64_t, int, bool);
 template void arnoldi_step_cgs1<double>(dmlmc_ctx*, c64*, double*, const c128*, int, int64_t, int,
-                                        const KrylovArrays&, const double*, int64_t, int);
+                                        const KrylovArrays&, const double*, int64_t, int, bool);

@@ -38,17 +38,22 @@ void arnoldi_step(dmlmc_ctx* ctx, Cx<RV>* V, c128* w, int j, int64_t n, int nrhs
 // i at i * nrhs * ld.
 // dots_G > 0: the dots were already formed as dots_G block partials per RHS in the buffer
 // gs_partials returns (launch_wilson_dots); only their sums and the update remain.
+// deferred (n <= GS_SPLIT_MAX_N): the scale, the rotations and the residual estimate of step j
+// are completed by step j + 1 or arnoldi_finish_deferred; nothing else may use the context's
+// partial-sum buffer in between.
 template <typename RW>
 void arnoldi_step_cgs1(dmlmc_ctx* ctx, c64* U, double* scale, const Cx<RW>* w, int j, int64_t n, int nrhs,
-                       const KrylovArrays& k, const double* wscale = nullptr, int64_t ld = 0, int dots_G = 0);
+                       const KrylovArrays& k, const double* wscale = nullptr, int64_t ld = 0, int dots_G = 0,
+                       bool deferred = false);
+// Completes step j (the last) of steps made with deferred.
+void arnoldi_finish_deferred(dmlmc_ctx* ctx, double* scale, int j, int nrhs, const KrylovArrays& k);
 // The context's Gram-Schmidt partial-sum buffer, large enough for the passes on vectors of
 // length n and for extra_G block partials per RHS (its address stays valid for both).
 double* gs_partials(dmlmc_ctx* ctx, int64_t n, int nrhs, int extra_G);
-// Vectors longer than this take the multi-workgroup Gram-Schmidt passes.
-int64_t gs_fused_max_n();
-void krylov_solution(dmlmc_ctx* ctx, const KrylovArrays& k, int iters, int nrhs);
-// y[r][i] *= scale[i][r] for i < iters
-void krylov_scale_y(dmlmc_ctx* ctx, const KrylovArrays& k, const double* scale, int iters, int nrhs);
+// Vectors longer than this take the Gram-Schmidt passes over many workgroups.
+constexpr int64_t GS_SPLIT_MAX_N = 16384;
+// y[r] = R^-1 g of the first iters columns, times scale[i][r] where given
+void krylov_solution(dmlmc_ctx* ctx, const KrylovArrays& k, int iters, int nrhs, const double* scale = nullptr);
 template <typename RZ, typename RX>
 // x = sum_i y_i Z_i, or x += sum_i y_i Z_i (in FP64) when accumulate; Z_i holds RHS r at
 // i * nrhs * ldz + r * ldz, x at r * ldx (0: n)

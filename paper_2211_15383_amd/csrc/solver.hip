@@ -58,28 +58,6 @@ __global__ void init_cycle_kernel(const double* __restrict__ nrm2, c128* __restr
   res[r] = beta;
 }
 
-// y = R^-1 g over the first k columns (upper triangular, zero pivots give zero).
-__global__ void backsub_kernel(int k, int m, const c128* __restrict__ H, const c128* __restrict__ g,
-                               c128* __restrict__ y, int nrhs) {
-  const int r = blockIdx.x * blockDim.x + threadIdx.x;
-  if (r >= nrhs) return;
-  const c128* Hr = H + (int64_t)r * (m + 1) * m;
-  for (int i = k - 1; i >= 0; --i) {
-    c128 acc = g[(int64_t)r * (m + 1) + i];
-    for (int l = i + 1; l < k; ++l) acc = acc - Hr[l * (m + 1) + i] * y[r * m + l];
-    const c128 d = Hr[i * (m + 1) + i];
-    const double dd = cabs2(d);
-    y[r * m + i] = dd > 0.0 ? cmk((acc.x * d.x + acc.y * d.y) / dd, (acc.y * d.x - acc.x * d.y) / dd)
-                            : cmk(0.0, 0.0);
-  }
-}
-
-__global__ void scale_y_kernel(c128* __restrict__ y, int m, const double* __restrict__ scale, int iters, int nrhs) {
-  const int r = blockIdx.x * blockDim.x + threadIdx.x;
-  if (r >= nrhs) return;
-  for (int i = 0; i < iters; ++i) y[r * m + i] = scale[(int64_t)i * nrhs + r] * y[r * m + i];
-}
-
 // v_out (RV) = w * invb[r]
 template <typename RV>
 __global__ void scale_store_kernel(const c128* __restrict__ w, const double* __restrict__ invb, Cx<RV>* __restrict__ v,
@@ -236,17 +214,6 @@ void krylov_init(dmlmc_ctx* ctx, const KrylovArrays& k, int nrhs) {
   LAUNCH_CHECK();
 }
 
-void krylov_scale_y(dmlmc_ctx* ctx, const KrylovArrays& k, const double* scale, int iters, int nrhs) {
-  hipLaunchKernelGGL(scale_y_kernel, dim3(ceil_div(nrhs, 64)), dim3(64), 0, ctx->stream, k.y, k.m, scale, iters, nrhs);
-  LAUNCH_CHECK();
-}
-
-void krylov_solution(dmlmc_ctx* ctx, const KrylovArrays& k, int iters, int nrhs) {
-  hipLaunchKernelGGL(backsub_kernel, dim3(ceil_div(nrhs, 64)), dim3(64), 0, ctx->stream, iters, k.m, k.H, k.g, k.y,
-                     nrhs);
-  LAUNCH_CHECK();
-}
-
 template <typename RZ, typename RX>
 void launch_combine(dmlmc_ctx* ctx, const Cx<RZ>* Z, int iters, const KrylovArrays& k, Cx<RX>* x, int64_t n,
                     int nrhs, bool accumulate, int64_t ldz, int64_t ldx) {
@@ -320,13 +287,15 @@ void coarsest_gmres(dmlmc_hier* H, int l, const Cx<R>* b_in, Cx<R>* x, int nrhs)
     c64* U = (c64*)V;
     HIPCHK(hipMemcpyAsync(U, b, sizeof(c64) * (size_t)vstride, hipMemcpyDeviceToDevice, ctx->stream));
     HIPCHK(hipMemcpyAsync(scale, k.invb, sizeof(double) * nrhs, hipMemcpyDeviceToDevice, ctx->stream));
+    const bool deferred = n <= GS_SPLIT_MAX_N;
     for (int j = 0; j < m; ++j) {
       // D (s_j u_j) = s_j (D u_j): the scale enters the Gram-Schmidt step
       apply_op<float>(ctx, L, U + j * vstride, (c64*)wr, nrhs);
-      arnoldi_step_cgs1<float>(ctx, U, scale, (const c64*)wr, j, n, nrhs, k, scale + (int64_t)j * nrhs);
+      arnoldi_step_cgs1<float>(ctx, U, scale, (const c64*)wr, j, n, nrhs, k, scale + (int64_t)j * nrhs, 0, 0,
+                               deferred);
     }
-    krylov_solution(ctx, k, m, nrhs);
-    krylov_scale_y(ctx, k, scale, m, nrhs);
+    if (deferred) arnoldi_finish_deferred(ctx, scale, m - 1, nrhs, k);
+    krylov_solution(ctx, k, m, nrhs, scale);
   } else {
     c128* w = (c128*)hier_buf(H, "cg_w", l, sizeof(c128) * (size_t)nrhs * n);
     launch_cast<double, R>(ctx, b, w, n, nrhs, n, n);
@@ -454,7 +423,7 @@ int fgmres_cycle(dmlmc_hier* H, int l, const c128* r, const double* rnorm2, c128
       // update takes y_j s_j
       // on the fine level the operator pass also forms the Gram-Schmidt dots (one read of
       // the new vector less)
-      const bool fused = L.fine && n > gs_fused_max_n() && j + 1 <= 8;
+      const bool fused = L.fine && n > GS_SPLIT_MAX_N && j + 1 <= 8;
       run_graphed(H, key, [&]() {
         vcycle<RP>(H, l, (const Cx<RP>*)(U + j * vstride), zj, nrhs, ldw);
         if (fused) {
@@ -481,8 +450,7 @@ int fgmres_cycle(dmlmc_hier* H, int l, const c128* r, const double* rnorm2, c128
     }
     if (done) break;
   }
-  krylov_solution(ctx, k, it, nrhs);
-  if (f32) krylov_scale_y(ctx, k, scale, it, nrhs);
+  krylov_solution(ctx, k, it, nrhs, scale);
   launch_combine<RP, double>(ctx, Z, it, k, x, n, nrhs, true, ldw, n);
   return it;
 }

@@ -1522,8 +1522,10 @@ void launch_coarse(dmlmc_ctx* ctx, const Level& L, const Cx<R>* x, Cx<R>* y, int
             "matrix-core coarse stencil needs 16-byte aligned RHS rows");
     // built-in rule: whole-line traffic staged through LDS (measured at 1024^2 with the
     // swizzled LDS rows: 65536 sites 290 -> 267 us, 4096 sites 21.9 -> 20.1 us, 1024 sites
-    // 8.0 -> 7.0 us against the best of the other forms)
-    const int split = L.kv[KV_COARSE_SPLIT] > 0 ? L.kv[KV_COARSE_SPLIT] : 3;
+    // 8.0 -> 7.0 us against the best of the other forms); below 1024 sites two wavefronts per
+    // site without the staging, whose latency is what such a launch takes (256 sites, 20 RHS:
+    // 7.6 -> 5.8 us)
+    const int split = L.kv[KV_COARSE_SPLIT] > 0 ? L.kv[KV_COARSE_SPLIT] : (V < 1024 ? 2 : 3);
     dim3 grid((unsigned)ceil_div(V * (split == 2 ? 2 : 1), 4));
     if (split == 3) {
       if (gamma5_left)

@@ -1,4 +1,5 @@
-"""Fixed-count GMRES of small coarsest levels (one launch up to 2048 entries) against numpy.
+"""Fixed-count GMRES of coarsest levels against numpy: one launch up to 2048 entries, split
+Gram-Schmidt steps up to 16384, passes over many workgroups beyond.
 
 dmlmc_apply(OP_VCYCLE) at the coarsest level is the coarsest solve alone: x = e0 + GMRES_m(r)
 with r = b - W W^H b, e0 = X Lambda^-1 W^H b for an attached deflation (r = b, e0 = 0
@@ -20,6 +21,8 @@ SHAPES = {
     "50x24": ((20, 40), (4, 4), 12),   # 1200: more than 16 dofs
     "128x16": ((64, 32), (4, 4), 8),   # 2048: the largest in one launch
     "132x16": ((48, 44), (4, 4), 8),   # 2112: the first in separate launches
+    "1024x16": ((128, 128), (4, 4), 8),  # 16384: the largest with split Gram-Schmidt steps
+    "1056x16": ((132, 128), (4, 4), 8),  # 16896: the first with the passes of long vectors
 }
 
 
