@@ -30,8 +30,7 @@ struct KrylovArrays {
 };
 KrylovArrays krylov_arrays(dmlmc_hier* H, const char* prefix, int level, int m, int nrhs);
 void krylov_init(dmlmc_ctx* ctx, const KrylovArrays& k, int nrhs);
-template <typename RV>
-void arnoldi_step(dmlmc_ctx* ctx, Cx<RV>* V, c128* w, int j, int64_t n, int nrhs, const KrylovArrays& k);
+void arnoldi_step(dmlmc_ctx* ctx, c128* V, c128* w, int j, int64_t n, int nrhs, const KrylovArrays& k);
 // Single-pass form: unnormalised complex-FP32 basis u_i with scales s_i = 1/||u_i||
 // (scale[i][nrhs]); the new vector is wscale[r] * w (wscale NULL: factor 1), w complex
 // FP32 or FP64; FP64 arithmetic.  U and w hold RHS r at r * ld (ld = 0: n), basis vector

@@ -297,13 +297,12 @@ void coarsest_gmres(dmlmc_hier* H, int l, const Cx<R>* b_in, Cx<R>* x, int nrhs)
     if (deferred) arnoldi_finish_deferred(ctx, scale, m - 1, nrhs, k);
     krylov_solution(ctx, k, m, nrhs, scale);
   } else {
-    c128* w = (c128*)hier_buf(H, "cg_w", l, sizeof(c128) * (size_t)nrhs * n);
-    launch_cast<double, R>(ctx, b, w, n, nrhs, n, n);
-    launch_scale_store<R>(ctx, w, k.invb, V, n, nrhs);
+    c128* V64 = (c128*)V;
+    c128* w = (c128*)wr;
+    launch_scale_store<double>(ctx, (const c128*)b, k.invb, V64, n, nrhs);
     for (int j = 0; j < m; ++j) {
-      apply_op<R>(ctx, L, V + j * vstride, wr, nrhs);
-      launch_cast<double, R>(ctx, wr, w, n, nrhs, n, n);
-      arnoldi_step<R>(ctx, V, w, j, n, nrhs, k);
+      apply_op<double>(ctx, L, V64 + j * vstride, w, nrhs);
+      arnoldi_step(ctx, V64, w, j, n, nrhs, k);
     }
     krylov_solution(ctx, k, m, nrhs);
   }
@@ -439,7 +438,7 @@ int fgmres_cycle(dmlmc_hier* H, int l, const c128* r, const double* rnorm2, c128
     } else {
       vcycle<RP>(H, l, (const Cx<RP>*)(V + j * vstride), zj, nrhs);
       apply_op<RP>(ctx, L, zj, (Cx<RP>*)w, nrhs);
-      arnoldi_step<double>(ctx, V, w, j, n, nrhs, k);
+      arnoldi_step(ctx, V, w, j, n, nrhs, k);
     }
     it = j + 1;
     readback(ctx, {{k.res, res_host.data(), sizeof(double) * nrhs}});

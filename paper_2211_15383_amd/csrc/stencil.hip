@@ -121,14 +121,22 @@ __global__ __launch_bounds__(256) void wilson_kernel(const Cx<R>* __restrict__ U
   }
 }
 
+// The scalar kernels below ask for CHUNK block (or interpolation) entries and their vector
+// entries before the first product, so that a thread waits for memory once per chunk; the
+// products keep their order.
+constexpr int CHUNK = 8;
+constexpr int CHUNK1 = 16;  // where a thread has one right-hand side
+
 // Coarse block stencil: y_s = sum_dir A[s][dir] x_{s+dir}; blocks column-major
 // (A[s][dir][j * d + i] = row i, column j).  Thread per (site, row), RB right-hand sides
-// per thread so that every block entry is loaded once per RB vectors.
+// per thread so that every block entry is loaded once per RB vectors.  Measured at 256 sites,
+// 16 dofs, FP64, one RHS: 17 us with a load and its product at a time on 16 workgroups, 7.6 us.
 template <typename R, int RB, bool G5, typename RO = R>
 __global__ __launch_bounds__(256) void coarse_kernel(const Cx<R>* __restrict__ A, const Cx<R>* __restrict__ in,
                                                      Cx<RO>* __restrict__ out, int Lx, int Lt, int d, int spb,
                                                      int nrhs, int64_t ldx, int64_t ldy,
                                                      const Cx<R>* __restrict__ sub) {
+  constexpr int CH = RB == 1 ? CHUNK1 : CHUNK;
   const int64_t V = (int64_t)Lx * Lt;
   const int i = threadIdx.x % d;
   const int64_t s = (int64_t)blockIdx.x * spb + threadIdx.x / d;
@@ -141,14 +149,28 @@ __global__ __launch_bounds__(256) void coarse_kernel(const Cx<R>* __restrict__ A
 #pragma unroll
   for (int q = 0; q < RB; ++q) acc[q] = cmk((R)0, (R)0);
   const Cx<R>* Ab = A + s * 5 * d * d;
+#pragma unroll
   for (int dir = 0; dir < 5; ++dir) {
     const Cx<R>* Ad = Ab + dir * d * d + i;
-    const int64_t base = sites[dir] * d;
-    for (int j = 0; j < d; ++j) {
-      const Cx<R> a = Ad[j * d];
+    const Cx<R>* xd = in + r0 * ldx + sites[dir] * d;
+    for (int j0 = 0; j0 < d; j0 += CH) {
+      Cx<R> a[CH], x[RB][CH];
 #pragma unroll
-      for (int q = 0; q < RB; ++q) {
-        if (q < nr) cfma(acc[q], a, in[(r0 + q) * ldx + base + j]);
+      for (int j = 0; j < CH; ++j) {
+        if (j0 + j < d) {
+          a[j] = Ad[(j0 + j) * d];
+#pragma unroll
+          for (int q = 0; q < RB; ++q)
+            if (q < nr) x[q][j] = xd[q * ldx + j0 + j];
+        }
+      }
+#pragma unroll
+      for (int j = 0; j < CH; ++j) {
+        if (j0 + j < d) {
+#pragma unroll
+          for (int q = 0; q < RB; ++q)
+            if (q < nr) cfma(acc[q], a[j], x[q][j]);
+        }
       }
     }
   }
@@ -325,14 +347,26 @@ __global__ __launch_bounds__(256) void coarse_gs_kernel(const Cx<R>* __restrict_
     Cx<R> acc = cmk((R)0, (R)0);
     if (active) {
       acc = b[r * ld + s * d + i];
+#pragma unroll
       for (int dir = 0; dir < 5; ++dir) {
         const Cx<R>* Ad = Ab + dir * d * d + i;
-        const int64_t base = sites[dir] * d;
-        for (int j = 0; j < d; ++j) {
-          const Cx<R> a = Ad[j * d];
-          const Cx<R> v = xr[base + j];
-          acc.x -= a.x * v.x - a.y * v.y;
-          acc.y -= a.x * v.y + a.y * v.x;
+        const Cx<R>* xd = xr + sites[dir] * d;
+        for (int j0 = 0; j0 < d; j0 += CHUNK1) {
+          Cx<R> a[CHUNK1], v[CHUNK1];
+#pragma unroll
+          for (int j = 0; j < CHUNK1; ++j) {
+            if (j0 + j < d) {
+              a[j] = Ad[(j0 + j) * d];
+              v[j] = xd[j0 + j];
+            }
+          }
+#pragma unroll
+          for (int j = 0; j < CHUNK1; ++j) {
+            if (j0 + j < d) {
+              acc.x -= a[j].x * v[j].x - a[j].y * v[j].y;
+              acc.y -= a[j].x * v[j].y + a[j].y * v[j].x;
+            }
+          }
         }
       }
     }
@@ -342,6 +376,7 @@ __global__ __launch_bounds__(256) void coarse_gs_kernel(const Cx<R>* __restrict_
     if (active) {
       Cx<R> e = cmk((R)0, (R)0);
       const Cx<R>* Ai = Ainv + s * d * d + i;
+#pragma unroll CHUNK1
       for (int j = 0; j < d; ++j) cfma(e, Ai[j * d], res[ls * d + j]);
       Cx<R>* xw = x + r * ld + s * d + i;
       *xw = *xw + e;
@@ -374,16 +409,34 @@ __global__ __launch_bounds__(256) void restrict_kernel(const Cx<R>* __restrict__
 #pragma unroll
   for (int q = 0; q < RB; ++q) acc[q] = cmk((R)0, (R)0);
   const Cx<R>* xr = xf + (int64_t)r0 * ldf;
-  int row = 0;
-  for (int lt = 0; lt < at; ++lt) {
-    const int64_t srow = (int64_t)(T * at + lt) * Lxf + (int64_t)X * ax;
-    for (int lx = 0; lx < ax; ++lx) {
-      const int64_t fbase = (srow + lx) * df + c * h;
-      for (int j = 0; j < h; ++j, ++row) {
-        const Cx<R> pv = Pb[(int64_t)row * N];
+  // row = (lx + ax lt) h + j, counted up one by one
+  int lx = 0, lt = 0, j = 0;
+  const int64_t corner = ((int64_t)(T * at) * Lxf + (int64_t)X * ax) * df + c * h;
+  for (int row0 = 0; row0 < rows; row0 += CHUNK) {
+    Cx<R> pv[CHUNK], x[RB][CHUNK];
+#pragma unroll
+    for (int u = 0; u < CHUNK; ++u) {
+      if (row0 + u < rows) {
+        const int64_t f = corner + ((int64_t)lt * Lxf + lx) * df + j;
+        pv[u] = Pb[(int64_t)(row0 + u) * N];
 #pragma unroll
         for (int q = 0; q < RB; ++q)
-          if (q < nr) cfmac(acc[q], pv, xr[q * ldf + fbase + j]);
+          if (q < nr) x[q][u] = xr[q * ldf + f];
+        if (++j == h) {
+          j = 0;
+          if (++lx == ax) {
+            lx = 0;
+            ++lt;
+          }
+        }
+      }
+    }
+#pragma unroll
+    for (int u = 0; u < CHUNK; ++u) {
+      if (row0 + u < rows) {
+#pragma unroll
+        for (int q = 0; q < RB; ++q)
+          if (q < nr) cfmac(acc[q], pv[u], x[q][u]);
       }
     }
   }
@@ -392,7 +445,8 @@ __global__ __launch_bounds__(256) void restrict_kernel(const Cx<R>* __restrict__
     if (q < nr) yc[(int64_t)(r0 + q) * ldc + cs * 2 * N + c * N + k] = acc[q];
 }
 
-// Prolongation x_f (+)= P e_c; thread per (fine dof, group of RB right-hand sides).
+// Prolongation x_f (+)= P e_c; thread per (fine dof, group of RB right-hand sides).  A thread's
+// interpolation row is one request (FP64, 256^2 onto the fine level, 16 RHS: 105 -> 34 us).
 template <typename R, int RB>
 __global__ __launch_bounds__(256) void prolong_kernel(const Cx<R>* __restrict__ P, const Cx<R>* __restrict__ ec,
                                                       Cx<R>* __restrict__ xf, int Lxf, int Ltf, int df, int ax, int at,
@@ -417,11 +471,23 @@ __global__ __launch_bounds__(256) void prolong_kernel(const Cx<R>* __restrict__ 
 #pragma unroll
   for (int q = 0; q < RB; ++q)
     acc[q] = (add && q < nr) ? xf[(int64_t)(r0 + q) * ldf + tid] : cmk((R)0, (R)0);
-  for (int kk = 0; kk < N; ++kk) {
-    const Cx<R> pv = Pr[kk];
+  for (int k0 = 0; k0 < N; k0 += CHUNK) {
+    Cx<R> pv[CHUNK];
 #pragma unroll
-    for (int q = 0; q < RB; ++q)
-      if (q < nr) cfma(acc[q], pv, er[q * ldc + kk]);
+    for (int k = 0; k < CHUNK; ++k)
+      if (k0 + k < N) pv[k] = Pr[k0 + k];
+#pragma unroll
+    for (int q = 0; q < RB; ++q) {
+      if (q < nr) {
+        Cx<R> e[CHUNK];
+#pragma unroll
+        for (int k = 0; k < CHUNK; ++k)
+          if (k0 + k < N) e[k] = er[q * ldc + k0 + k];
+#pragma unroll
+        for (int k = 0; k < CHUNK; ++k)
+          if (k0 + k < N) cfma(acc[q], pv[k], e[k]);
+      }
+    }
   }
 #pragma unroll
   for (int q = 0; q < RB; ++q)
@@ -813,6 +879,54 @@ __global__ __launch_bounds__(256) void coarse16_f64_mfma_kernel(const c128* __re
       if (va) out[(int64_t)ra * ldy + e] = ccast<RO>(sub ? sub[(int64_t)ra * ldx + e] - ya : ya);
       if (vb) out[(int64_t)rb * ldy + e] = ccast<RO>(sub ? sub[(int64_t)rb * ldx + e] - yb : yb);
     }
+  }
+}
+
+// The same on small levels: a wavefront per site and 16-RHS tile (blockIdx.y), every load out
+// before the first product (160 registers; the tiles' results are those of the form above).
+// Measured at 256 sites, 48 RHS (the eigensolver's blocks): 18.1 -> 9.9 us.
+template <bool G5, typename RO = double>
+__global__ __launch_bounds__(256) void coarse16_f64_mfma_tile_kernel(const c128* __restrict__ A,
+                                                                     const c128* __restrict__ in,
+                                                                     Cx<RO>* __restrict__ out, int Lx, int Lt,
+                                                                     int nrhs, int64_t ldx, int64_t ldy,
+                                                                     const c128* __restrict__ sub) {
+  const int64_t V = (int64_t)Lx * Lt;
+  const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
+  const int64_t s = (int64_t)blockIdx.x * 4 + w;
+  if (s >= V) return;  // wave-uniform
+  const int row = lane & 15, kq = lane >> 4;
+  const int prow = 4 * (row & 3) + (row >> 2);
+  const Nbr nb = neighbours(s, Lx, Lt);
+  const int64_t sites[5] = {s, nb.xp, nb.xm, nb.tp, nb.tm};
+  const double sg = (G5 && kq >= 2) ? -1.0 : 1.0;
+  const int r = 16 * blockIdx.y + row;
+  const bool on = r < nrhs;
+  const c128* x = in + (int64_t)min(r, nrhs - 1) * ldx + 4 * kq;
+  const c128* Ab = A + s * 5 * 256 + 64 * kq + prow;
+  c128 a[5][4], u[5][4];
+#pragma unroll
+  for (int dir = 0; dir < 5; ++dir) {
+#pragma unroll
+    for (int t = 0; t < 4; ++t) {
+      a[dir][t] = Ab[dir * 256 + 16 * t];
+      u[dir][t] = x[sites[dir] * 16 + t];
+    }
+  }
+  __builtin_amdgcn_sched_barrier(0);
+  const c128 zero = cmk(0.0, 0.0);
+  f64x4 re = {0.0, 0.0, 0.0, 0.0}, im = re;
+#pragma unroll
+  for (int dir = 0; dir < 5; ++dir) {
+#pragma unroll
+    for (int t = 0; t < 4; ++t) cmfma64(re, im, a[dir][t], on ? u[dir][t] : zero);
+  }
+  if (!on) return;
+#pragma unroll
+  for (int q = 0; q < 4; ++q) {
+    const int64_t e = s * 16 + 4 * kq + q;
+    const c128 y = cmk(sg * re[q], sg * im[q]);
+    out[(int64_t)r * ldy + e] = ccast<RO>(sub ? sub[(int64_t)r * ldx + e] - y : y);
   }
 }
 
@@ -1506,11 +1620,32 @@ int launch_wilson_dots(dmlmc_ctx* ctx, const Level& L, const c64* z, c64* y, int
   return G;
 }
 
+// Sites below which the FP64 matrix-core stencil takes a wavefront per RHS tile
+constexpr int64_t F64_TILE_MAX_SITES = 2048;
+
+// coarse_kernel with RB right-hand sides per thread; workgroups of 64 threads until 256-thread
+// ones would be 2048 (small levels spread over more CUs)
+template <typename R, int RB, typename RO>
+static void launch_coarse_scalar(dmlmc_ctx* ctx, const Level& L, const Cx<R>* A, const Cx<R>* x, Cx<RO>* y, int nrhs,
+                                 int64_t ldx, int64_t ldy, bool gamma5_left, const Cx<R>* sub) {
+  const int d = L.dofs;
+  const int64_t V = L.sites();
+  const int threads = ceil_div(V * d, 256) * ceil_div(nrhs, RB) >= 2048 ? 256 : 64;
+  const int spb = std::max(1, threads / d);
+  const dim3 grid((unsigned)ceil_div(V, spb), (unsigned)ceil_div(nrhs, RB)), block((unsigned)(spb * d));
+  if (gamma5_left)
+    hipLaunchKernelGGL((coarse_kernel<R, RB, true, RO>), grid, block, 0, ctx->stream, A, x, y, L.Lx, L.Lt, d, spb, nrhs,
+                       ldx, ldy, (const Cx<R>*)nullptr);
+  else
+    hipLaunchKernelGGL((coarse_kernel<R, RB, false, RO>), grid, block, 0, ctx->stream, A, x, y, L.Lx, L.Lt, d, spb,
+                       nrhs, ldx, ldy, sub);
+  LAUNCH_CHECK();
+}
+
 template <typename R>
 void launch_coarse(dmlmc_ctx* ctx, const Level& L, const Cx<R>* x, Cx<R>* y, int nrhs, int64_t ldx, int64_t ldy,
                    bool gamma5_left, const Cx<R>* sub) {
   const int d = L.dofs;
-  const int spb = std::max(1, 256 / d);
   const int64_t V = L.sites();
   const Cx<R>* A = std::is_same<R, float>::value ? (const Cx<R>*)L.A32.p : (const Cx<R>*)L.A64.p;
   REQUIRE(!(sub && gamma5_left), "the residual form has no Gamma5");
@@ -1555,6 +1690,17 @@ void launch_coarse(dmlmc_ctx* ctx, const Level& L, const Cx<R>* x, Cx<R>* y, int
     // FP64 matrix cores pay from a few RHS on (a 16-wide tile); single vectors keep the
     // scalar kernel
     dim3 grid((unsigned)ceil_div(V, 4));
+    if (V < F64_TILE_MAX_SITES) {
+      grid.y = (unsigned)ceil_div(nrhs, 16);
+      if (gamma5_left)
+        hipLaunchKernelGGL((coarse16_f64_mfma_tile_kernel<true>), grid, dim3(256), 0, ctx->stream, (const c128*)A,
+                           (const c128*)x, (c128*)y, L.Lx, L.Lt, nrhs, ldx, ldy, (const c128*)nullptr);
+      else
+        hipLaunchKernelGGL((coarse16_f64_mfma_tile_kernel<false>), grid, dim3(256), 0, ctx->stream, (const c128*)A,
+                           (const c128*)x, (c128*)y, L.Lx, L.Lt, nrhs, ldx, ldy, (const c128*)sub);
+      LAUNCH_CHECK();
+      return;
+    }
     if (gamma5_left)
       hipLaunchKernelGGL((coarse16_f64_mfma_kernel<true>), grid, dim3(256), 0, ctx->stream, (const c128*)A,
                          (const c128*)x, (c128*)y, L.Lx, L.Lt, nrhs, ldx, ldy, (const c128*)nullptr);
@@ -1564,16 +1710,10 @@ void launch_coarse(dmlmc_ctx* ctx, const Level& L, const Cx<R>* x, Cx<R>* y, int
     LAUNCH_CHECK();
     return;
   }
-  constexpr int RB = 4;
-  dim3 grid((unsigned)ceil_div(V, spb), (unsigned)ceil_div(nrhs, RB));
-  dim3 block((unsigned)(spb * d));
-  if (gamma5_left)
-    hipLaunchKernelGGL((coarse_kernel<R, RB, true>), grid, block, 0, ctx->stream, A, x, y, L.Lx, L.Lt, d, spb, nrhs,
-                       ldx, ldy, (const Cx<R>*)nullptr);
+  if (nrhs == 1)
+    launch_coarse_scalar<R, 1, R>(ctx, L, A, x, y, nrhs, ldx, ldy, gamma5_left, sub);
   else
-    hipLaunchKernelGGL((coarse_kernel<R, RB, false>), grid, block, 0, ctx->stream, A, x, y, L.Lx, L.Lt, d, spb,
-                       nrhs, ldx, ldy, sub);
-  LAUNCH_CHECK();
+    launch_coarse_scalar<R, 4, R>(ctx, L, A, x, y, nrhs, ldx, ldy, gamma5_left, sub);
 }
 
 template <typename R>
@@ -1614,17 +1754,20 @@ void apply_residual_to32(dmlmc_ctx* ctx, const Level& L, const c128* x, const c1
   const int d = L.dofs;
   KTimer kt(ctx, "coarse", vec_bytes + (double)V * 5 * d * d * sizeof(c128));
   if (d == 16 && nrhs >= 8) {
-    hipLaunchKernelGGL((coarse16_f64_mfma_kernel<false, float>), dim3((unsigned)ceil_div(V, 4)), dim3(256), 0,
-                       ctx->stream, L.A64.as<c128>(), x, r, L.Lx, L.Lt, nrhs, ldx, ldr, b);
+    const dim3 grid((unsigned)ceil_div(V, 4), V < F64_TILE_MAX_SITES ? (unsigned)ceil_div(nrhs, 16) : 1u);
+    if (V < F64_TILE_MAX_SITES)
+      hipLaunchKernelGGL((coarse16_f64_mfma_tile_kernel<false, float>), grid, dim3(256), 0, ctx->stream,
+                         L.A64.as<c128>(), x, r, L.Lx, L.Lt, nrhs, ldx, ldr, b);
+    else
+      hipLaunchKernelGGL((coarse16_f64_mfma_kernel<false, float>), grid, dim3(256), 0, ctx->stream, L.A64.as<c128>(),
+                         x, r, L.Lx, L.Lt, nrhs, ldx, ldr, b);
     LAUNCH_CHECK();
     return;
   }
-  constexpr int RB = 4;
-  const int spb = std::max(1, 256 / d);
-  dim3 grid((unsigned)ceil_div(V, spb), (unsigned)ceil_div(nrhs, RB));
-  hipLaunchKernelGGL((coarse_kernel<double, RB, false, float>), grid, dim3((unsigned)(spb * d)), 0, ctx->stream,
-                     L.A64.as<c128>(), x, r, L.Lx, L.Lt, d, spb, nrhs, ldx, ldr, b);
-  LAUNCH_CHECK();
+  if (nrhs == 1)
+    launch_coarse_scalar<double, 1, float>(ctx, L, L.A64.as<c128>(), x, r, nrhs, ldx, ldr, false, b);
+  else
+    launch_coarse_scalar<double, 4, float>(ctx, L, L.A64.as<c128>(), x, r, nrhs, ldx, ldr, false, b);
 }
 
 template <typename R>
@@ -1670,7 +1813,6 @@ void launch_coarse_gs(dmlmc_ctx* ctx, const Level& L, Cx<R>* x, const Cx<R>* b, 
   if (ld <= 0) ld = L.n();
   REQUIRE(ld >= L.n(), "Gauss-Seidel vectors need a stride of at least the level size");
   const int d = L.dofs;
-  const int spb = std::max(1, 256 / d);
   const int64_t V = L.sites();
   const Cx<R>* A = std::is_same<R, float>::value ? (const Cx<R>*)L.A32.p : (const Cx<R>*)L.A64.p;
   const Cx<R>* Ai = std::is_same<R, float>::value ? (const Cx<R>*)L.Ainv32.p : (const Cx<R>*)L.Ainv64.p;
@@ -1712,6 +1854,8 @@ void launch_coarse_gs(dmlmc_ctx* ctx, const Level& L, Cx<R>* x, const Cx<R>* b, 
   }
   KTimer kt(ctx, "coarse_gs",
             (double)nrhs * (V / 2) * d * 4 * sizeof(Cx<R>) + (double)(V / 2) * 6 * d * d * sizeof(Cx<R>));
+  // workgroups of 64 threads until 256-thread ones would be 2048, as in the stencil
+  const int spb = std::max(1, (ceil_div(nsites * d, 256) * ceil_div(nrhs, rb) >= 2048 ? 256 : 64) / d);
   dim3 grid((unsigned)ceil_div(nsites, spb), (unsigned)ceil_div(nrhs, rb));
   dim3 block((unsigned)(spb * d));
   size_t shm = (size_t)spb * d * sizeof(Cx<R>);

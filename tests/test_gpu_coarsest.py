@@ -106,3 +106,34 @@ def test_coarsest_gmres(shape, prec, k):
             assert np.array_equal(x[r], np.zeros(n))
         else:
             assert np.linalg.norm(x[r] - ref) <= tol * np.linalg.norm(ref), (shape, prec, k, r)
+
+
+@pytest.mark.parametrize("nrhs", [1, 3, 8, 17, 33])
+@pytest.mark.parametrize("shape", ["8x2", "60x10", "64x16", "50x24", "132x16"])
+def test_coarse_operator_and_transfers(shape, nrhs):
+    """D, P^H and P of small levels: one right-hand side, the remainders of the groups of 4
+    and 16, FP64 (a matrix-core tile per wavefront from 8 on at 16 dofs) and complex FP32."""
+    import torch
+
+    from paper_2211_15383_amd import dmlmc
+
+    (Lx, Lt), agg, ntv = SHAPES[shape]
+    rng = np.random.default_rng(23)
+
+    def cn(*s):
+        return rng.standard_normal(s) + 1j * rng.standard_normal(s)
+
+    H = dmlmc.Hierarchy(dmlmc.Context(0), rng.normal(0.0, 0.3, (2, Lt, Lx)), 0.1, [agg], [ntv],
+                        import_tv=[cn(2 * Lx * Lt, ntv)])
+    lx, lt, _ = H.level_info(2)
+    P, A = H.export(1, P=True)["P"], H.export(2, Dc=True)["Dc"]
+    xf, xc = cn(nrhs, H.n(1)), cn(nrhs, H.n(2))
+    for prec, dt, tol in ((dmlmc.FP64, torch.complex128, 1e-13), (dmlmc.MIXED, torch.complex64, 1e-6)):
+        f, c = (torch.as_tensor(v, device="cuda").to(dt) for v in (xf, xc))
+        hf, hc = (t.cpu().numpy().astype(np.complex128) for t in (f, c))
+        for op, lv, src, ref in ((dmlmc.OP_D, 2, c, _blocks_apply(A, lx, lt, hc.T).T),
+                                 (dmlmc.OP_RESTRICT, 1, f, hf @ P.conj()),
+                                 (dmlmc.OP_PROLONG, 1, c, hc @ P.T)):
+            out = H.apply(op, lv, src, torch.full(ref.shape, float("nan"), dtype=dt, device="cuda"), prec=prec)
+            err = np.linalg.norm(out.cpu().numpy() - ref, axis=1) / np.linalg.norm(ref, axis=1)
+            assert err.max() <= tol, (shape, nrhs, prec, op, err.max())
