@@ -178,7 +178,6 @@ void dmlmc_destroy(dmlmc_ctx* ctx) {
   ctx->scratch_dots.release();
   ctx->scratch_small.release();
   if (ctx->pinned) (void)hipHostFree(ctx->pinned);
-  if (ctx->readback_event) (void)hipEventDestroy(ctx->readback_event);
   if (ctx->own_stream) (void)hipStreamDestroy(ctx->stream);
   delete ctx;
 }

@@ -10,6 +10,7 @@
 //     path (complex FP32 operator and preconditioner inside the cycle) converges to the
 //     FP64 tolerance.
 #include <algorithm>
+#include <chrono>
 #include <cmath>
 
 #include "coarsest.h"
@@ -17,30 +18,75 @@
 #include "dense.h"
 #include "solver.h"
 
+namespace {
+
+constexpr size_t PINNED_BYTES = 64 * 1024;
+constexpr size_t PINNED_HEAD = 64;  // the sequence word's line
+constexpr int PUBLISH_PARTS = 4;
+
+struct Published {
+  const uint64_t* src[PUBLISH_PARTS];
+  int words[PUBLISH_PARTS];
+  int n;
+};
+
+__global__ __launch_bounds__(256) void publish_kernel(Published p, uint64_t* __restrict__ host,
+                                                      uint64_t* __restrict__ word, uint64_t seq) {
+  int at = 0;
+  for (int k = 0; k < p.n; ++k) {
+    for (int i = threadIdx.x; i < p.words[k]; i += 256) host[at + i] = p.src[k][i];
+    at += p.words[k];
+  }
+  __threadfence_system();
+  __syncthreads();
+  if (threadIdx.x == 0) __hip_atomic_store(word, seq, __ATOMIC_RELEASE, __HIP_MEMORY_SCOPE_SYSTEM);
+}
+
+void publish_and_wait(dmlmc_ctx* ctx, const Published& p) {
+  if (!ctx->pinned) {
+    HIPCHK(hipHostMalloc(&ctx->pinned, PINNED_BYTES, hipHostMallocDefault));
+    std::memset(ctx->pinned, 0, PINNED_HEAD);
+    ctx->published = 0;
+  }
+  uint64_t* word = static_cast<uint64_t*>(ctx->pinned);
+  const uint64_t seq = ++ctx->published;
+  hipLaunchKernelGGL(publish_kernel, dim3(1), dim3(256), 0, ctx->stream, p,
+                     reinterpret_cast<uint64_t*>(static_cast<char*>(ctx->pinned) + PINNED_HEAD), word, seq);
+  LAUNCH_CHECK();
+  const auto t0 = std::chrono::steady_clock::now();
+  for (int spin = 0;; ++spin) {
+    if (__atomic_load_n(word, __ATOMIC_ACQUIRE) == seq) return;
+    if (spin % 256 == 255 && std::chrono::steady_clock::now() - t0 > std::chrono::milliseconds(2)) break;
+  }
+  HIPCHK(hipStreamSynchronize(ctx->stream));  // a long wait: no polling
+  if (__atomic_load_n(word, __ATOMIC_ACQUIRE) != seq)
+    throw DmlmcError(DMLMC_EHIP, "the stream finished without publishing its results");
+}
+
+}  // namespace
+
 void readback(dmlmc_ctx* ctx, std::initializer_list<ReadbackPart> parts) {
+  Published p{};
   size_t total = 0;
-  for (const ReadbackPart& p : parts) total += (p.bytes + 15) / 16 * 16;
-  if (total > ctx->pinned_bytes) {
-    if (ctx->pinned) HIPCHK(hipHostFree(ctx->pinned));
-    ctx->pinned = nullptr;
-    ctx->pinned_bytes = 0;
-    const size_t want = std::max<size_t>(total, 64 * 1024);
-    HIPCHK(hipHostMalloc(&ctx->pinned, want, hipHostMallocDefault));
-    ctx->pinned_bytes = want;
+  for (const ReadbackPart& r : parts) {
+    total += r.bytes;
+    if (p.n < PUBLISH_PARTS) {
+      p.src[p.n] = static_cast<const uint64_t*>(r.dev);
+      p.words[p.n] = (int)(r.bytes / 8);
+    }
+    ++p.n;
   }
-  if (!ctx->readback_event) HIPCHK(hipEventCreateWithFlags(&ctx->readback_event, hipEventDisableTiming));
-  char* stage = static_cast<char*>(ctx->pinned);
-  size_t off = 0;
-  for (const ReadbackPart& p : parts) {
-    HIPCHK(hipMemcpyAsync(stage + off, p.dev, p.bytes, hipMemcpyDeviceToHost, ctx->stream));
-    off += (p.bytes + 15) / 16 * 16;
+  if (p.n > PUBLISH_PARTS || total > PINNED_BYTES - PINNED_HEAD) {
+    for (const ReadbackPart& r : parts)
+      HIPCHK(hipMemcpyAsync(r.host, r.dev, r.bytes, hipMemcpyDeviceToHost, ctx->stream));
+    HIPCHK(hipStreamSynchronize(ctx->stream));
+    return;
   }
-  HIPCHK(hipEventRecord(ctx->readback_event, ctx->stream));
-  HIPCHK(hipEventSynchronize(ctx->readback_event));
-  off = 0;
-  for (const ReadbackPart& p : parts) {
-    std::memcpy(p.host, stage + off, p.bytes);
-    off += (p.bytes + 15) / 16 * 16;
+  publish_and_wait(ctx, p);
+  const char* at = static_cast<const char*>(ctx->pinned) + PINNED_HEAD;
+  for (const ReadbackPart& r : parts) {
+    std::memcpy(r.host, at, r.bytes);
+    at += r.bytes;
   }
 }
 

@@ -142,15 +142,18 @@ def lib() -> C.CDLL:
     return _LIB
 
 
-def _ptr(t) -> int:
-    """Device address of a tensor handed to the library.  The library enqueues on its own
-    stream when torch runs on the default one, so torch's pending work on t's device (which
-    may still be writing t) is waited for before the address is passed on."""
-    if t.is_cuda:
-        import torch
+def _ptrs(*tensors):
+    """Device addresses of tensors handed to the library.  The library enqueues on its own
+    stream when torch runs on the default one, so torch's pending work on the tensors' device
+    (which may still be writing them) is waited for, once, before the addresses are passed on."""
+    waited = None
+    for t in tensors:
+        if t.is_cuda and t.device != waited:
+            import torch
 
-        torch.cuda.current_stream(t.device).synchronize()
-    return t.data_ptr()
+            waited = t.device
+            torch.cuda.current_stream(waited).synchronize()
+    return [t.data_ptr() for t in tensors]
 
 
 # Library objects still alive at interpreter exit are released child-first (deflations,
@@ -225,7 +228,7 @@ class Context:
     def z2_noise(self, n: int, seed: int, level: int, sample0: int, nrhs: int, prec: int = FP64):
         dt = self.torch.complex128 if prec == FP64 else self.torch.complex64
         out = self.torch.empty((nrhs, n), dtype=dt, device=f"cuda:{self.device}")
-        self.check(lib().dmlmc_z2_noise(self.h, n, seed, level, sample0, nrhs, C.c_void_p(_ptr(out)), prec))
+        self.check(lib().dmlmc_z2_noise(self.h, n, seed, level, sample0, nrhs, *_ptrs(out), prec))
         return out
 
 
@@ -310,12 +313,12 @@ class Hierarchy:
         """ld_in / ld_out: strides between the RHS of x / out in complex entries (0: the
         vector's level size); with both 0 this is dmlmc_apply, else dmlmc_apply_strided."""
         nrhs = x.shape[0] if op != OP_PROLONG else out.shape[0]
+        px, po = _ptrs(x, out)
         if ld_in == 0 and ld_out == 0:
-            self.ctx.check(lib().dmlmc_apply(self.ctx.h, self.h, op, level, C.c_void_p(_ptr(x)),
-                                             C.c_void_p(_ptr(out)), nrhs, prec, arg))
+            self.ctx.check(lib().dmlmc_apply(self.ctx.h, self.h, op, level, px, po, nrhs, prec, arg))
         else:
-            self.ctx.check(lib().dmlmc_apply_strided(self.ctx.h, self.h, op, level, C.c_void_p(_ptr(x)), ld_in,
-                                                     C.c_void_p(_ptr(out)), ld_out, nrhs, prec, arg))
+            self.ctx.check(lib().dmlmc_apply_strided(self.ctx.h, self.h, op, level, px, ld_in, po, ld_out, nrhs, prec,
+                                                     arg))
         return out
 
     def work_stride(self, level: int) -> int:
@@ -331,8 +334,7 @@ class Hierarchy:
         X = torch.empty_like(B)
         stats = SolveStats()
         st = lib().dmlmc_solve_multi_rhs(self.ctx.h, self.h, level, proj.h if proj is not None else None,
-                                         C.c_void_p(_ptr(B)), C.c_void_p(_ptr(X)), B.shape[0], B.shape[1], prec,
-                                         rtol, maxiter, C.byref(stats))
+                                         *_ptrs(B, X), B.shape[0], B.shape[1], prec, rtol, maxiter, C.byref(stats))
         if st not in (OK,):
             raise DmlmcError(st, lib().dmlmc_last_error(self.ctx.h).decode())
         return X, stats
@@ -445,8 +447,7 @@ class Deflation:
     def project_noalloc(self, x, out):
         """out = x - W (W^H x) through dmlmc_deflate_project_noalloc (complex128 [nrhs][n]
         tensors on the device; the library allocates nothing for it)."""
-        self.hier.ctx.check(lib().dmlmc_deflate_project_noalloc(self.hier.ctx.h, self.h, C.c_void_p(_ptr(x)),
-                                                                C.c_void_p(_ptr(out)), x.shape[0]))
+        self.hier.ctx.check(lib().dmlmc_deflate_project_noalloc(self.hier.ctx.h, self.h, *_ptrs(x, out), x.shape[0]))
         return out
 
     def export(self):

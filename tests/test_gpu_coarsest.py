@@ -137,3 +137,18 @@ def test_coarse_operator_and_transfers(shape, nrhs):
             out = H.apply(op, lv, src, torch.full(ref.shape, float("nan"), dtype=dt, device="cuda"), prec=prec)
             err = np.linalg.norm(out.cpu().numpy() - ref, axis=1) / np.linalg.norm(ref, axis=1)
             assert err.max() <= tol, (shape, nrhs, prec, op, err.max())
+
+
+def test_block_larger_than_the_readback_buffer():
+    """8200 right-hand sides: their norms (8 bytes each) exceed the pinned staging buffer."""
+    import torch
+
+    from paper_2211_15383_amd import dmlmc
+
+    rng = np.random.default_rng(5)
+    H = dmlmc.Hierarchy(dmlmc.Context(0), rng.normal(0.0, 0.3, (2, 8, 8)), 0.1, [(4, 4)], [2])
+    n = H.n(1)
+    b = torch.as_tensor(rng.standard_normal((8200, n)) + 0j, device="cuda")
+    x, st = H.solve(1, b, prec=dmlmc.FP64, rtol=1e-10)
+    r = b - H.apply(dmlmc.OP_D, 1, x, torch.empty_like(x))
+    assert st.converged and float((r.norm(dim=1) / b.norm(dim=1)).max()) <= 1.01e-10
