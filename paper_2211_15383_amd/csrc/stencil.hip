@@ -66,15 +66,27 @@ __device__ __forceinline__ int64_t xcd_block() {
   return (g & 7) * (full >> 3) + (g >> 3);
 }
 
+// A workgroup of the fine stencil has tiles of TILE_X sites by TILE_T rows, a row per
+// wavefront (tiles_x tiles to a row of them), or, with tiles_x = 0, 256 consecutive sites.
+constexpr int TILE_X = 64, TILE_T = 4;
+
 // Thread per site, RHS [r0, r1) in sequence; the five spinors of RHS r + 1 are requested
-// before RHS r is computed, so a thread always has a full set of loads in flight.
+// before RHS r is computed, so a thread always has a full set of loads in flight.  Bound by
+// memory and by the neighbours' re-reads through L1 and L2: of a tile of 64 x 4 sites two
+// rows of six are fetched by another workgroup as well, of 256 sites in a row two of three.
 template <typename R, bool G5, typename RO = R>
 __global__ __launch_bounds__(256) void wilson_kernel(const Cx<R>* __restrict__ U, const Cx<R>* __restrict__ in,
                                                      Cx<RO>* __restrict__ out, int Lx, int Lt, R diag, int nrhs,
                                                      int rb, int64_t ldx, int64_t ldy,
-                                                     const Cx<R>* __restrict__ sub) {
+                                                     const Cx<R>* __restrict__ sub, int tiles_x) {
   const int64_t V = (int64_t)Lx * Lt;
-  const int64_t s = xcd_block() * blockDim.x + threadIdx.x;
+  int64_t s = xcd_block() * blockDim.x + threadIdx.x;
+  if (tiles_x) {
+    const unsigned blk = (unsigned)xcd_block(), row = blk / (unsigned)tiles_x;
+    const int x = (int)(blk - row * tiles_x) * TILE_X + (threadIdx.x & (TILE_X - 1));
+    const int t = (int)row * TILE_T + threadIdx.x / TILE_X;
+    s = x < Lx && t < Lt ? (int64_t)t * Lx + x : V;
+  }
   if (s >= V) return;
   const Nbr nb = neighbours(s, Lx, Lt);
   const Cx<R> ux = U[s], ut = U[V + s], uxm = U[nb.xm], utm = U[V + nb.tm];
@@ -1575,22 +1587,46 @@ bool restrict16_pair_selected(const Level& L) {
 }
 bool prolong16_pair_selected(const Level& L) { return transfer16_pair_available(L) && prolong_staged_rule(L); }
 
+namespace {
+struct WilsonGrid {
+  unsigned blocks;
+  int tiles_x, rb;
+};
+
+// Tiles where at most an eighth of their threads lies outside the lattice, from 2^15 sites
+// (linear -> tiles, 32 RHS: 1024^2 253 -> 234 us in FP32 and 598 -> 567 in FP64, 400 x 300
+// 38.6 -> 37.0; with a quarter outside, 200 x 180, 18.6 -> 19.5; 128^2 20.0 -> 20.2).
+// Right-hand sides per thread: 8 while input and output (`bytes` an entry pair) fit into
+// the 256 MB last-level cache, as links are then re-read least (1024^2, 4 RHS: 37.9 us, with
+// 2 39.7); beyond it 2, since few streams at a time keep the neighbours' rows in the L2s
+// (768 x 600, 32 RHS: 87.1 -> 79.5 us; 512^2 57.0 -> 53.9).
+WilsonGrid wilson_grid(const Level& L, int nrhs, size_t bytes) {
+  const int64_t V = L.sites(), tx = ceil_div(L.Lx, TILE_X), tt = ceil_div(L.Lt, TILE_T);
+  const bool tiles = V >= 32768 && 8 * (tx * tt * TILE_X * TILE_T) <= 9 * V;
+  WilsonGrid g;
+  g.blocks = (unsigned)(tiles ? tx * tt : ceil_div(V, 256));
+  g.tiles_x = tiles ? (int)tx : 0;
+  const int most = tiles && (double)nrhs * L.n() * bytes > 256e6 ? 2 : 8;
+  g.rb = L.kv[KV_WILSON_RB] > 0 ? std::min(L.kv[KV_WILSON_RB], nrhs) : std::min(most, rhs_block_for(V, nrhs));
+  return g;
+}
+}  // namespace
+
 template <typename R>
 void launch_wilson(dmlmc_ctx* ctx, const Level& L, const Cx<R>* x, Cx<R>* y, int nrhs, int64_t ldx, int64_t ldy,
                    bool gamma5_left, const Cx<R>* sub) {
   const int64_t V = L.sites();
-  // at most 8 RHS per thread: more workgroups in flight; links are re-read nrhs / 8 times
-  const int rb = L.kv[KV_WILSON_RB] > 0 ? std::min(L.kv[KV_WILSON_RB], nrhs) : std::min(8, rhs_block_for(V, nrhs));
-  dim3 grid((unsigned)ceil_div(V, 256), (unsigned)ceil_div(nrhs, rb));
+  const WilsonGrid g = wilson_grid(L, nrhs, 2 * sizeof(Cx<R>));
+  const dim3 grid(g.blocks, (unsigned)ceil_div(nrhs, g.rb));
   const Cx<R>* U = std::is_same<R, float>::value ? (const Cx<R>*)L.U32.p : (const Cx<R>*)L.U64.p;
   REQUIRE(!(sub && gamma5_left), "the residual form has no Gamma5");
   KTimer kt(ctx, "wilson", (double)nrhs * V * (sub ? 6 : 4) * sizeof(Cx<R>) + (double)V * 2 * sizeof(Cx<R>));
   if (gamma5_left)
     hipLaunchKernelGGL((wilson_kernel<R, true>), grid, dim3(256), 0, ctx->stream, U, x, y, L.Lx, L.Lt,
-                       (R)(L.m0 + 2.0), nrhs, rb, ldx, ldy, (const Cx<R>*)nullptr);
+                       (R)(L.m0 + 2.0), nrhs, g.rb, ldx, ldy, (const Cx<R>*)nullptr, g.tiles_x);
   else
     hipLaunchKernelGGL((wilson_kernel<R, false>), grid, dim3(256), 0, ctx->stream, U, x, y, L.Lx, L.Lt,
-                       (R)(L.m0 + 2.0), nrhs, rb, ldx, ldy, sub);
+                       (R)(L.m0 + 2.0), nrhs, g.rb, ldx, ldy, sub, g.tiles_x);
   LAUNCH_CHECK();
 }
 
@@ -1743,11 +1779,11 @@ void apply_residual_to32(dmlmc_ctx* ctx, const Level& L, const c128* x, const c1
   // reads x and b (FP64), writes r (complex FP32)
   const double vec_bytes = (double)nrhs * L.n() * (2 * sizeof(c128) + sizeof(c64));
   if (L.fine) {
-    const int rb = std::min(8, rhs_block_for(V, nrhs));
-    dim3 grid((unsigned)ceil_div(V, 256), (unsigned)ceil_div(nrhs, rb));
+    const WilsonGrid g = wilson_grid(L, nrhs, 2 * sizeof(c128));
+    const dim3 grid(g.blocks, (unsigned)ceil_div(nrhs, g.rb));
     KTimer kt(ctx, "wilson", vec_bytes + (double)V * 2 * sizeof(c128));
     hipLaunchKernelGGL((wilson_kernel<double, false, float>), grid, dim3(256), 0, ctx->stream, L.U64.as<c128>(), x,
-                       r, L.Lx, L.Lt, L.m0 + 2.0, nrhs, rb, ldx, ldr, b);
+                       r, L.Lx, L.Lt, L.m0 + 2.0, nrhs, g.rb, ldx, ldr, b, g.tiles_x);
     LAUNCH_CHECK();
     return;
   }

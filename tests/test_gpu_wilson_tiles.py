@@ -1,0 +1,43 @@
+"""The fine stencil where a workgroup has a tile of 64 x 4 sites: from 2^15 sites, at most an
+eighth of the tiles' threads outside the lattice; 2 right-hand sides per thread once input
+and output exceed 256 MB.  Against the oracle's D, with the bounds of the other stencil tests
+(about a dozen roundings per entry)."""
+import numpy as np
+import pytest
+
+from oracle import wilson as ow
+from paper_2211_15383_amd.inputs import link_angles
+
+from _helpers import random_vectors, rel_err, to_dev, to_host
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.mark.parametrize("Lx,Lt,nrhs,precs", [
+    (256, 128, 3, "both"),   # the smallest in tiles: 32768 sites, whole tiles
+    (180, 180, 3, "both"),   # 32400 sites: consecutive sites
+    (184, 180, 9, "both"),   # a ragged last tile
+    (60, 548, 2, "both"),    # one ragged tile across
+    (68, 484, 2, "both"),    # nearly half of the tiles' threads outside: consecutive sites
+    (252, 132, 121, "fp64"),  # 257.6 MB: 2 right-hand sides per thread, an odd last one
+    (252, 132, 241, "mixed"),
+])
+def test_stencil_tiles(gpu, Lx, Lt, nrhs, precs):
+    torch, dm, ctx = gpu
+    theta = link_angles(Lx, Lt, 0.5, Lx * 1000 + Lt)
+    m0 = -0.07
+    H = dm.Hierarchy(ctx, theta, m0, [], [])
+    D = ow.dirac_operator(theta, m0)
+    x = random_vectors(D.shape[0], nrhs, 1)
+    ref = D @ x
+    g5 = np.tile([1.0, -1.0], D.shape[0] // 2)
+    for name, prec, dt, tol in (("fp64", dm.FP64, torch.complex128, 1e-13),
+                                ("mixed", dm.MIXED, torch.complex64, 1e-6)):
+        if precs not in ("both", name):
+            continue
+        xd = to_dev(torch, x, dt)
+        y = torch.empty_like(xd)
+        H.apply(dm.OP_D, 1, xd, y, prec)
+        assert rel_err(to_host(y), ref) < tol, name
+        H.apply(dm.OP_GAMMA5_D, 1, xd, y, prec)
+        assert rel_err(to_host(y), g5[:, None] * ref) < tol, name
