@@ -10,7 +10,9 @@
 //   * operator: a thread per row (column-major blocks, so that a wavefront's loads are
 //     contiguous; the complex-FP32 d = 16 blocks, row-major for the matrix cores, have a
 //     copy by column pairs on levels of this size).  In complex FP64 the contraction is split
-//     over P threads where the rows alone would leave threads idle;
+//     over P threads where the rows alone would leave threads idle.  The short loops are
+//     straight-line where the sizes allow it: a uniform branch for each load and product, and
+//     the integer divisions of the site numbers, took longer than the products;
 //   * Gram-Schmidt as in gram.hip: complex FP32 one pass on the unnormalised basis, complex
 //     FP64 two passes on the normalised one; FP64 arithmetic;
 //   * the last wavefront applies the Givens rotations to a step's Hessenberg column before it
@@ -24,9 +26,10 @@
 // magnify a last-bit change of the coarse operators to 1e-8 in the coarsest samples.
 //
 // Measured (MI355X) against the separate launches: 8 steps with 32 deflation vectors, n = 1024,
-// 32 right-hand sides 228 -> 82 us (a step 18.7 kclk: operator 11.5 of its 10.2 floor, dots 4.1,
-// update 1.9); 24 steps, n = 600 with 10 dofs, 5 right-hand sides 920 -> 195 us; the 16^2 FP64
-// estimate 20.7 -> 5.6 ms, the 128^2 mixed one 39.4 -> 23.4 ms.
+// 32 right-hand sides 228 -> 82 us (a step 18.5 kclk: operator 11.7, of which 10.2 at 64 bytes
+// per clock, dots 3.3, update 1.8); 24 steps, n = 600 with 10 dofs, 5 right-hand sides 920 -> 177 us
+// (operator 6.3 kclk, dots 6.8, update 4.1); complex FP64, 8 steps, n = 128 with 16 deflation
+// vectors 42 us (operator 3.4 kclk; 61 us and 8.5 kclk with the contraction in LDS partial sums).
 #include <algorithm>
 
 #include "coarsest.h"
@@ -38,6 +41,7 @@ namespace {
 constexpr int CS_THREADS = 1024;
 constexpr int CS_WAVES = CS_THREADS / 64;
 constexpr int CS_COLS = 16;    // FP32 operator columns whose loads a thread has in flight (half in FP64)
+constexpr int CS_PAD = 8;      // coefficients of zero past the last basis vector
 constexpr int CS_MAX_M = 31;
 constexpr int CS_MAX_K = SMALL_LEVEL_N / 4;  // deflation vectors
 constexpr size_t CS_LDS = 160 * 1024;  // per workgroup
@@ -81,11 +85,11 @@ struct SmallArgs {
 // spilled registers).  The deflation coefficients are used before the Hessenberg matrix is.
 struct SmallShared {
   union {
-    c128 H[(CS_MAX_M + 1) * CS_MAX_M];
+    c128 H[(CS_MAX_M + 1) * (CS_MAX_M + 3)];  // three columns more for the back substitution
     c128 defl[2][CS_MAX_K];  // W^H b and Lambda^-1 W^H b
   };
   double stage[CS_WAVES * 64];
-  c128 cf[CS_MAX_M + 1], cs[CS_MAX_M + 1], g[CS_MAX_M + 1], rs[CS_MAX_M + 1];
+  c128 cf[CS_MAX_M + 1 + CS_PAD], cs[CS_MAX_M + 1 + CS_PAD], g[CS_MAX_M + 1], rs[CS_MAX_M + 1];
   double sc[CS_MAX_M + 1], rc[CS_MAX_M + 1], red[CS_WAVES];
 };
 
@@ -96,8 +100,12 @@ __host__ __device__ inline size_t small_dynamic(int n, int d, int P, int kl, boo
   return sizeof(Cx<R>) * (size_t)n * (2 + (P > 1 ? P : 0) + kl + (blocks ? 5 * d : 0));
 }
 
+// a / b for 0 <= a < 4096, inv = 1 / b: a + 1/2 is at least 1/(2 b) from the next multiple of b,
+// far beyond the rounding (an integer division takes some 35 instructions)
+__device__ __forceinline__ int quotient(int a, float inv) { return (int)(((float)a + 0.5f) * inv); }
+
 __device__ __forceinline__ void site_neighbours(int s, int Lx, int Lt, int* nb) {
-  const int x = s % Lx, t = s / Lx;
+  const int t = quotient(s, 1.0f / (float)Lx), x = s - t * Lx;
   nb[0] = s;
   nb[1] = (x + 1 == Lx) ? s - (Lx - 1) : s + 1;
   nb[2] = (x == 0) ? s + (Lx - 1) : s - 1;
@@ -128,13 +136,36 @@ __device__ __forceinline__ void mfma_order(c64& acc, const float4 (&m4)[4], cons
   }
 }
 
+// One row of the operator with PAIRS column pairs per direction, straight-line (a uniform
+// branch around each load and product costs more than they do)
+template <int PAIRS>
+__device__ __forceinline__ c64 row_of_pairs(const float4* As, const c64* __restrict__ u, const int (&nb)[5]) {
+  constexpr int d = 2 * PAIRS;
+  c64 acc = cmk(0.f, 0.f);
+#pragma unroll 1
+  for (int dir = 0; dir < 5; ++dir) {
+    const int site = dir == 0 ? nb[0] : dir == 1 ? nb[1] : dir == 2 ? nb[2] : dir == 3 ? nb[3] : nb[4];
+    const float4* ud = reinterpret_cast<const float4*>(u + site * d);
+    float4 m[PAIRS];
+#pragma unroll
+    for (int q = 0; q < PAIRS; ++q) m[q] = As[(dir * PAIRS + q) * d];
+#pragma unroll
+    for (int q = 0; q < PAIRS; ++q) {
+      const float4 v = ud[q];
+      cfma(acc, cmk(m[q].x, m[q].y), cmk(v.x, v.y));
+      cfma(acc, cmk(m[q].z, m[q].w), cmk(v.z, v.w));
+    }
+  }
+  return acc;
+}
+
 // w = D u in complex FP32 (u, w in LDS; blocks by column pairs, in LDS or global memory), a
 // thread per row, in the order of the coarse stencils; ends with a barrier
 template <bool D16>
 __device__ void small_op(const SmallArgs& a, const c64* A, const c64* __restrict__ u, c64* __restrict__ w, c64*) {
   const int d = D16 ? 16 : a.d, pairs = d / 2;
   for (int row = threadIdx.x; row < a.n; row += CS_THREADS) {
-    const int s = row / d;
+    const int s = D16 ? row / 16 : quotient(row, 1.0f / (float)d);
     int nb[5];
     site_neighbours(s, a.Lx, a.Lt, nb);
     // lane i of a site reads entries (i, 2 q), (i, 2 q + 1) as 16 bytes
@@ -159,6 +190,10 @@ __device__ void small_op(const SmallArgs& a, const c64* A, const c64* __restrict
         for (int k = 0; k < 4; ++k) v4[k] = ud[2 * k + 1];
         mfma_order(acc, m1, v4);
       }
+    } else if (pairs == 4) {
+      acc = row_of_pairs<4>(As, u, nb);
+    } else if (pairs == 5) {
+      acc = row_of_pairs<5>(As, u, nb);
     } else {
 #pragma unroll 1
       for (int dir = 0; dir < 5; ++dir) {
@@ -187,39 +222,58 @@ __device__ void small_op(const SmallArgs& a, const c64* A, const c64* __restrict
   __syncthreads();
 }
 
-// The same in complex FP64 (column-major blocks), the 5 d products of a row dealt to P threads
+// The same in complex FP64 (column-major blocks), a row's columns dealt to P threads (P divides
+// d): thread (site, p, i) has columns p, p + P, .. of row i, so that a site's threads read
+// whole columns, and where its d P threads are lanes of one wavefront their sums meet in it
 template <bool D16>
 __device__ void small_op(const SmallArgs& a, const c128* A, const c128* __restrict__ u, c128* __restrict__ w,
                          c128* __restrict__ part) {
-  const int d = a.d, P = a.P;
-  for (int e = threadIdx.x; e < a.n * P; e += CS_THREADS) {
-    const int row = e % a.n, p0 = e / a.n;  // P > 1 only when n P <= CS_THREADS
-    const int s = row / d;
+  const int d = a.d, P = a.P, site_threads = d * P, cols = d / P;
+  const bool lanes = P == 1 || (site_threads <= 64 && (site_threads & (site_threads - 1)) == 0);
+  for (int e = threadIdx.x; e < a.n * P; e += CS_THREADS) {  // one pass when P > 1
+    const int s = quotient(e, 1.0f / (float)site_threads), rest = e - s * site_threads;
+    const int p0 = quotient(rest, 1.0f / (float)d), i = rest - p0 * d;
     int nb[5];
     site_neighbours(s, a.Lx, a.Lt, nb);
-    const c128* As = A + (int64_t)s * 5 * d * d + (row - s * d);
+    const c128* As = A + (int64_t)s * 5 * d * d + p0 * d + i;
+    const c128* up = u + p0;
     c128 acc = cmk(0.0, 0.0);
-    for (int q0 = p0; q0 < 5 * d; q0 += CS_COLS / 2 * P) {
-      c128 m[CS_COLS / 2];
+    if (cols == 2) {
+      c128 m[5][2];
 #pragma unroll
-      for (int t = 0; t < CS_COLS / 2; ++t)
-        if (q0 + t * P < 5 * d) m[t] = As[(q0 + t * P) * d];
+      for (int dir = 0; dir < 5; ++dir) {
+        m[dir][0] = As[dir * d * d];
+        m[dir][1] = As[dir * d * d + P * d];
+      }
 #pragma unroll
-      for (int t = 0; t < CS_COLS / 2; ++t) {
-        const int q = q0 + t * P;
-        if (q < 5 * d) {
-          const int dir = (q >= d) + (q >= 2 * d) + (q >= 3 * d) + (q >= 4 * d);
-          const int site = dir == 0 ? nb[0] : dir == 1 ? nb[1] : dir == 2 ? nb[2] : dir == 3 ? nb[3] : nb[4];
-          cfma(acc, m[t], u[site * d + q - dir * d]);
+      for (int dir = 0; dir < 5; ++dir) {
+        cfma(acc, m[dir][0], up[nb[dir] * d]);
+        cfma(acc, m[dir][1], up[nb[dir] * d + P]);
+      }
+    } else {
+#pragma unroll 1
+      for (int dir = 0; dir < 5; ++dir) {
+        const int site = dir == 0 ? nb[0] : dir == 1 ? nb[1] : dir == 2 ? nb[2] : dir == 3 ? nb[3] : nb[4];
+#pragma unroll 1
+        for (int q0 = 0; q0 < cols; q0 += CS_COLS / 2) {
+          c128 m[CS_COLS / 2];
+#pragma unroll
+          for (int t = 0; t < CS_COLS / 2; ++t)
+            if (q0 + t < cols) m[t] = As[dir * d * d + (q0 + t) * P * d];
+#pragma unroll
+          for (int t = 0; t < CS_COLS / 2; ++t)
+            if (q0 + t < cols) cfma(acc, m[t], up[site * d + (q0 + t) * P]);
         }
       }
     }
-    if (P > 1)
-      part[e] = acc;
-    else
-      w[row] = acc;
+    if (lanes) {
+      acc = cmk(wave::sum_lanes(acc.x, d, site_threads), wave::sum_lanes(acc.y, d, site_threads));
+      if (p0 == 0) w[s * d + i] = acc;
+    } else {
+      part[p0 * a.n + s * d + i] = acc;
+    }
   }
-  if (P > 1) {
+  if (!lanes) {
     __syncthreads();
     for (int row = threadIdx.x; row < a.n; row += CS_THREADS) {
       c128 acc = part[row];
@@ -254,13 +308,31 @@ __device__ __forceinline__ c128 small_dot(const Cx<R>* v, const Cx<R>* __restric
   return cmk(wave::sum(re), wave::sum(im));
 }
 
-// red[i] = <v_i, w> for i < nb, a wavefront per basis vector; the caller synchronises
+// red[i] = <v_i, w> for i < nb, a wavefront per basis vector, zero for the CS_PAD entries after
+// them; the caller synchronises
 __device__ __forceinline__ void small_dots64(const Basis<double>& V, int nb, const c128* __restrict__ w,
                                              c128* __restrict__ red) {
   for (int i = threadIdx.x >> 6; i < nb; i += CS_WAVES) {
     const c128 d = i < V.kl ? small_dot(V.lds + i * V.n, w, V.n) : small_dot(V.mem_at(i), w, V.n);
     if ((threadIdx.x & 63) == 0) red[i] = d;
   }
+  if (threadIdx.x >= nb && threadIdx.x < nb + CS_PAD) red[threadIdx.x] = cmk(0.0, 0.0);
+}
+
+// Entry p of sum_i h_i v_i over i < nb; h is zero for the CS_PAD entries after them, so that the
+// vectors come four (LDS; kl is a multiple of four, or past the last vector) or eight (memory)
+// at a time without a branch for each, the last one once more beyond nb
+__device__ __forceinline__ c128 small_combine(const Basis<double>& V, const c128* __restrict__ h, int nb, int p) {
+  c128 s = cmk(0.0, 0.0);
+  for (int i0 = 0; i0 < min(nb, V.kl); i0 += 4) {
+#pragma unroll
+    for (int i = i0; i < i0 + 4; ++i) cfma(s, h[i], V.lds[min(i, nb - 1) * V.n + p]);
+  }
+  for (int i0 = V.kl; i0 < nb; i0 += CS_PAD) {
+#pragma unroll
+    for (int i = i0; i < i0 + CS_PAD; ++i) cfma(s, h[i], V.mem_at(min(i, nb - 1))[p]);
+  }
+  return s;
 }
 
 // Sum of v over the workgroup, in every thread (two barriers)
@@ -316,10 +388,11 @@ __device__ __forceinline__ void small_dots32(const Basis<float>& V, int nb, cons
   }
   __syncthreads();
   if (tid < 2 * nb) {
-    double s = 0.0;
+    double s = 0.0, v[CS_WAVES];
 #pragma unroll
-    for (int k = 0; k < CS_WAVES; ++k)
-      if (k < nw) s += stage[k * 64 + tid];
+    for (int k = 0; k < CS_WAVES; ++k) v[k] = stage[k * 64 + tid];  // (those from nw on stay unused)
+#pragma unroll
+    for (int k = 0; k < CS_WAVES; ++k) s = k < nw ? s + v[k] : s;
     reinterpret_cast<double*>(raw)[tid] = s;
   }
   __syncthreads();
@@ -385,10 +458,11 @@ __global__ __launch_bounds__(CS_THREADS) void coarsest_small_kernel(SmallArgs a)
   __syncthreads();
   if (a.k > 0) {
     for (int i = tid >> 6; i < a.k; i += CS_WAVES) {
+      const double li = 1.0 / a.lam[i];
       const c128 d = small_dot(W + (int64_t)i * n, w, n);
       if ((tid & 63) == 0) {
         S.defl[0][i] = d;
-        S.defl[1][i] = (1.0 / a.lam[i]) * d;
+        S.defl[1][i] = li * d;
       }
     }
     __syncthreads();
@@ -478,22 +552,19 @@ __global__ __launch_bounds__(CS_THREADS) void coarsest_small_kernel(SmallArgs a)
       if (tid < nb) hcol[tid] = S.cf[tid];
       nrm = 0.0;
       for (int p = tid; p < n; p += CS_THREADS) {
-        c128 wp = w[p];
-        BASIS_LOOP(V, 0, nb, "unroll 4", { wp = wp - S.cf[i] * v[p]; })
+        const c128 wp = w[p] - small_combine(V, S.cf, nb, p);
         w[p] = wp;
         nrm += cabs2(wp);
       }
       nrm = small_sum(nrm, S.red);  // its barriers also order w' before the dots
       small_dots64(V, nb, w, S.cs);
       __syncthreads();
-      double h2n = 0.0;
-      for (int i = 0; i < nb; ++i) h2n += cabs2(S.cs[i]);
+      const double h2n = wave::sum((tid & 63) < nb ? cabs2(S.cs[tid & 63]) : 0.0);
       if (tid < nb) hcol[tid] = hcol[tid] + S.cs[tid];
       bn = sqrt(fmax(nrm - h2n, 0.0));
       const double inv = bn > 0.0 ? 1.0 / bn : 0.0;
       for (int p = tid; p < n; p += CS_THREADS) {
-        c128 wp = w[p];
-        BASIS_LOOP(V, 0, nb, "unroll 4", { wp = wp - S.cs[i] * v[p]; })
+        const c128 wp = w[p] - small_combine(V, S.cs, nb, p);
         store(nb, p, inv * wp);
       }
       if (tid == 0) S.sc[nb] = 1.0;
@@ -531,8 +602,9 @@ SmallPlan small_plan(const Level& L, int m, int k) {
   SmallPlan p;
   if (L.fine || m < 1 || m > CS_MAX_M || L.n() > SMALL_LEVEL_N) return p;
   const int n = (int)L.n(), d = L.dofs;
+  // as many threads to a row as leave each two columns of every direction
   if (sizeof(R) == 8)
-    while (2 * p.P * n <= CS_THREADS && 2 * p.P <= 5 * d) p.P *= 2;
+    while (2 * p.P * n <= CS_THREADS && 4 * p.P <= d && d % (2 * p.P) == 0) p.P *= 2;
   if (k > CS_MAX_K) return p;
   const size_t room = CS_LDS - sizeof(SmallShared);
   auto bytes = [&](int kl, bool blocks) { return small_dynamic<R>(n, d, p.P, kl, blocks); };

@@ -47,6 +47,18 @@ __device__ __forceinline__ double sum(double v) {
   return v;
 }
 
+// v summed over the lanes that differ in the bits lo, 2 lo, .. < hi of their number (lo, hi
+// powers of two, hi <= 64), in every lane.
+__device__ __forceinline__ double sum_lanes(double v, int lo, int hi) {
+  if (lo <= 1 && 1 < hi) v += dpp<0xb1>(v);
+  if (lo <= 2 && 2 < hi) v += dpp<0x4e>(v);
+  if (lo <= 4 && 4 < hi) v += xor4(v);
+  if (lo <= 8 && 8 < hi) v += dpp<0x128>(v);
+  if (lo <= 16 && 16 < hi) v = fold16(v, v);
+  if (lo <= 32 && 32 < hi) v = fold32(v, v);
+  return v;
+}
+
 // The sums of v[0..7], v[l >> 3] in lane l.
 __device__ __forceinline__ double sum8(double (&v)[8]) {
 #pragma unroll

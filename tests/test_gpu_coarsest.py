@@ -16,6 +16,9 @@ M, M_DEFL = 24, 8  # default iteration counts without and with a deflation
 SHAPES = {
     "8x2": ((8, 16), (4, 4), 1),       # 16 entries, the smallest level
     "16x8": ((16, 16), (4, 4), 4),     # 128: blocks in LDS
+    "12x10": ((16, 12), (4, 4), 5),    # 120: in FP64 a row over two threads, summed through LDS
+    "6x24": ((12, 8), (4, 4), 12),     # 144: the same over four, a site's threads in two wavefronts
+    "8x12": ((16, 8), (4, 4), 6),      # 96: three columns a direction and thread
     "60x10": ((24, 40), (4, 4), 5),    # 600: dofs that are no power of two
     "64x16": ((32, 32), (4, 4), 8),    # 1024: part of the FP32 basis outside LDS
     "50x24": ((20, 40), (4, 4), 12),   # 1200: more than 16 dofs
