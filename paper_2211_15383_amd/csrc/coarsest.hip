@@ -100,10 +100,6 @@ __host__ __device__ inline size_t small_dynamic(int n, int d, int P, int kl, boo
   return sizeof(Cx<R>) * (size_t)n * (2 + (P > 1 ? P : 0) + kl + (blocks ? 5 * d : 0));
 }
 
-// a / b for 0 <= a < 4096, inv = 1 / b: a + 1/2 is at least 1/(2 b) from the next multiple of b,
-// far beyond the rounding (an integer division takes some 35 instructions)
-__device__ __forceinline__ int quotient(int a, float inv) { return (int)(((float)a + 0.5f) * inv); }
-
 __device__ __forceinline__ void site_neighbours(int s, int Lx, int Lt, int* nb) {
   const int t = quotient(s, 1.0f / (float)Lx), x = s - t * Lx;
   nb[0] = s;

@@ -48,6 +48,11 @@ template <typename R>
 __host__ __device__ __forceinline__ Cx<R> cdot(Cx<R> a, Cx<R> b) {
   return cmk(a.x * b.x + a.y * b.y, a.x * b.y - a.y * b.x);
 }
+// a / b for 0 <= a < 2^20, inv = 1 / b: a + 1/2 is at least 1/(2 b) from the next multiple of b,
+// beyond the rounding of the product.  Four instructions where an integer division by a run-time
+// value takes about 35 (64 bits: well over 100), which the kernels of small levels feel.
+__device__ __forceinline__ int quotient(int a, float inv) { return (int)(((float)a + 0.5f) * inv); }
+
 // acc += a * b
 template <typename R>
 __host__ __device__ __forceinline__ void cfma(Cx<R>& acc, Cx<R> a, Cx<R> b) {

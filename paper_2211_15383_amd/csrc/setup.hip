@@ -125,9 +125,9 @@ __global__ void scatter_kernel(const c128* __restrict__ C, int Lxc, int Ltc, int
   const int64_t nc = Vc * dc;
   const int64_t tid = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;  // (X, i)
   if (tid >= nc) return;
-  const int i = (int)(tid % dc);
-  const int64_t s = tid / dc;
-  const int x = (int)(s % Lxc), t = (int)(s / Lxc);
+  const int64_t s = (unsigned)tid / (unsigned)dc;
+  const int i = (int)(tid - s * dc);
+  const int t = (int)((unsigned)s / (unsigned)Lxc), x = (int)(s - (int64_t)t * Lxc);
   const int dx[5] = {0, 1, -1, 0, 0}, dt[5] = {0, 0, 0, 1, -1};
   int64_t nbs[5];
   for (int dir = 0; dir < 5; ++dir) {
