@@ -144,20 +144,23 @@ __global__ __launch_bounds__(256) void wilson_kernel(const Cx<R>* __restrict__ U
 
 // The scalar kernels below ask for CHUNK block (or interpolation) entries and their vector
 // entries before the first product, so that a thread waits for memory once per chunk; the
-// products keep their order.
+// products keep their order.  A uniform branch around each of them costs more than the load
+// and the product together, so the usual dofs are template arguments (D; 0: any), right-hand
+// sides past the last repeat it, and a thread with one right-hand side has the next
+// direction's entries on their way during this one's products.
 constexpr int CHUNK = 8;
-constexpr int CHUNK1 = 16;  // where a thread has one right-hand side
 
 // Coarse block stencil: y_s = sum_dir A[s][dir] x_{s+dir}; blocks column-major
 // (A[s][dir][j * d + i] = row i, column j).  Thread per (site, row), RB right-hand sides
 // per thread so that every block entry is loaded once per RB vectors.  Measured at 256 sites,
-// 16 dofs, FP64, one RHS: 17 us with a load and its product at a time on 16 workgroups, 7.6 us.
-template <typename R, int RB, bool G5, typename RO = R>
+// 16 dofs, FP64, one RHS: 17 us with a load and its product at a time on 16 workgroups, 7.6 with
+// 16 at a time on 64, 3.7 straight-line.
+template <typename R, int RB, bool G5, typename RO, int D>
 __global__ __launch_bounds__(256) void coarse_kernel(const Cx<R>* __restrict__ A, const Cx<R>* __restrict__ in,
-                                                     Cx<RO>* __restrict__ out, int Lx, int Lt, int d, int spb,
+                                                     Cx<RO>* __restrict__ out, int Lx, int Lt, int dofs, int spb,
                                                      int nrhs, int64_t ldx, int64_t ldy,
                                                      const Cx<R>* __restrict__ sub) {
-  constexpr int CH = RB == 1 ? CHUNK1 : CHUNK;
+  const int d = D ? D : dofs;
   const int64_t V = (int64_t)Lx * Lt;
   const int i = threadIdx.x % d;
   const int64_t s = (int64_t)blockIdx.x * spb + threadIdx.x / d;
@@ -169,28 +172,71 @@ __global__ __launch_bounds__(256) void coarse_kernel(const Cx<R>* __restrict__ A
   Cx<R> acc[RB];
 #pragma unroll
   for (int q = 0; q < RB; ++q) acc[q] = cmk((R)0, (R)0);
-  const Cx<R>* Ab = A + s * 5 * d * d;
+  const Cx<R>* Ab = A + s * 5 * d * d + i;
+  const Cx<R>* xq[RB];
 #pragma unroll
-  for (int dir = 0; dir < 5; ++dir) {
-    const Cx<R>* Ad = Ab + dir * d * d + i;
-    const Cx<R>* xd = in + r0 * ldx + sites[dir] * d;
-    for (int j0 = 0; j0 < d; j0 += CH) {
-      Cx<R> a[CH], x[RB][CH];
+  for (int q = 0; q < RB; ++q) xq[q] = in + min(r0 + q, nrhs - 1) * ldx;
+  if constexpr (D > 0) {
+    constexpr int CH = RB > 1 && D > 8 ? D / 2 : D, NC = 5 * D / CH, NB = RB == 1 ? 2 : 1;
+    Cx<R> a[NB][CH], x[NB][RB][CH];
+    auto load = [&](int buf, int k) {  // columns k CH ..
+      const int dir = k * CH / D;
+      const int64_t site = dir == 0 ? s : dir == 1 ? nb.xp : dir == 2 ? nb.xm : dir == 3 ? nb.tp : nb.tm;
+      const int64_t xo = site * D + k * CH % D;
 #pragma unroll
       for (int j = 0; j < CH; ++j) {
-        if (j0 + j < d) {
-          a[j] = Ad[(j0 + j) * d];
+        a[buf][j] = Ab[(k * CH + j) * D];
 #pragma unroll
-          for (int q = 0; q < RB; ++q)
-            if (q < nr) x[q][j] = xd[q * ldx + j0 + j];
-        }
+        for (int q = 0; q < RB; ++q) x[buf][q][j] = xq[q][xo + j];
       }
+    };
+    auto products = [&](int buf) {
 #pragma unroll
       for (int j = 0; j < CH; ++j) {
-        if (j0 + j < d) {
 #pragma unroll
-          for (int q = 0; q < RB; ++q)
-            if (q < nr) cfma(acc[q], a[j], x[q][j]);
+        for (int q = 0; q < RB; ++q) cfma(acc[q], a[buf][j], x[buf][q][j]);
+      }
+    };
+    if constexpr (NB == 2) {
+      load(0, 0);
+#pragma unroll 1
+      for (int k = 0; k < NC - 1; k += 2) {
+        load(1, k + 1);
+        __builtin_amdgcn_sched_barrier(0);
+        products(0);
+        load(0, k + 2);
+        __builtin_amdgcn_sched_barrier(0);
+        products(1);
+      }
+      products(0);
+      static_assert(NC % 2 == 1, "five directions in pairs and one");
+    } else {
+#pragma unroll 1
+      for (int k = 0; k < NC; ++k) {
+        load(0, k);
+        __builtin_amdgcn_sched_barrier(0);
+        products(0);
+      }
+    }
+  } else {
+#pragma unroll
+    for (int dir = 0; dir < 5; ++dir) {
+      for (int j0 = 0; j0 < d; j0 += CHUNK) {
+        Cx<R> a[CHUNK], x[RB][CHUNK];
+#pragma unroll
+        for (int j = 0; j < CHUNK; ++j) {
+          if (j0 + j < d) {
+            a[j] = Ab[(dir * d + j0 + j) * d];
+#pragma unroll
+            for (int q = 0; q < RB; ++q) x[q][j] = xq[q][sites[dir] * d + j0 + j];
+          }
+        }
+#pragma unroll
+        for (int j = 0; j < CHUNK; ++j) {
+          if (j0 + j < d) {
+#pragma unroll
+            for (int q = 0; q < RB; ++q) cfma(acc[q], a[j], x[q][j]);
+          }
         }
       }
     }
@@ -334,12 +380,13 @@ __global__ __launch_bounds__(256) void sap_kernel(const Cx<R>* __restrict__ U, C
 // Red/black point-block Gauss-Seidel on a coarse level: for every site of colour
 // `color`, x_s <- x_s + A_ss^-1 (b_s - (D x)_s).  Thread per (site, row); the residual of
 // a site is exchanged through LDS.
-template <typename R>
+template <typename R, int D>
 __global__ __launch_bounds__(256) void coarse_gs_kernel(const Cx<R>* __restrict__ A, const Cx<R>* __restrict__ Ainv,
                                                         Cx<R>* __restrict__ x, const Cx<R>* __restrict__ b, int Lx,
-                                                        int Lt, int d, int spb, int nrhs, int rb, int color,
+                                                        int Lt, int dofs, int spb, int nrhs, int rb, int color,
                                                         int even_lx, int64_t ld) {
   extern __shared__ unsigned char smem_raw[];
+  const int d = D ? D : dofs;
   Cx<R>* res = reinterpret_cast<Cx<R>*>(smem_raw);
   const int64_t V = (int64_t)Lx * Lt;
   const int i = threadIdx.x % d;
@@ -366,26 +413,54 @@ __global__ __launch_bounds__(256) void coarse_gs_kernel(const Cx<R>* __restrict_
   for (int r = r0; r < r1; ++r) {
     const Cx<R>* xr = x + r * ld;
     Cx<R> acc = cmk((R)0, (R)0);
+    Cx<R> ai[D ? D : 1];
     if (active) {
       acc = b[r * ld + s * d + i];
+      if constexpr (D > 0) {
+        Cx<R> a[2][D], v[2][D];
+        auto load = [&](int dir) {
 #pragma unroll
-      for (int dir = 0; dir < 5; ++dir) {
-        const Cx<R>* Ad = Ab + dir * d * d + i;
-        const Cx<R>* xd = xr + sites[dir] * d;
-        for (int j0 = 0; j0 < d; j0 += CHUNK1) {
-          Cx<R> a[CHUNK1], v[CHUNK1];
-#pragma unroll
-          for (int j = 0; j < CHUNK1; ++j) {
-            if (j0 + j < d) {
-              a[j] = Ad[(j0 + j) * d];
-              v[j] = xd[j0 + j];
-            }
+          for (int j = 0; j < D; ++j) {
+            a[dir & 1][j] = Ab[(dir * D + j) * D + i];
+            v[dir & 1][j] = xr[sites[dir] * D + j];
           }
+        };
+        load(0);
 #pragma unroll
-          for (int j = 0; j < CHUNK1; ++j) {
-            if (j0 + j < d) {
-              acc.x -= a[j].x * v[j].x - a[j].y * v[j].y;
-              acc.y -= a[j].x * v[j].y + a[j].y * v[j].x;
+        for (int dir = 0; dir < 5; ++dir) {
+          if (dir < 4) {
+            load(dir + 1);
+          } else {
+#pragma unroll
+            for (int j = 0; j < D; ++j) ai[j] = Ainv[(s * D + j) * D + i];
+          }
+          __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+          for (int j = 0; j < D; ++j) {
+            acc.x -= a[dir & 1][j].x * v[dir & 1][j].x - a[dir & 1][j].y * v[dir & 1][j].y;
+            acc.y -= a[dir & 1][j].x * v[dir & 1][j].y + a[dir & 1][j].y * v[dir & 1][j].x;
+          }
+        }
+      } else {
+#pragma unroll
+        for (int dir = 0; dir < 5; ++dir) {
+          const Cx<R>* Ad = Ab + dir * d * d + i;
+          const Cx<R>* xd = xr + sites[dir] * d;
+          for (int j0 = 0; j0 < d; j0 += CHUNK) {
+            Cx<R> a[CHUNK], v[CHUNK];
+#pragma unroll
+            for (int j = 0; j < CHUNK; ++j) {
+              if (j0 + j < d) {
+                a[j] = Ad[(j0 + j) * d];
+                v[j] = xd[j0 + j];
+              }
+            }
+#pragma unroll
+            for (int j = 0; j < CHUNK; ++j) {
+              if (j0 + j < d) {
+                acc.x -= a[j].x * v[j].x - a[j].y * v[j].y;
+                acc.y -= a[j].x * v[j].y + a[j].y * v[j].x;
+              }
             }
           }
         }
@@ -396,9 +471,14 @@ __global__ __launch_bounds__(256) void coarse_gs_kernel(const Cx<R>* __restrict_
     __syncthreads();
     if (active) {
       Cx<R> e = cmk((R)0, (R)0);
-      const Cx<R>* Ai = Ainv + s * d * d + i;
-#pragma unroll CHUNK1
-      for (int j = 0; j < d; ++j) cfma(e, Ai[j * d], res[ls * d + j]);
+      if constexpr (D > 0) {
+#pragma unroll
+        for (int j = 0; j < D; ++j) cfma(e, ai[j], res[ls * D + j]);
+      } else {
+        const Cx<R>* Ai = Ainv + s * d * d + i;
+#pragma unroll CHUNK
+        for (int j = 0; j < d; ++j) cfma(e, Ai[j * d], res[ls * d + j]);
+      }
       Cx<R>* xw = x + r * ld + s * d + i;
       *xw = *xw + e;
     }
@@ -427,39 +507,66 @@ __global__ __launch_bounds__(256) void restrict_kernel(const Cx<R>* __restrict__
   const int r0 = blockIdx.y * RB;
   const int nr = min(RB, nrhs - r0);
   Cx<R> acc[RB];
+  const Cx<R>* xq[RB];
 #pragma unroll
-  for (int q = 0; q < RB; ++q) acc[q] = cmk((R)0, (R)0);
-  const Cx<R>* xr = xf + (int64_t)r0 * ldf;
-  // row = (lx + ax lt) h + j, counted up one by one
-  int lx = 0, lt = 0, j = 0;
-  const int64_t corner = ((int64_t)(T * at) * Lxf + (int64_t)X * ax) * df + c * h;
-  for (int row0 = 0; row0 < rows; row0 += CHUNK) {
-    Cx<R> pv[CHUNK], x[RB][CHUNK];
-#pragma unroll
-    for (int u = 0; u < CHUNK; ++u) {
-      if (row0 + u < rows) {
-        const int64_t f = corner + ((int64_t)lt * Lxf + lx) * df + j;
-        pv[u] = Pb[(int64_t)(row0 + u) * N];
-#pragma unroll
-        for (int q = 0; q < RB; ++q)
-          if (q < nr) x[q][u] = xr[q * ldf + f];
-        if (++j == h) {
-          j = 0;
-          if (++lx == ax) {
-            lx = 0;
-            ++lt;
-          }
-        }
-      }
-    }
+  for (int q = 0; q < RB; ++q) {
+    acc[q] = cmk((R)0, (R)0);
+    xq[q] = xf + min(r0 + q, nrhs - 1) * ldf;
+  }
+  // f: the fine entry of the next row (row = (lx + ax lt) h + j, counted up one by one)
+  int lx = 0, j = 0;
+  int64_t f = ((int64_t)(T * at) * Lxf + (int64_t)X * ax) * df + c * h;
+  const int64_t next_site = df - h, next_line = (int64_t)(Lxf - ax) * df;
+  auto step = [&] {
+    const bool site = ++j == h;
+    j = site ? 0 : j;
+    lx += site;
+    const bool line = lx == ax;
+    lx = line ? 0 : lx;
+    f += 1 + (site ? next_site : 0) + (line ? next_line : 0);
+  };
+  constexpr int NB = RB == 1 ? 2 : 1;
+  Cx<R> pv[NB][CHUNK], x[NB][RB][CHUNK];
+  auto load = [&](int buf, int row0) {
 #pragma unroll
     for (int u = 0; u < CHUNK; ++u) {
-      if (row0 + u < rows) {
+      pv[buf][u] = Pb[(int64_t)(row0 + u) * N];
 #pragma unroll
-        for (int q = 0; q < RB; ++q)
-          if (q < nr) cfmac(acc[q], pv[u], x[q][u]);
-      }
+      for (int q = 0; q < RB; ++q) x[buf][q][u] = xq[q][f];
+      step();
     }
+  };
+  auto products = [&](int buf) {
+#pragma unroll
+    for (int u = 0; u < CHUNK; ++u) {
+#pragma unroll
+      for (int q = 0; q < RB; ++q) cfmac(acc[q], pv[buf][u], x[buf][q][u]);
+    }
+  };
+  const int full = rows / CHUNK * CHUNK;
+  if constexpr (NB == 2) {
+    if (full > 0) load(0, 0);
+    for (int row0 = 0; row0 < full; row0 += 2 * CHUNK) {
+      if (row0 + CHUNK < full) load(1, row0 + CHUNK);
+      __builtin_amdgcn_sched_barrier(0);
+      products(0);
+      if (row0 + CHUNK >= full) break;
+      if (row0 + 2 * CHUNK < full) load(0, row0 + 2 * CHUNK);
+      __builtin_amdgcn_sched_barrier(0);
+      products(1);
+    }
+  } else {
+    for (int row0 = 0; row0 < full; row0 += CHUNK) {
+      load(0, row0);
+      __builtin_amdgcn_sched_barrier(0);
+      products(0);
+    }
+  }
+  for (int row = full; row < rows; ++row) {
+    const Cx<R> p = Pb[(int64_t)row * N];
+#pragma unroll
+    for (int q = 0; q < RB; ++q) cfmac(acc[q], p, xq[q][f]);
+    step();
   }
 #pragma unroll
   for (int q = 0; q < RB; ++q)
@@ -468,10 +575,11 @@ __global__ __launch_bounds__(256) void restrict_kernel(const Cx<R>* __restrict__
 
 // Prolongation x_f (+)= P e_c; thread per (fine dof, group of RB right-hand sides).  A thread's
 // interpolation row is one request (FP64, 256^2 onto the fine level, 16 RHS: 105 -> 34 us).
-template <typename R, int RB>
+template <typename R, int RB, int NT>
 __global__ __launch_bounds__(256) void prolong_kernel(const Cx<R>* __restrict__ P, const Cx<R>* __restrict__ ec,
                                                       Cx<R>* __restrict__ xf, int Lxf, int Ltf, int df, int ax, int at,
-                                                      int N, int nrhs, int add, int64_t ldf, int64_t ldc) {
+                                                      int ntv, int nrhs, int add, int64_t ldf, int64_t ldc) {
+  const int N = NT ? NT : ntv;
   const int64_t nf = (int64_t)Lxf * Ltf * df;
   const int64_t tid = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
   if (tid >= nf) return;
@@ -487,26 +595,27 @@ __global__ __launch_bounds__(256) void prolong_kernel(const Cx<R>* __restrict__ 
   const Cx<R>* Pr = P + ((cs * 2 + c) * (int64_t)rows + row) * N;
   const int r0 = blockIdx.y * RB;
   const int nr = min(RB, nrhs - r0);
-  const Cx<R>* er = ec + (int64_t)r0 * ldc + cs * 2 * N + c * N;
+  const Cx<R>* er = ec + cs * 2 * N + c * N;
   Cx<R> acc[RB];
 #pragma unroll
   for (int q = 0; q < RB; ++q)
     acc[q] = (add && q < nr) ? xf[(int64_t)(r0 + q) * ldf + tid] : cmk((R)0, (R)0);
   for (int k0 = 0; k0 < N; k0 += CHUNK) {
-    Cx<R> pv[CHUNK];
+    Cx<R> pv[CHUNK], e[RB][CHUNK];
 #pragma unroll
-    for (int k = 0; k < CHUNK; ++k)
-      if (k0 + k < N) pv[k] = Pr[k0 + k];
+    for (int k = 0; k < CHUNK; ++k) {
+      if (NT == CHUNK || k0 + k < N) {
+        pv[k] = Pr[k0 + k];
 #pragma unroll
-    for (int q = 0; q < RB; ++q) {
-      if (q < nr) {
-        Cx<R> e[CHUNK];
+        for (int q = 0; q < RB; ++q) e[q][k] = er[min(r0 + q, nrhs - 1) * ldc + k0 + k];
+      }
+    }
+    __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
-        for (int k = 0; k < CHUNK; ++k)
-          if (k0 + k < N) e[k] = er[q * ldc + k0 + k];
+    for (int k = 0; k < CHUNK; ++k) {
+      if (NT == CHUNK || k0 + k < N) {
 #pragma unroll
-        for (int k = 0; k < CHUNK; ++k)
-          if (k0 + k < N) cfma(acc[q], pv[k], e[k]);
+        for (int q = 0; q < RB; ++q) cfma(acc[q], pv[k], e[q][k]);
       }
     }
   }
@@ -1680,12 +1789,21 @@ static void launch_coarse_scalar(dmlmc_ctx* ctx, const Level& L, const Cx<R>* A,
   const int threads = ceil_div(V * d, 256) * ceil_div(nrhs, RB) >= 2048 ? 256 : 64;
   const int spb = std::max(1, threads / d);
   const dim3 grid((unsigned)ceil_div(V, spb), (unsigned)ceil_div(nrhs, RB)), block((unsigned)(spb * d));
-  if (gamma5_left)
-    hipLaunchKernelGGL((coarse_kernel<R, RB, true, RO>), grid, block, 0, ctx->stream, A, x, y, L.Lx, L.Lt, d, spb, nrhs,
-                       ldx, ldy, (const Cx<R>*)nullptr);
-  else
-    hipLaunchKernelGGL((coarse_kernel<R, RB, false, RO>), grid, block, 0, ctx->stream, A, x, y, L.Lx, L.Lt, d, spb,
-                       nrhs, ldx, ldy, sub);
+#define COARSE_DOFS(D)                                                                                                 \
+  if (gamma5_left)                                                                                                    \
+    hipLaunchKernelGGL((coarse_kernel<R, RB, true, RO, D>), grid, block, 0, ctx->stream, A, x, y, L.Lx, L.Lt, d, spb,  \
+                       nrhs, ldx, ldy, (const Cx<R>*)nullptr);                                                        \
+  else                                                                                                                \
+    hipLaunchKernelGGL((coarse_kernel<R, RB, false, RO, D>), grid, block, 0, ctx->stream, A, x, y, L.Lx, L.Lt, d, spb, \
+                       nrhs, ldx, ldy, sub)
+  switch (d) {
+    case 8: COARSE_DOFS(8); break;
+    case 10: COARSE_DOFS(10); break;
+    case 12: COARSE_DOFS(12); break;
+    case 16: COARSE_DOFS(16); break;
+    default: COARSE_DOFS(0);
+  }
+#undef COARSE_DOFS
   LAUNCH_CHECK();
 }
 
@@ -1906,8 +2024,17 @@ void launch_coarse_gs(dmlmc_ctx* ctx, const Level& L, Cx<R>* x, const Cx<R>* b, 
   dim3 grid((unsigned)ceil_div(nsites, spb), (unsigned)ceil_div(nrhs, rb));
   dim3 block((unsigned)(spb * d));
   size_t shm = (size_t)spb * d * sizeof(Cx<R>);
-  hipLaunchKernelGGL((coarse_gs_kernel<R>), grid, block, shm, ctx->stream, A, Ai, x, b, L.Lx, L.Lt, d, spb, nrhs,
-                     rb, color, even, ld);
+#define GS_DOFS(D)                                                                                                  \
+  hipLaunchKernelGGL((coarse_gs_kernel<R, D>), grid, block, shm, ctx->stream, A, Ai, x, b, L.Lx, L.Lt, d, spb, nrhs, \
+                     rb, color, even, ld)
+  switch (d) {
+    case 8: GS_DOFS(8); break;
+    case 10: GS_DOFS(10); break;
+    case 12: GS_DOFS(12); break;
+    case 16: GS_DOFS(16); break;
+    default: GS_DOFS(0);
+  }
+#undef GS_DOFS
   LAUNCH_CHECK();
 }
 
@@ -1955,10 +2082,16 @@ void launch_restrict(dmlmc_ctx* ctx, const Level& L, const Cx<R>* xf, Cx<R>* yc,
     LAUNCH_CHECK();
     return;
   }
-  constexpr int RB = 4;
-  dim3 grid((unsigned)ceil_div(threads, 256), (unsigned)ceil_div(nrhs, RB));
-  hipLaunchKernelGGL((restrict_kernel<R, RB>), grid, dim3(256), 0, ctx->stream, P, xf, yc, L.Lx, L.Lt, L.dofs, L.ax,
-                     L.at, L.N, nrhs, ldf, ldc);
+  // 64-thread workgroups until 256-thread ones would be 1024, one RHS per thread for one RHS
+  const int RB = nrhs == 1 ? 1 : 4;
+  const int wg = ceil_div(threads, 256) * ceil_div(nrhs, RB) >= 1024 ? 256 : 64;
+  const dim3 grid((unsigned)ceil_div(threads, wg), (unsigned)ceil_div(nrhs, RB));
+  if (RB == 1)
+    hipLaunchKernelGGL((restrict_kernel<R, 1>), grid, dim3(wg), 0, ctx->stream, P, xf, yc, L.Lx, L.Lt, L.dofs, L.ax,
+                       L.at, L.N, nrhs, ldf, ldc);
+  else
+    hipLaunchKernelGGL((restrict_kernel<R, 4>), grid, dim3(wg), 0, ctx->stream, P, xf, yc, L.Lx, L.Lt, L.dofs, L.ax,
+                       L.at, L.N, nrhs, ldf, ldc);
   LAUNCH_CHECK();
 }
 
@@ -2028,8 +2161,12 @@ void launch_prolong(dmlmc_ctx* ctx, const Level& L, const Cx<R>* ec, Cx<R>* xf, 
   }
   constexpr int RB = 4;
   dim3 grid((unsigned)ceil_div(nf, 256), (unsigned)ceil_div(nrhs, RB));
-  hipLaunchKernelGGL((prolong_kernel<R, RB>), grid, dim3(256), 0, ctx->stream, P, ec, xf, L.Lx, L.Lt, L.dofs, L.ax,
-                     L.at, L.N, nrhs, add ? 1 : 0, ldf, ldc);
+  if (L.N == CHUNK)
+    hipLaunchKernelGGL((prolong_kernel<R, RB, CHUNK>), grid, dim3(256), 0, ctx->stream, P, ec, xf, L.Lx, L.Lt, L.dofs,
+                       L.ax, L.at, L.N, nrhs, add ? 1 : 0, ldf, ldc);
+  else
+    hipLaunchKernelGGL((prolong_kernel<R, RB, 0>), grid, dim3(256), 0, ctx->stream, P, ec, xf, L.Lx, L.Lt, L.dofs, L.ax,
+                       L.at, L.N, nrhs, add ? 1 : 0, ldf, ldc);
   LAUNCH_CHECK();
 }
 

@@ -23,6 +23,9 @@ SHAPES = {
     "64x16": ((32, 32), (4, 4), 8),    # 1024: part of the FP32 basis outside LDS
     "50x24": ((20, 40), (4, 4), 12),   # 1200: more than 16 dofs
     "128x16": ((64, 32), (4, 4), 8),   # 2048: the largest in one launch
+    "rows8": ((16, 16), (4, 2), 3),    # 8, 12 and 24 rows per interpolation block: one chunk of eight,
+    "rows12": ((16, 12), (4, 3), 4),   # one and a remainder, three
+    "rows24": ((16, 24), (4, 6), 5),
     "132x16": ((48, 44), (4, 4), 8),   # 2112: the first in separate launches
     "1024x16": ((128, 128), (4, 4), 8),  # 16384: the largest with split Gram-Schmidt steps
     "1056x16": ((132, 128), (4, 4), 8),  # 16896: the first with the passes of long vectors
@@ -112,7 +115,7 @@ def test_coarsest_gmres(shape, prec, k):
 
 
 @pytest.mark.parametrize("nrhs", [1, 3, 8, 17, 33])
-@pytest.mark.parametrize("shape", ["8x2", "60x10", "64x16", "50x24", "132x16"])
+@pytest.mark.parametrize("shape", ["8x2", "16x8", "8x12", "60x10", "64x16", "50x24", "132x16", "rows8", "rows12", "rows24"])
 def test_coarse_operator_and_transfers(shape, nrhs):
     """D, P^H and P of small levels: one right-hand side, the remainders of the groups of 4
     and 16, FP64 (a matrix-core tile per wavefront from 8 on at 16 dofs) and complex FP32."""
@@ -140,6 +143,42 @@ def test_coarse_operator_and_transfers(shape, nrhs):
             out = H.apply(op, lv, src, torch.full(ref.shape, float("nan"), dtype=dt, device="cuda"), prec=prec)
             err = np.linalg.norm(out.cpu().numpy() - ref, axis=1) / np.linalg.norm(ref, axis=1)
             assert err.max() <= tol, (shape, nrhs, prec, op, err.max())
+
+
+@pytest.mark.parametrize("nrhs", [1, 5])
+@pytest.mark.parametrize("Lx,Lt,ntv", [(16, 16, 4), (16, 16, 5), (16, 24, 6), (16, 16, 8), (16, 16, 3)])
+def test_coarse_gauss_seidel(Lx, Lt, ntv, nrhs):
+    """Two red/black sweeps on the second of three levels: 8, 10, 12 and 16 dofs and any other
+    count."""
+    import torch
+
+    from paper_2211_15383_amd import dmlmc
+
+    rng = np.random.default_rng(29)
+
+    def cn(*s):
+        return rng.standard_normal(s) + 1j * rng.standard_normal(s)
+
+    H = dmlmc.Hierarchy(dmlmc.Context(0), rng.normal(0.0, 0.3, (2, Lt, Lx)), 0.3, [(4, 4), (2, 2)],
+                        [ntv, 2], import_tv=[cn(2 * Lx * Lt, ntv), cn(Lx * Lt // 16 * 2 * ntv, 2)])
+    lx, lt, d = H.level_info(2)
+    A = H.export(2, Dc=True)["Dc"]
+    Ainv = np.linalg.inv(A[:, 0])
+    t, x = np.divmod(np.arange(lx * lt), lx)
+    b = cn(nrhs, H.n(2))
+    # sums of up to 6 d products, inverse blocks with condition numbers of order 10
+    for prec, dt, tol in ((dmlmc.FP64, torch.complex128, 1e-12), (dmlmc.MIXED, torch.complex64, 1e-4)):
+        H.solver_params(smoother_half=0)
+        bd = torch.as_tensor(b, device="cuda").to(dt)
+        out = H.apply(dmlmc.OP_SMOOTH, 2, bd, torch.zeros_like(bd), prec=prec, arg=2).cpu().numpy()
+        bh = bd.cpu().numpy().astype(np.complex128).T
+        y = np.zeros_like(bh)
+        for _ in range(2):
+            for color in (0, 1):
+                r = (bh - _blocks_apply(A, lx, lt, y)).reshape(lx * lt, d, nrhs)
+                on = (x + t) % 2 == color
+                y.reshape(lx * lt, d, nrhs)[on] += (Ainv @ r)[on]
+        assert np.linalg.norm(out.T - y) <= tol * np.linalg.norm(y), (prec, nrhs)
 
 
 def test_block_larger_than_the_readback_buffer():
