@@ -130,17 +130,21 @@ __device__ void finish_pass(const Fin& f, int r, int nv, const double* red) {
   }
 }
 
-// Block reduce, then either finish (one workgroup per RHS) or write partials.
-template <int NV>
-__device__ void reduce_or_partial(const double (&acc)[NV], int nv, double* lds, double* red, double* __restrict__ part,
-                                  const Fin& f, int r) {
-  block_reduce(acc, nv, lds, red);
+// The reduced sums red[0..nv) of a workgroup: finish (one workgroup per RHS) or write partials.
+__device__ void finish_or_partial(int nv, const double* red, double* __restrict__ part, const Fin& f, int r) {
   if (gridDim.x == 1) {
     finish_pass(f, r, nv, red);
   } else {
     double* pr = part + ((int64_t)r * gridDim.x + blockIdx.x) * nv;
     for (int q = threadIdx.x; q < nv; q += blockDim.x) pr[q] = red[q];
   }
+}
+
+template <int NV>
+__device__ void reduce_or_partial(const double (&acc)[NV], int nv, double* lds, double* red, double* __restrict__ part,
+                                  const Fin& f, int r) {
+  block_reduce(acc, nv, lds, red);
+  finish_or_partial(nv, red, part, f, r);
 }
 
 // One workgroup per RHS, value q by wavefront q mod FINISH_WAVES: lane l adds the partials of
@@ -176,34 +180,87 @@ struct __align__(4 * sizeof(R)) Pair {
   Cx<R> a, b;
 };
 
-// ---------------------------------------------------------------- two-pass form kernels
-template <typename RV>
-__global__ __launch_bounds__(256) void gs_dots_kernel(const Cx<RV>* __restrict__ V, int nb, const c128* __restrict__ w,
+// ---------------------------------------------------------------- two-pass form, n > 16384
+// Workgroups of 256 threads with LONG_EL entries to a thread and pass, the basis eight vectors
+// at a time (past the last one it repeats: no branch per vector).  Bound by memory on long
+// vectors and by latency on a few short ones: at n = 131072, one RHS, 24 basis vectors at most,
+// a dots pass took 24 us and an update 18 with 64 workgroups and a branch per vector, 5.3 and 5.1
+// like this.
+constexpr int LONG_EL = 2;
+
+// lds[wavefront][q] = the wavefront's sums over its passes, then part (or the finish)
+__global__ __launch_bounds__(256) void gs_dots_kernel(const c128* __restrict__ V, int nb, const c128* __restrict__ w,
                                                       int64_t n, int64_t vstride, double* __restrict__ part, Fin f) {
-  __shared__ double lds[4 * NVMAX];
+  __shared__ double lds[4][NVMAX];
   __shared__ double red[NVMAX];
-  const int r = blockIdx.y;
-  double acc[NVMAX];
-#pragma unroll
-  for (int q = 0; q < NVMAX; ++q) acc[q] = 0.0;
+  const int r = blockIdx.y, lane = threadIdx.x & 63, wv = threadIdx.x >> 6;
   const c128* wr = w + (int64_t)r * n;
-  const Cx<RV>* Vr = V + (int64_t)r * n;
-  for (int64_t p = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; p < n; p += (int64_t)gridDim.x * blockDim.x) {
-    const c128 b = wr[p];
+  const c128* Vr = V + (int64_t)r * n;
+  lds[wv][lane] = 0.0;
+  for (int64_t p0 = (int64_t)blockIdx.x * (256 * LONG_EL); p0 < n; p0 += (int64_t)gridDim.x * (256 * LONG_EL)) {
+    c128 b[LONG_EL];
+    int64_t p[LONG_EL];
 #pragma unroll
-    for (int i = 0; i < NBMAX; ++i) {
-      if (i < nb) {
-        const Cx<RV> a = Vr[i * vstride + p];
-        acc[2 * i] += (double)a.x * b.x + (double)a.y * b.y;
-        acc[2 * i + 1] += (double)a.x * b.y - (double)a.y * b.x;
+    for (int k = 0; k < LONG_EL; ++k) {
+      const int64_t e = p0 + 256 * k + threadIdx.x;
+      p[k] = e < n ? e : 0;
+      b[k] = wr[p[k]];
+      if (e >= n) b[k] = cmk(0.0, 0.0);
+    }
+    for (int c0 = 0; c0 < nb; c0 += 8) {
+      c128 v[LONG_EL][8];
+#pragma unroll
+      for (int i = 0; i < 8; ++i) {
+        const c128* vi = Vr + min(c0 + i, nb - 1) * vstride;
+#pragma unroll
+        for (int k = 0; k < LONG_EL; ++k) v[k][i] = vi[p[k]];
       }
+      double acc[16];
+#pragma unroll
+      for (int i = 0; i < 8; ++i) {
+        acc[2 * i] = acc[2 * i + 1] = 0.0;
+#pragma unroll
+        for (int k = 0; k < LONG_EL; ++k) {
+          acc[2 * i] = fma(v[k][i].y, b[k].y, fma(v[k][i].x, b[k].x, acc[2 * i]));
+          acc[2 * i + 1] = fma(-v[k][i].y, b[k].x, fma(v[k][i].x, b[k].y, acc[2 * i + 1]));
+        }
+      }
+      const double s = wave::sum16(acc);
+      if ((lane & 3) == 0) lds[wv][2 * c0 + (lane >> 2)] += s;
     }
   }
-  reduce_or_partial(acc, 2 * nb, lds, red, part, f, r);
+  __syncthreads();
+  const int nv = 2 * nb;
+  if (threadIdx.x < nv) red[threadIdx.x] = (lds[0][threadIdx.x] + lds[1][threadIdx.x]) + (lds[2][threadIdx.x] + lds[3][threadIdx.x]);
+  __syncthreads();
+  finish_or_partial(nv, red, part, f, r);
 }
 
-template <typename RV>
-__global__ __launch_bounds__(256) void gs_update_norm_kernel(const Cx<RV>* __restrict__ V, int nb,
+// b[k] -= sum_i h_i v_i[p[k]], hs zero from nb up to a multiple of eight
+__device__ __forceinline__ void long_update(c128 (&b)[LONG_EL], const int64_t (&p)[LONG_EL], const c128* __restrict__ Vr,
+                                            int nb, int64_t vstride, const c128* hs) {
+  for (int c0 = 0; c0 < nb; c0 += 8) {
+    c128 v[LONG_EL][8];
+#pragma unroll
+    for (int i = 0; i < 8; ++i) {
+      const c128* vi = Vr + min(c0 + i, nb - 1) * vstride;
+#pragma unroll
+      for (int k = 0; k < LONG_EL; ++k) v[k][i] = vi[p[k]];
+    }
+#pragma unroll
+    for (int i = 0; i < 8; ++i) {
+#pragma unroll
+      for (int k = 0; k < LONG_EL; ++k) b[k] = b[k] - cprod<true>(hs[c0 + i], v[k][i]);
+    }
+  }
+}
+
+__device__ __forceinline__ void long_coefficients(c128* hs, const c128* __restrict__ h, int nb) {
+  if (threadIdx.x < NBMAX) hs[threadIdx.x] = threadIdx.x < nb ? h[threadIdx.x] : cmk(0.0, 0.0);
+  __syncthreads();
+}
+
+__global__ __launch_bounds__(256) void gs_update_norm_kernel(const c128* __restrict__ V, int nb,
                                                              c128* __restrict__ w, int64_t n, int64_t vstride,
                                                              const c128* __restrict__ h, int hld,
                                                              double* __restrict__ part, Fin f) {
@@ -211,53 +268,56 @@ __global__ __launch_bounds__(256) void gs_update_norm_kernel(const Cx<RV>* __res
   __shared__ double red[NVMAX];
   __shared__ c128 hs[NBMAX];
   const int r = blockIdx.y;
-  if (threadIdx.x < nb) hs[threadIdx.x] = h[(int64_t)r * hld + threadIdx.x];
-  __syncthreads();
+  long_coefficients(hs, h + (int64_t)r * hld, nb);
   double acc[1] = {0.0};
   c128* wr = w + (int64_t)r * n;
-  const Cx<RV>* Vr = V + (int64_t)r * n;
-  for (int64_t p = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; p < n; p += (int64_t)gridDim.x * blockDim.x) {
-    c128 v = wr[p];
+  for (int64_t p0 = (int64_t)blockIdx.x * (256 * LONG_EL); p0 < n; p0 += (int64_t)gridDim.x * (256 * LONG_EL)) {
+    c128 b[LONG_EL];
+    int64_t p[LONG_EL];
 #pragma unroll
-    for (int i = 0; i < NBMAX; ++i) {
-      if (i < nb) {
-        const Cx<RV> a = Vr[i * vstride + p];
-        const c128 hi = hs[i];
-        v.x -= hi.x * (double)a.x - hi.y * (double)a.y;
-        v.y -= hi.x * (double)a.y + hi.y * (double)a.x;
+    for (int k = 0; k < LONG_EL; ++k) {
+      const int64_t e = p0 + 256 * k + threadIdx.x;
+      p[k] = e < n ? e : 0;
+      b[k] = wr[p[k]];
+    }
+    long_update(b, p, V + (int64_t)r * n, nb, vstride, hs);
+#pragma unroll
+    for (int k = 0; k < LONG_EL; ++k) {
+      const int64_t e = p0 + 256 * k + threadIdx.x;
+      if (e < n) {
+        wr[e] = b[k];
+        acc[0] += cabs2(b[k]);
       }
     }
-    wr[p] = v;
-    acc[0] += v.x * v.x + v.y * v.y;
   }
   reduce_or_partial(acc, 1, lds, red, part, f, r);
 }
 
-template <typename RV>
-__global__ __launch_bounds__(256) void gs_update_store_kernel(Cx<RV>* __restrict__ V, int nb,
+__global__ __launch_bounds__(256) void gs_update_store_kernel(c128* __restrict__ V, int nb,
                                                               const c128* __restrict__ w, int64_t n, int64_t vstride,
                                                               const c128* __restrict__ h, int hld,
                                                               const double* __restrict__ invb) {
   __shared__ c128 hs[NBMAX];
   const int r = blockIdx.y;
-  if (threadIdx.x < nb) hs[threadIdx.x] = h[(int64_t)r * hld + threadIdx.x];
-  __syncthreads();
+  long_coefficients(hs, h + (int64_t)r * hld, nb);
   const double sc = invb[r];
   const c128* wr = w + (int64_t)r * n;
-  const Cx<RV>* Vr = V + (int64_t)r * n;
-  Cx<RV>* out = V + (int64_t)nb * vstride + (int64_t)r * n;
-  for (int64_t p = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; p < n; p += (int64_t)gridDim.x * blockDim.x) {
-    c128 v = wr[p];
+  c128* out = V + (int64_t)nb * vstride + (int64_t)r * n;
+  for (int64_t p0 = (int64_t)blockIdx.x * (256 * LONG_EL); p0 < n; p0 += (int64_t)gridDim.x * (256 * LONG_EL)) {
+    c128 b[LONG_EL];
+    int64_t p[LONG_EL];
 #pragma unroll
-    for (int i = 0; i < NBMAX; ++i) {
-      if (i < nb) {
-        const Cx<RV> a = Vr[i * vstride + p];
-        const c128 hi = hs[i];
-        v.x -= hi.x * (double)a.x - hi.y * (double)a.y;
-        v.y -= hi.x * (double)a.y + hi.y * (double)a.x;
-      }
+    for (int k = 0; k < LONG_EL; ++k) {
+      const int64_t e = p0 + 256 * k + threadIdx.x;
+      p[k] = e < n ? e : 0;
+      b[k] = wr[p[k]];
     }
-    out[p] = cmk((RV)(v.x * sc), (RV)(v.y * sc));
+    long_update(b, p, V + (int64_t)r * n, nb, vstride, hs);
+#pragma unroll
+    for (int k = 0; k < LONG_EL; ++k) {
+      const int64_t e = p0 + 256 * k + threadIdx.x;
+      if (e < n) out[e] = sc * b[k];
+    }
   }
 }
 
@@ -401,8 +461,9 @@ __device__ __forceinline__ void split_finish(const Fin& f, int r, const double* 
 }
 
 // part[(r 16 + wave) 64 + 2 i + (0: re, 1: im)] = the wavefront's sum of <u_i, w>, i in the
-// chunk blockIdx.z.  Blocks x = 16, z = 0 (where launched) complete the previous step (prev)
-// beside.  (A wavefront per 64 pairs meeting in LDS, as in the update: 5.8 us against 4.3 at
+// chunk blockIdx.z (past the last basis vector the chunk repeats it, into places that nothing
+// reads: no branch per vector).  Blocks x = 16, z = 0 (where launched) complete the previous step
+// (prev) beside.  (A wavefront per 64 pairs meeting in LDS, as in the update: 5.8 us against 4.3 at
 // n = 4096.)
 template <typename RW>
 __global__ __launch_bounds__(64) void gs1_split_dots_kernel(const c64* __restrict__ U, int nb,
@@ -418,6 +479,9 @@ __global__ __launch_bounds__(64) void gs1_split_dots_kernel(const c64* __restric
   const Pair<RW>* wr = reinterpret_cast<const Pair<RW>*>(w + (int64_t)r * ld);
   const Pair<float>* Ur = reinterpret_cast<const Pair<float>*>(U + (int64_t)r * ld);
   const int64_t np = n / 2, vs = vstride / 2;
+  const Pair<float>* Uc[SPLIT_CHUNK];
+#pragma unroll
+  for (int i = 0; i < SPLIT_CHUNK; ++i) Uc[i] = Ur + min(c0 + i, nb - 1) * vs;
   double acc[2 * SPLIT_CHUNK];
 #pragma unroll
   for (int q = 0; q < 2 * SPLIT_CHUNK; ++q) acc[q] = 0.0;
@@ -426,16 +490,13 @@ __global__ __launch_bounds__(64) void gs1_split_dots_kernel(const c64* __restric
     const Pair<RW> b = wr[p];
     Pair<float> u[SPLIT_CHUNK];
 #pragma unroll
-    for (int i = 0; i < SPLIT_CHUNK; ++i)
-      if (c0 + i < nb) u[i] = Ur[(c0 + i) * vs + p];
+    for (int i = 0; i < SPLIT_CHUNK; ++i) u[i] = Uc[i][p];
 #pragma unroll
     for (int i = 0; i < SPLIT_CHUNK; ++i) {
-      if (c0 + i < nb) {
-        acc[2 * i] += (double)u[i].a.x * b.a.x + (double)u[i].a.y * b.a.y + (double)u[i].b.x * b.b.x +
-                      (double)u[i].b.y * b.b.y;
-        acc[2 * i + 1] += (double)u[i].a.x * b.a.y - (double)u[i].a.y * b.a.x + (double)u[i].b.x * b.b.y -
-                          (double)u[i].b.y * b.b.x;
-      }
+      acc[2 * i] += (double)u[i].a.x * b.a.x + (double)u[i].a.y * b.a.y + (double)u[i].b.x * b.b.x +
+                    (double)u[i].b.y * b.b.y;
+      acc[2 * i + 1] += (double)u[i].a.x * b.a.y - (double)u[i].a.y * b.a.x + (double)u[i].b.x * b.b.y -
+                        (double)u[i].b.y * b.b.x;
     }
   }
   const double s = wave::sum16(acc);
@@ -445,14 +506,14 @@ __global__ __launch_bounds__(64) void gs1_split_dots_kernel(const c64* __restric
 // h_i = s_w s_i <u_i, w> from the partial sums, u_{j+1} = s_w w - sum_i h_i s_i u_i on the
 // wavefront's pairs, npart[r 16 + wave] = their part of ||u_{j+1}||^2 (of the stored values).
 // A wavefront per 64 pairs (q-th of the workgroup: pairs 1024 q + 64 wave ..), the basis loads
-// out before the sums are ready.
-template <typename RW>
+// out before the sums are ready.  NBT: the basis count rounded up to a multiple of 8; the vectors
+// past the last repeat it with a coefficient of zero (no branch per vector).
+template <typename RW, int NBT>
 __global__ __launch_bounds__(512) void gs1_split_update_kernel(c64* __restrict__ U, int nb,
                                                                const Cx<RW>* __restrict__ w, int64_t n,
                                                                int64_t vstride, const double* __restrict__ wscale,
                                                                const double* __restrict__ part,
                                                                double* __restrict__ npart, Fin f, int64_t ld) {
-  constexpr int CH = 16;
   __shared__ double cf[2 * NBMAX];  // h_i s_i
   __shared__ double nq[8][64];
   const int r = blockIdx.y, lane = threadIdx.x & 63, q = threadIdx.x >> 6;
@@ -462,10 +523,9 @@ __global__ __launch_bounds__(512) void gs1_split_update_kernel(c64* __restrict__
   const int64_t np = n / 2, vs = vstride / 2, p = 64 * (SPLIT_WAVES * q + blockIdx.x) + lane;
   const int64_t pl = p < np ? p : 0;  // idle lanes load pair 0
   const Pair<RW> b = wr[pl];
-  Pair<float> u[CH];
+  Pair<float> u[NBT];
 #pragma unroll
-  for (int i = 0; i < CH; ++i)
-    if (i < nb) u[i] = Ur[i * vs + pl];
+  for (int i = 0; i < NBT; ++i) u[i] = Ur[min(i, nb - 1) * vs + pl];
   if (threadIdx.x < 2 * nb) {
     const double* pr = part + (int64_t)r * SPLIT_WAVES * NVMAX + lane;
     double v[SPLIT_WAVES];
@@ -478,23 +538,21 @@ __global__ __launch_bounds__(512) void gs1_split_update_kernel(c64* __restrict__
     const double h = ws * sc * sum;
     if (blockIdx.x == 0) reinterpret_cast<double*>(f.h + (int64_t)r * f.hld)[lane] = h;
     cf[lane] = h * sc;
+  } else if (threadIdx.x < 2 * NBT) {
+    cf[lane] = 0.0;
   }
   __syncthreads();
-  c128 v0 = cmk(ws * b.a.x, ws * b.a.y), v1 = cmk(ws * b.b.x, ws * b.b.y);
-  for (int c0 = 0; c0 < nb; c0 += CH) {
-    if (c0 > 0) {
+  c128 v0, v1;
+  {
+#pragma clang fp contract(off)
+    v0 = cmk(ws * b.a.x, ws * b.a.y);  // rounded, not fused into the first subtraction
+    v1 = cmk(ws * b.b.x, ws * b.b.y);
+  }
 #pragma unroll
-      for (int i = 0; i < CH; ++i)
-        if (c0 + i < nb) u[i] = Ur[(c0 + i) * vs + pl];
-    }
-#pragma unroll
-    for (int i = 0; i < CH; ++i) {
-      if (c0 + i < nb) {
-        const c128 h = cmk(cf[2 * (c0 + i)], cf[2 * (c0 + i) + 1]);
-        v0 = v0 - cprod<true>(h, ccast<double>(u[i].a));
-        v1 = v1 - cprod<true>(h, ccast<double>(u[i].b));
-      }
-    }
+  for (int i = 0; i < NBT; ++i) {
+    const c128 h = cmk(cf[2 * i], cf[2 * i + 1]);
+    v0 = v0 - cprod<true>(h, ccast<double>(u[i].a));
+    v1 = v1 - cprod<true>(h, ccast<double>(u[i].b));
   }
   Pair<float> st;
   st.a = ccast<float>(v0);
@@ -559,8 +617,7 @@ __global__ __launch_bounds__(TWO_BLOCK) void gs2_split_dots_kernel(const c128* _
   c128 v[8];
   const c128 b = w[o];
 #pragma unroll
-  for (int i = 0; i < 8; ++i)
-    if (c0 + i < nb) v[i] = V[(c0 + i) * vstride + o];
+  for (int i = 0; i < 8; ++i) v[i] = V[min(c0 + i, nb - 1) * vstride + o];
   double acc[16];
 #pragma unroll
   for (int i = 0; i < 8; ++i) {
@@ -577,7 +634,8 @@ __global__ __launch_bounds__(TWO_BLOCK) void gs2_split_dots_kernel(const c128* _
   }
 }
 
-// NBT: the basis count rounded up to 8, 16 or 32
+// NBT: the basis count rounded up to a multiple of 8 (the vectors past the last repeat it with
+// a coefficient of zero)
 template <int NBT>
 __global__ __launch_bounds__(TWO_BLOCK) void gs2_split_update_dots_kernel(const c128* __restrict__ V, int nb,
                                                                           c128* __restrict__ w, int64_t n,
@@ -592,13 +650,12 @@ __global__ __launch_bounds__(TWO_BLOCK) void gs2_split_update_dots_kernel(const 
   c128 v[NBT];
   c128 b = w[o];
 #pragma unroll
-  for (int i = 0; i < NBT; ++i)
-    if (i < nb) v[i] = V[i * vstride + o];
+  for (int i = 0; i < NBT; ++i) v[i] = V[min(i, nb - 1) * vstride + o];
+  if (threadIdx.x >= 2 * nb && threadIdx.x < 2 * NBT) h[threadIdx.x] = 0.0;
   two_add_partials(part1 + (int64_t)r * G * TWO_PART, G, 2 * nb, lds, h);
   if (blockIdx.x == 0 && threadIdx.x < 2 * nb) reinterpret_cast<double*>(f.h + (int64_t)r * f.hld)[threadIdx.x] = h[threadIdx.x];
 #pragma unroll
-  for (int i = 0; i < NBT; ++i)
-    if (i < nb) b = b - cprod<true>(cmk(h[2 * i], h[2 * i + 1]), v[i]);
+  for (int i = 0; i < NBT; ++i) b = b - cprod<true>(cmk(h[2 * i], h[2 * i + 1]), v[i]);
   if (on) w[o] = b;
 #pragma unroll
   for (int c0 = 0; c0 < NBT; c0 += 8) {
@@ -640,12 +697,11 @@ __global__ __launch_bounds__(TWO_BLOCK) void gs2_split_store_kernel(c128* __rest
   if (!completes) {
     b = w[o];
 #pragma unroll
-    for (int i = 0; i < NBT; ++i)
-      if (i < nb) v[i] = V[i * vstride + o];
+    for (int i = 0; i < NBT; ++i) v[i] = V[min(i, nb - 1) * vstride + o];
   }
   two_add_partials(part2 + (int64_t)r * G * TWO_PART, G, 2 * nb + 1, lds, h);
-  double h2n = 0.0;
-  for (int q = 0; q < 2 * nb; ++q) h2n = fma(h[q], h[q], h2n);
+  const int lane = threadIdx.x & 63;
+  const double h2n = wave::sum(lane < 2 * nb ? h[lane] * h[lane] : 0.0);
   const double beta = sqrt(fmax(h[2 * nb] - h2n, 0.0));
   if (completes) {
     const int l = threadIdx.x;
@@ -655,8 +711,10 @@ __global__ __launch_bounds__(TWO_BLOCK) void gs2_split_store_kernel(c128* __rest
   }
   const double inv = beta > 0.0 ? 1.0 / beta : 0.0;
 #pragma unroll
-  for (int i = 0; i < NBT; ++i)
-    if (i < nb) b = b - cprod<true>(cmk(h[2 * i], h[2 * i + 1]), v[i]);
+  for (int i = 0; i < NBT; ++i) {
+    const bool use = i < nb;  // (h[2 nb] is the norm)
+    b = b - cprod<true>(cmk(use ? h[2 * i] : 0.0, use ? h[2 * i + 1] : 0.0), v[i]);
+  }
   if (on) V[nb * vstride + o] = inv * b;
 }
 
@@ -715,7 +773,6 @@ int gs_max_basis() { return NBMAX; }
 // One Arnoldi step, two-pass form: orthogonalise w (FP64, [nrhs][n]) against V_0..V_j,
 // update the Hessenberg column and rotations, store V_{j+1} = w / ||w||.
 void arnoldi_step(dmlmc_ctx* ctx, c128* V, c128* w, int j, int64_t n, int nrhs, const KrylovArrays& k) {
-  using RV = double;
   const int nb = j + 1;
   if (nb > NBMAX) throw DmlmcError(DMLMC_EINVAL, "Krylov basis larger than the Gram-Schmidt limit");
   const int64_t vstride = (int64_t)nrhs * n;
@@ -742,13 +799,16 @@ void arnoldi_step(dmlmc_ctx* ctx, c128* V, c128* w, int j, int64_t n, int nrhs, 
       GS2_SPLIT(8);
     } else if (nb <= 16) {
       GS2_SPLIT(16);
+    } else if (nb <= 24) {
+      GS2_SPLIT(24);
     } else {
       GS2_SPLIT(NBMAX);
     }
 #undef GS2_SPLIT
     return;
   }
-  const int G = gs_blocks(2 * n, nrhs);  // one element per thread and iteration here
+  // (partial sums bounded as in gs_blocks)
+  const int G = (int)std::max<int64_t>(1, std::min<int64_t>(ceil_div(n, 256 * LONG_EL), 16384 / std::max(1, nrhs)));
   ctx->scratch_dots.ensure(sizeof(double) * (size_t)nrhs * G * NVMAX);
   double* part = ctx->scratch_dots.as<double>();
   dim3 grid(G, nrhs);
@@ -757,8 +817,8 @@ void arnoldi_step(dmlmc_ctx* ctx, c128* V, c128* w, int j, int64_t n, int nrhs, 
   fa.out = (double*)k.h1;
   fa.ostride = 2 * k.hld;
   {
-    KTimer kt(ctx, "gs_dots", (double)nrhs * n * (nb * sizeof(Cx<RV>) + sizeof(c128)));
-    hipLaunchKernelGGL((gs_dots_kernel<RV>), grid, dim3(256), 0, ctx->stream, V, nb, w, n, vstride, part, fa);
+    KTimer kt(ctx, "gs_dots", (double)nrhs * n * (nb * sizeof(c128) + sizeof(c128)));
+    hipLaunchKernelGGL(gs_dots_kernel, grid, dim3(256), 0, ctx->stream, V, nb, w, n, vstride, part, fa);
     LAUNCH_CHECK();
     launch_partial_finish(ctx, part, G, 2 * nb, fa, nrhs);
   }
@@ -767,8 +827,8 @@ void arnoldi_step(dmlmc_ctx* ctx, c128* V, c128* w, int j, int64_t n, int nrhs, 
   fb.out = k.nrm2;
   fb.ostride = 1;
   {
-    KTimer kt(ctx, "gs_update", (double)nrhs * n * (nb * sizeof(Cx<RV>) + 2 * sizeof(c128)));
-    hipLaunchKernelGGL((gs_update_norm_kernel<RV>), grid, dim3(256), 0, ctx->stream, V, nb, w, n, vstride, k.h1,
+    KTimer kt(ctx, "gs_update", (double)nrhs * n * (nb * sizeof(c128) + 2 * sizeof(c128)));
+    hipLaunchKernelGGL(gs_update_norm_kernel, grid, dim3(256), 0, ctx->stream, V, nb, w, n, vstride, k.h1,
                        k.hld, part, fb);
     LAUNCH_CHECK();
     launch_partial_finish(ctx, part, G, 1, fb, nrhs);
@@ -779,14 +839,14 @@ void arnoldi_step(dmlmc_ctx* ctx, c128* V, c128* w, int j, int64_t n, int nrhs, 
   fc.h = k.h2;
   fc.nrm2 = k.nrm2;
   {
-    KTimer kt(ctx, "gs_dots", (double)nrhs * n * (nb * sizeof(Cx<RV>) + sizeof(c128)));
-    hipLaunchKernelGGL((gs_dots_kernel<RV>), grid, dim3(256), 0, ctx->stream, V, nb, w, n, vstride, part, fc);
+    KTimer kt(ctx, "gs_dots", (double)nrhs * n * (nb * sizeof(c128) + sizeof(c128)));
+    hipLaunchKernelGGL(gs_dots_kernel, grid, dim3(256), 0, ctx->stream, V, nb, w, n, vstride, part, fc);
     LAUNCH_CHECK();
     launch_partial_finish(ctx, part, G, 2 * nb, fc, nrhs);
   }
   {
-    KTimer kt(ctx, "gs_update", (double)nrhs * n * (nb * sizeof(Cx<RV>) + sizeof(c128) + sizeof(Cx<RV>)));
-    hipLaunchKernelGGL((gs_update_store_kernel<RV>), grid, dim3(256), 0, ctx->stream, V, nb, w, n, vstride, k.h2,
+    KTimer kt(ctx, "gs_update", (double)nrhs * n * (nb * sizeof(c128) + sizeof(c128) + sizeof(c128)));
+    hipLaunchKernelGGL(gs_update_store_kernel, grid, dim3(256), 0, ctx->stream, V, nb, w, n, vstride, k.h2,
                        k.hld, k.invb);
     LAUNCH_CHECK();
   }
@@ -842,8 +902,18 @@ void arnoldi_step_cgs1(dmlmc_ctx* ctx, c64* U, double* scale, const Cx<RW>* w, i
     hipLaunchKernelGGL((gs1_split_dots_kernel<RW>), dgrid, dim3(64), 0, ctx->stream, U, nb, w, n, vstride, part, npart,
                        prev, ld);
     LAUNCH_CHECK();
-    hipLaunchKernelGGL((gs1_split_update_kernel<RW>), dim3(SPLIT_WAVES, nrhs), dim3(64 * per_lane), 0, ctx->stream, U,
-                       nb, w, n, vstride, wscale, part, npart, f, ld);
+#define GS1_SPLIT_UPDATE(NBT)                                                                                           \
+  hipLaunchKernelGGL((gs1_split_update_kernel<RW, NBT>), dim3(SPLIT_WAVES, nrhs), dim3(64 * per_lane), 0, ctx->stream, \
+                     U, nb, w, n, vstride, wscale, part, npart, f, ld)
+    if (nb <= 8)
+      GS1_SPLIT_UPDATE(8);
+    else if (nb <= 16)
+      GS1_SPLIT_UPDATE(16);
+    else if (nb <= 24)
+      GS1_SPLIT_UPDATE(24);
+    else
+      GS1_SPLIT_UPDATE(NBMAX);
+#undef GS1_SPLIT_UPDATE
     LAUNCH_CHECK();
     if (!deferred) {
       hipLaunchKernelGGL(gs1_split_finish_kernel, dim3(nrhs), dim3(64), 0, ctx->stream, npart, f);

@@ -29,6 +29,7 @@ SHAPES = {
     "132x16": ((48, 44), (4, 4), 8),   # 2112: the first in separate launches
     "1024x16": ((128, 128), (4, 4), 8),  # 16384: the largest with split Gram-Schmidt steps
     "1056x16": ((132, 128), (4, 4), 8),  # 16896: the first with the passes of long vectors
+    "1064x16": ((152, 112), (4, 4), 8),  # 17024: their last workgroup half empty
 }
 
 
