@@ -624,6 +624,59 @@ __global__ __launch_bounds__(256) void prolong_kernel(const Cx<R>* __restrict__ 
     if (q < nr) xf[(int64_t)(r0 + q) * ldf + tid] = acc[q];
 }
 
+// The same for eight test vectors on levels that fill the chip: thread per fine dof, every
+// blockIdx.y-th pair of right-hand sides.  A wavefront's 64 interpolation rows (128 bytes each in
+// FP64) are read by whole lines, eight lanes to a row, and handed over through LDS; read by their
+// own threads every load touches 64 lines, which do not stay in L1 for the row's other loads.
+// Measured in FP64 with 16 RHS onto 65536 sites of 2 dofs 32 -> 23 us, onto 2^20 sites 507 -> 331.
+template <typename R>
+__global__ __launch_bounds__(256) void prolong_rows_kernel(const Cx<R>* __restrict__ P, const Cx<R>* __restrict__ ec,
+                                                           Cx<R>* __restrict__ xf, int Lxf, int Ltf, int df, int ax,
+                                                           int at, int nrhs, int add, int64_t ldf, int64_t ldc) {
+  constexpr int N = 8, RB = 2;
+  __shared__ Cx<R> stage[4][64][N + 1];
+  const int64_t nf = (int64_t)Lxf * Ltf * df;
+  const int lane = threadIdx.x & 63;
+  Cx<R>(*rowsP)[N + 1] = stage[wave_index()];
+  const int64_t tid = xcd_block() * blockDim.x + threadIdx.x;
+  const unsigned me = (unsigned)(tid < nf ? tid : nf - 1);
+  const unsigned site = me / (unsigned)df;
+  const int dof = (int)(me - site * (unsigned)df);
+  const int t = (int)(site / (unsigned)Lxf), x = (int)(site - (unsigned)t * (unsigned)Lxf);
+  const int X = x / ax, T = t / at, h = df / 2;
+  const int64_t cs = (int64_t)X + (int64_t)(Lxf / ax) * T;
+  const int c = dof >= h, j = dof - c * h;
+  const int row = ((x - X * ax) + ax * (t - T * at)) * h + j;
+  const unsigned prow = (unsigned)((cs * 2 + c) * (int64_t)(ax * at * h) + row);
+#pragma unroll
+  for (int i = 0; i < 8; ++i) {
+    const int r = 8 * i + (lane >> 3);
+    rowsP[r][lane & 7] = P[(int64_t)(unsigned)__shfl((int)prow, r, 64) * N + (lane & 7)];
+  }
+  __builtin_amdgcn_wave_barrier();
+  Cx<R> pv[N];
+#pragma unroll
+  for (int k = 0; k < N; ++k) pv[k] = rowsP[lane][k];
+  const Cx<R>* er = ec + cs * 2 * N + c * N;
+  for (int r0 = blockIdx.y * RB; r0 < nrhs; r0 += gridDim.y * RB) {
+    Cx<R> acc[RB], e[RB][N];
+#pragma unroll
+    for (int q = 0; q < RB; ++q) {
+      const int64_t r = min(r0 + q, nrhs - 1);
+      acc[q] = add ? xf[r * ldf + me] : cmk((R)0, (R)0);
+#pragma unroll
+      for (int k = 0; k < N; ++k) e[q][k] = er[r * ldc + k];
+    }
+    __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+    for (int q = 0; q < RB; ++q) {
+#pragma unroll
+      for (int k = 0; k < N; ++k) cfma(acc[q], pv[k], e[q][k]);
+      if (tid < nf && r0 + q < nrhs) xf[(int64_t)(r0 + q) * ldf + tid] = acc[q];
+    }
+  }
+}
+
 // ---------------------------------------------------------------- matrix-core forms (d = 16, complex FP32)
 // One wavefront computes 16 (dofs) x 16 (RHS) tiles of one site with v_mfma_f32_16x16x4_f32:
 // lane l supplies A[l % 16][l / 16] and B[l / 16][l % 16] and receives D[4 (l / 16) + v][l % 16].
@@ -1012,25 +1065,26 @@ __global__ __launch_bounds__(256) void coarse16_f64_mfma_kernel(const c128* __re
   }
 }
 
-// The same on small levels: a wavefront per site and 16-RHS tile (blockIdx.y), every load out
-// before the first product (160 registers; the tiles' results are those of the form above).
+// The same with a wavefront per site and 16-RHS tile (a site's tiles in adjacent wavefronts),
+// every load out before the first product (160 registers; the results are those of the form above).
 // Measured at 256 sites, 48 RHS (the eigensolver's blocks): 18.1 -> 9.9 us.
 template <bool G5, typename RO = double>
 __global__ __launch_bounds__(256) void coarse16_f64_mfma_tile_kernel(const c128* __restrict__ A,
                                                                      const c128* __restrict__ in,
                                                                      Cx<RO>* __restrict__ out, int Lx, int Lt,
-                                                                     int nrhs, int64_t ldx, int64_t ldy,
+                                                                     int nrhs, int tiles, int64_t ldx, int64_t ldy,
                                                                      const c128* __restrict__ sub) {
   const int64_t V = (int64_t)Lx * Lt;
   const int lane = threadIdx.x & 63, w = wave_index();
-  const int64_t s = (int64_t)blockIdx.x * 4 + w;
+  const unsigned wv = (unsigned)(xcd_block() * 4 + w), site = wv / (unsigned)tiles;
+  const int64_t s = site;
   if (s >= V) return;  // wave-uniform
   const int row = lane & 15, kq = lane >> 4;
   const int prow = 4 * (row & 3) + (row >> 2);
   const Nbr nb = neighbours(s, Lx, Lt);
   const int64_t sites[5] = {s, nb.xp, nb.xm, nb.tp, nb.tm};
   const double sg = (G5 && kq >= 2) ? -1.0 : 1.0;
-  const int r = 16 * blockIdx.y + row;
+  const int r = 16 * (int)(wv - site * tiles) + row;
   const bool on = r < nrhs;
   const c128* x = in + (int64_t)min(r, nrhs - 1) * ldx + 4 * kq;
   const c128* Ab = A + s * 5 * 256 + 64 * kq + prow;
@@ -1776,8 +1830,11 @@ int launch_wilson_dots(dmlmc_ctx* ctx, const Level& L, const c64* z, c64* y, int
   return G;
 }
 
-// Sites below which the FP64 matrix-core stencil takes a wavefront per RHS tile
-constexpr int64_t F64_TILE_MAX_SITES = 2048;
+// Whether the FP64 matrix-core stencil takes a wavefront per RHS tile: on small levels, whose
+// launches are short of wavefronts, and with one tile, where the blocks are read once either way
+// and all of a site's loads are in flight (4096 sites, 16 RHS: 38 -> 28 us; 16384: 139 -> 113).
+// With two tiles a wavefront of its own reads the blocks again (65536 sites, 32 RHS: 660 -> 778 us).
+static bool f64_tile_form(int64_t V, int tiles) { return V < 2048 || tiles == 1; }
 
 // coarse_kernel with RB right-hand sides per thread; workgroups of 64 threads until 256-thread
 // ones would be 2048 (small levels spread over more CUs)
@@ -1854,18 +1911,19 @@ void launch_coarse(dmlmc_ctx* ctx, const Level& L, const Cx<R>* x, Cx<R>* y, int
   if (std::is_same<R, double>::value && d == 16 && nrhs >= 8) {
     // FP64 matrix cores pay from a few RHS on (a 16-wide tile); single vectors keep the
     // scalar kernel
-    dim3 grid((unsigned)ceil_div(V, 4));
-    if (V < F64_TILE_MAX_SITES) {
-      grid.y = (unsigned)ceil_div(nrhs, 16);
+    const int tiles = (int)ceil_div(nrhs, 16);
+    if (f64_tile_form(V, tiles)) {
+      const dim3 grid((unsigned)ceil_div(V * tiles, 4));
       if (gamma5_left)
         hipLaunchKernelGGL((coarse16_f64_mfma_tile_kernel<true>), grid, dim3(256), 0, ctx->stream, (const c128*)A,
-                           (const c128*)x, (c128*)y, L.Lx, L.Lt, nrhs, ldx, ldy, (const c128*)nullptr);
+                           (const c128*)x, (c128*)y, L.Lx, L.Lt, nrhs, tiles, ldx, ldy, (const c128*)nullptr);
       else
         hipLaunchKernelGGL((coarse16_f64_mfma_tile_kernel<false>), grid, dim3(256), 0, ctx->stream, (const c128*)A,
-                           (const c128*)x, (c128*)y, L.Lx, L.Lt, nrhs, ldx, ldy, (const c128*)sub);
+                           (const c128*)x, (c128*)y, L.Lx, L.Lt, nrhs, tiles, ldx, ldy, (const c128*)sub);
       LAUNCH_CHECK();
       return;
     }
+    const dim3 grid((unsigned)ceil_div(V, 4));
     if (gamma5_left)
       hipLaunchKernelGGL((coarse16_f64_mfma_kernel<true>), grid, dim3(256), 0, ctx->stream, (const c128*)A,
                          (const c128*)x, (c128*)y, L.Lx, L.Lt, nrhs, ldx, ldy, (const c128*)nullptr);
@@ -1919,13 +1977,13 @@ void apply_residual_to32(dmlmc_ctx* ctx, const Level& L, const c128* x, const c1
   const int d = L.dofs;
   KTimer kt(ctx, "coarse", vec_bytes + (double)V * 5 * d * d * sizeof(c128));
   if (d == 16 && nrhs >= 8) {
-    const dim3 grid((unsigned)ceil_div(V, 4), V < F64_TILE_MAX_SITES ? (unsigned)ceil_div(nrhs, 16) : 1u);
-    if (V < F64_TILE_MAX_SITES)
-      hipLaunchKernelGGL((coarse16_f64_mfma_tile_kernel<false, float>), grid, dim3(256), 0, ctx->stream,
-                         L.A64.as<c128>(), x, r, L.Lx, L.Lt, nrhs, ldx, ldr, b);
+    const int tiles = (int)ceil_div(nrhs, 16);
+    if (f64_tile_form(V, tiles))
+      hipLaunchKernelGGL((coarse16_f64_mfma_tile_kernel<false, float>), dim3((unsigned)ceil_div(V * tiles, 4)), dim3(256),
+                         0, ctx->stream, L.A64.as<c128>(), x, r, L.Lx, L.Lt, nrhs, tiles, ldx, ldr, b);
     else
-      hipLaunchKernelGGL((coarse16_f64_mfma_kernel<false, float>), grid, dim3(256), 0, ctx->stream, L.A64.as<c128>(),
-                         x, r, L.Lx, L.Lt, nrhs, ldx, ldr, b);
+      hipLaunchKernelGGL((coarse16_f64_mfma_kernel<false, float>), dim3((unsigned)ceil_div(V, 4)), dim3(256), 0,
+                         ctx->stream, L.A64.as<c128>(), x, r, L.Lx, L.Lt, nrhs, ldx, ldr, b);
     LAUNCH_CHECK();
     return;
   }
@@ -2161,6 +2219,16 @@ void launch_prolong(dmlmc_ctx* ctx, const Level& L, const Cx<R>* ec, Cx<R>* xf, 
   }
   constexpr int RB = 4;
   dim3 grid((unsigned)ceil_div(nf, 256), (unsigned)ceil_div(nrhs, RB));
+  if (L.N == 8 && ceil_div(nf, 256) >= 256) {
+    // about 1024 workgroups, a pair of right-hand sides each at least (as many more re-read P:
+    // 1024^2, 16 RHS 331 us with one workgroup a row block, 382 with four)
+    const int64_t blocks = ceil_div(nf, 256);
+    const dim3 rows_grid((unsigned)blocks, (unsigned)std::min<int64_t>(ceil_div(nrhs, 2), ceil_div(1024, blocks)));
+    hipLaunchKernelGGL((prolong_rows_kernel<R>), rows_grid, dim3(256), 0, ctx->stream, P, ec, xf, L.Lx, L.Lt, L.dofs, L.ax,
+                       L.at, nrhs, add ? 1 : 0, ldf, ldc);
+    LAUNCH_CHECK();
+    return;
+  }
   if (L.N == CHUNK)
     hipLaunchKernelGGL((prolong_kernel<R, RB, CHUNK>), grid, dim3(256), 0, ctx->stream, P, ec, xf, L.Lx, L.Lt, L.dofs,
                        L.ax, L.at, L.N, nrhs, add ? 1 : 0, ldf, ldc);

@@ -26,6 +26,7 @@ SHAPES = {
     "rows8": ((16, 16), (4, 2), 3),    # 8, 12 and 24 rows per interpolation block: one chunk of eight,
     "rows12": ((16, 12), (4, 3), 4),   # one and a remainder, three
     "rows24": ((16, 24), (4, 6), 5),
+    "2079x16": ((252, 132), (4, 4), 8),  # 66528 fine dofs: prolongation by whole rows, a ragged last block
     "132x16": ((48, 44), (4, 4), 8),   # 2112: the first in separate launches
     "1024x16": ((128, 128), (4, 4), 8),  # 16384: the largest with split Gram-Schmidt steps
     "1056x16": ((132, 128), (4, 4), 8),  # 16896: the first with the passes of long vectors
@@ -116,7 +117,8 @@ def test_coarsest_gmres(shape, prec, k):
 
 
 @pytest.mark.parametrize("nrhs", [1, 3, 8, 17, 33])
-@pytest.mark.parametrize("shape", ["8x2", "16x8", "8x12", "60x10", "64x16", "50x24", "132x16", "rows8", "rows12", "rows24"])
+@pytest.mark.parametrize("shape", ["8x2", "16x8", "8x12", "60x10", "64x16", "50x24", "132x16", "rows8", "rows12", "rows24",
+                                   "2079x16"])
 def test_coarse_operator_and_transfers(shape, nrhs):
     """D, P^H and P of small levels: one right-hand side, the remainders of the groups of 4
     and 16, FP64 (a matrix-core tile per wavefront from 8 on at 16 dofs) and complex FP32."""
