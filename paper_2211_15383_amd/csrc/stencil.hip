@@ -1065,36 +1065,46 @@ __global__ __launch_bounds__(256) void coarse16_f64_mfma_kernel(const c128* __re
   }
 }
 
+// Position of entry c of RHS row r in a wavefront's 4 KB of LDS (chunks XOR-swizzled by the row)
+__device__ __forceinline__ int sw64(int r, int c) { return r * 16 + (c ^ r); }
+
 // The same with a wavefront per site and 16-RHS tile (a site's tiles in adjacent wavefronts),
 // every load out before the first product (160 registers; the results are those of the form above).
-// Measured at 256 sites, 48 RHS (the eigensolver's blocks): 18.1 -> 9.9 us.
-template <bool G5, typename RO = double>
+// STAGED: vectors are read and written 16 lanes to a row's 256 bytes and change to the
+// fragments' layout in LDS; read in that layout each load touches 64 pieces of 16 bytes, which is
+// what a launch over few sites waits for.  Measured at 256 sites, 48 RHS (the eigensolver's
+// blocks): 18.1 us in the form above, 9.9 here, 8.0 staged; at 4096 sites, 16 RHS 28 us, staged 31.
+template <bool G5, bool STAGED, typename RO = double>
 __global__ __launch_bounds__(256) void coarse16_f64_mfma_tile_kernel(const c128* __restrict__ A,
                                                                      const c128* __restrict__ in,
                                                                      Cx<RO>* __restrict__ out, int Lx, int Lt,
                                                                      int nrhs, int tiles, int64_t ldx, int64_t ldy,
                                                                      const c128* __restrict__ sub) {
+  __shared__ c128 stage[STAGED ? 4 : 1][STAGED ? 256 : 1];
   const int64_t V = (int64_t)Lx * Lt;
   const int lane = threadIdx.x & 63, w = wave_index();
   const unsigned wv = (unsigned)(xcd_block() * 4 + w), site = wv / (unsigned)tiles;
   const int64_t s = site;
-  if (s >= V) return;  // wave-uniform
+  if (s >= V) return;  // wave-uniform; no workgroup barrier below
+  c128* buf = stage[STAGED ? w : 0];
   const int row = lane & 15, kq = lane >> 4;
   const int prow = 4 * (row & 3) + (row >> 2);
   const Nbr nb = neighbours(s, Lx, Lt);
   const int64_t sites[5] = {s, nb.xp, nb.xm, nb.tp, nb.tm};
   const double sg = (G5 && kq >= 2) ? -1.0 : 1.0;
-  const int r = 16 * (int)(wv - site * tiles) + row;
+  const int r0 = 16 * (int)(wv - site * tiles), r = r0 + row;
   const bool on = r < nrhs;
-  const c128* x = in + (int64_t)min(r, nrhs - 1) * ldx + 4 * kq;
   const c128* Ab = A + s * 5 * 256 + 64 * kq + prow;
+  // load i, t: row 4 i + kq, entry `row` (staged), or row `row`, entry 4 kq + t
+  auto row_of = [&](int i) { return r0 + (STAGED ? 4 * i + kq : row); };
+  auto entry_of = [&](int i) { return STAGED ? row : 4 * kq + i; };
   c128 a[5][4], u[5][4];
 #pragma unroll
   for (int dir = 0; dir < 5; ++dir) {
 #pragma unroll
     for (int t = 0; t < 4; ++t) {
       a[dir][t] = Ab[dir * 256 + 16 * t];
-      u[dir][t] = x[sites[dir] * 16 + t];
+      u[dir][t] = in[(int64_t)min(row_of(t), nrhs - 1) * ldx + sites[dir] * 16 + entry_of(t)];
     }
   }
   __builtin_amdgcn_sched_barrier(0);
@@ -1102,15 +1112,28 @@ __global__ __launch_bounds__(256) void coarse16_f64_mfma_tile_kernel(const c128*
   f64x4 re = {0.0, 0.0, 0.0, 0.0}, im = re;
 #pragma unroll
   for (int dir = 0; dir < 5; ++dir) {
+    if constexpr (STAGED) {  // LDS operations of a wavefront complete in order
+#pragma unroll
+      for (int t = 0; t < 4; ++t) buf[sw64(4 * t + kq, row)] = u[dir][t];
+      __builtin_amdgcn_wave_barrier();
+#pragma unroll
+      for (int t = 0; t < 4; ++t) u[dir][t] = buf[sw64(row, 4 * kq + t)];
+      __builtin_amdgcn_wave_barrier();
+    }
 #pragma unroll
     for (int t = 0; t < 4; ++t) cmfma64(re, im, a[dir][t], on ? u[dir][t] : zero);
   }
-  if (!on) return;
+  if constexpr (STAGED) {
+#pragma unroll
+    for (int q = 0; q < 4; ++q) buf[sw64(row, 4 * kq + q)] = cmk(sg * re[q], sg * im[q]);
+    __builtin_amdgcn_wave_barrier();
+  }
 #pragma unroll
   for (int q = 0; q < 4; ++q) {
-    const int64_t e = s * 16 + 4 * kq + q;
-    const c128 y = cmk(sg * re[q], sg * im[q]);
-    out[(int64_t)r * ldy + e] = ccast<RO>(sub ? sub[(int64_t)r * ldx + e] - y : y);
+    const int64_t e = s * 16 + entry_of(q);
+    const c128 y = STAGED ? buf[sw64(4 * q + kq, row)] : cmk(sg * re[q], sg * im[q]);
+    const int64_t ro = row_of(q);
+    if (ro < nrhs) out[ro * ldy + e] = ccast<RO>(sub ? sub[ro * ldx + e] - y : y);
   }
 }
 
@@ -1834,7 +1857,21 @@ int launch_wilson_dots(dmlmc_ctx* ctx, const Level& L, const c64* z, c64* y, int
 // launches are short of wavefronts, and with one tile, where the blocks are read once either way
 // and all of a site's loads are in flight (4096 sites, 16 RHS: 38 -> 28 us; 16384: 139 -> 113).
 // With two tiles a wavefront of its own reads the blocks again (65536 sites, 32 RHS: 660 -> 778 us).
-static bool f64_tile_form(int64_t V, int tiles) { return V < 2048 || tiles == 1; }
+constexpr int64_t F64_SMALL_SITES = 2048;
+static bool f64_tile_form(int64_t V, int tiles) { return V < F64_SMALL_SITES || tiles == 1; }
+
+template <bool G5, typename RO>
+static void launch_f64_tiles(dmlmc_ctx* ctx, const Level& L, const c128* A, const c128* x, Cx<RO>* y, int nrhs,
+                             int tiles, int64_t ldx, int64_t ldy, const c128* sub) {
+  const dim3 grid((unsigned)ceil_div(L.sites() * tiles, 4));
+  if (L.sites() < F64_SMALL_SITES)
+    hipLaunchKernelGGL((coarse16_f64_mfma_tile_kernel<G5, true, RO>), grid, dim3(256), 0, ctx->stream, A, x, y, L.Lx,
+                       L.Lt, nrhs, tiles, ldx, ldy, sub);
+  else
+    hipLaunchKernelGGL((coarse16_f64_mfma_tile_kernel<G5, false, RO>), grid, dim3(256), 0, ctx->stream, A, x, y, L.Lx,
+                       L.Lt, nrhs, tiles, ldx, ldy, sub);
+  LAUNCH_CHECK();
+}
 
 // coarse_kernel with RB right-hand sides per thread; workgroups of 64 threads until 256-thread
 // ones would be 2048 (small levels spread over more CUs)
@@ -1913,14 +1950,11 @@ void launch_coarse(dmlmc_ctx* ctx, const Level& L, const Cx<R>* x, Cx<R>* y, int
     // scalar kernel
     const int tiles = (int)ceil_div(nrhs, 16);
     if (f64_tile_form(V, tiles)) {
-      const dim3 grid((unsigned)ceil_div(V * tiles, 4));
       if (gamma5_left)
-        hipLaunchKernelGGL((coarse16_f64_mfma_tile_kernel<true>), grid, dim3(256), 0, ctx->stream, (const c128*)A,
-                           (const c128*)x, (c128*)y, L.Lx, L.Lt, nrhs, tiles, ldx, ldy, (const c128*)nullptr);
+        launch_f64_tiles<true, double>(ctx, L, (const c128*)A, (const c128*)x, (c128*)y, nrhs, tiles, ldx, ldy, nullptr);
       else
-        hipLaunchKernelGGL((coarse16_f64_mfma_tile_kernel<false>), grid, dim3(256), 0, ctx->stream, (const c128*)A,
-                           (const c128*)x, (c128*)y, L.Lx, L.Lt, nrhs, tiles, ldx, ldy, (const c128*)sub);
-      LAUNCH_CHECK();
+        launch_f64_tiles<false, double>(ctx, L, (const c128*)A, (const c128*)x, (c128*)y, nrhs, tiles, ldx, ldy,
+                                        (const c128*)sub);
       return;
     }
     const dim3 grid((unsigned)ceil_div(V, 4));
@@ -1978,12 +2012,12 @@ void apply_residual_to32(dmlmc_ctx* ctx, const Level& L, const c128* x, const c1
   KTimer kt(ctx, "coarse", vec_bytes + (double)V * 5 * d * d * sizeof(c128));
   if (d == 16 && nrhs >= 8) {
     const int tiles = (int)ceil_div(nrhs, 16);
-    if (f64_tile_form(V, tiles))
-      hipLaunchKernelGGL((coarse16_f64_mfma_tile_kernel<false, float>), dim3((unsigned)ceil_div(V * tiles, 4)), dim3(256),
-                         0, ctx->stream, L.A64.as<c128>(), x, r, L.Lx, L.Lt, nrhs, tiles, ldx, ldr, b);
-    else
-      hipLaunchKernelGGL((coarse16_f64_mfma_kernel<false, float>), dim3((unsigned)ceil_div(V, 4)), dim3(256), 0,
-                         ctx->stream, L.A64.as<c128>(), x, r, L.Lx, L.Lt, nrhs, ldx, ldr, b);
+    if (f64_tile_form(V, tiles)) {
+      launch_f64_tiles<false, float>(ctx, L, L.A64.as<c128>(), x, r, nrhs, tiles, ldx, ldr, b);
+      return;
+    }
+    hipLaunchKernelGGL((coarse16_f64_mfma_kernel<false, float>), dim3((unsigned)ceil_div(V, 4)), dim3(256), 0,
+                       ctx->stream, L.A64.as<c128>(), x, r, L.Lx, L.Lt, nrhs, ldx, ldr, b);
     LAUNCH_CHECK();
     return;
   }
