@@ -438,8 +438,8 @@ __global__ __launch_bounds__(256) void gs1_update_kernel(c64* __restrict__ U, in
 // leaves the dots' partial sums, the next adds them up in the fixed order, updates the vector and
 // leaves the norm's, which the step's finish (or the next step's dots launch) adds up.
 // Measured over 24 steps at n = 4096, 20 RHS: the step in one workgroup per RHS took 22 us (one
-// CU's L2 rate), these two launches 4.5 + 5.2 us; at n = 16384, 32 RHS, 15.4 us against 6.0 + 4.9
-// and 4.1 for the finish.
+// CU's L2 rate), these two launches 4.4 + 4.5 us (the update 3.7 to 5.5 with 8 to 24 vectors); at
+// n = 16384, 32 RHS, 15.4 us against 5.2 + 5.4 and 4.1 for the finish.
 constexpr int SPLIT_WAVES = 16;
 constexpr int SPLIT_CHUNK = 8;  // basis vectors per workgroup of the dots launch
 

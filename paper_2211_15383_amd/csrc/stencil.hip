@@ -1918,7 +1918,7 @@ void launch_coarse(dmlmc_ctx* ctx, const Level& L, const Cx<R>* x, Cx<R>* y, int
     // swizzled LDS rows: 65536 sites 290 -> 267 us, 4096 sites 21.9 -> 20.1 us, 1024 sites
     // 8.0 -> 7.0 us against the best of the other forms); below 1024 sites two wavefronts per
     // site without the staging, whose latency is what such a launch takes (256 sites, 20 RHS:
-    // 7.6 -> 5.8 us)
+    // 7.6 -> 5.3 us)
     const int split = L.kv[KV_COARSE_SPLIT] > 0 ? L.kv[KV_COARSE_SPLIT] : (V < 1024 ? 2 : 3);
     dim3 grid((unsigned)ceil_div(V * (split == 2 ? 2 : 1), 4));
     if (split == 3) {
