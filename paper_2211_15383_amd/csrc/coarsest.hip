@@ -357,6 +357,23 @@ __device__ __forceinline__ void small_dots32(const Basis<float>& V, int nb, cons
     const bool on = t < np;
     const float4 b = on ? reinterpret_cast<const float4*>(w)[t] : make_float4(0.f, 0.f, 0.f, 0.f);
     const double bx0 = b.x, by0 = b.y, bx1 = b.z, by1 = b.w;
+    // eight vectors at a time where four would take a second round (all of them in LDS): n = 600,
+    // 24 steps 170 -> 167 us
+    if (nb > 4 * groups && V.kl >= nb) {
+      for (int c0 = 8 * (wv / nw); c0 < nb; c0 += 8 * groups) {
+        double acc[16];
+        float4 u[8];
+#pragma unroll
+        for (int i = 0; i < 8; ++i) u[i] = reinterpret_cast<const float4*>(V.lds + min(c0 + i, nb - 1) * n)[on ? t : 0];
+#pragma unroll
+        for (int i = 0; i < 8; ++i) {
+          acc[2 * i] = (((double)u[i].x * bx0 + (double)u[i].y * by0) + (double)u[i].z * bx1) + (double)u[i].w * by1;
+          acc[2 * i + 1] = (((double)u[i].x * by0 - (double)u[i].y * bx0) + (double)u[i].z * by1) - (double)u[i].w * bx1;
+        }
+        const double s = wave::sum16(acc);
+        if ((lane & 3) == 0) stage[(wv % nw) * 64 + 2 * c0 + (lane >> 2)] = s;
+      }
+    } else
     for (int c0 = 4 * (wv / nw); c0 < nb; c0 += 4 * groups) {
       double acc[8];
       float4 u[4];
