@@ -27,9 +27,9 @@
 //
 // Measured (MI355X) against the separate launches: 8 steps with 32 deflation vectors, n = 1024,
 // 32 right-hand sides 228 -> 82 us (a step 18.5 kclk: operator 11.7, of which 10.2 at 64 bytes
-// per clock, dots 3.3, update 1.8); 24 steps, n = 600 with 10 dofs, 5 right-hand sides 920 -> 177 us
+// per clock, dots 3.3, update 1.8); 24 steps, n = 600 with 10 dofs, 5 right-hand sides 920 -> 165 us
 // (operator 6.3 kclk, dots 6.8, update 4.1); complex FP64, 8 steps, n = 128 with 16 deflation
-// vectors 42 us (operator 3.4 kclk; 61 us and 8.5 kclk with the contraction in LDS partial sums).
+// vectors 41 us (operator 3.4 kclk; 61 us and 8.5 kclk with the contraction in LDS partial sums).
 #include <algorithm>
 
 #include "coarsest.h"
@@ -589,7 +589,13 @@ __global__ __launch_bounds__(CS_THREADS) void coarsest_small_kernel(SmallArgs a)
     c128* last = S.H + (m - 1) * (m + 1);
     givens_column(last, last[m].x, S.rc, S.rs, S.g, m - 1);
     __builtin_amdgcn_wave_barrier();
-    givens_backsub(S.H, m + 1, S.g, m);
+    // (with room for 16 columns and more in registers the kernel spilled)
+    c128 y;
+    if (m <= 8)
+      y = givens_backsub<8>(S.H, m + 1, S.g, m);
+    else
+      y = givens_backsub_lds(S.H, m + 1, S.g, m);
+    if (tid < m) S.g[tid] = y;
   }
   __syncthreads();
   if (tid < m) S.cf[tid] = S.sc[tid] * S.g[tid];

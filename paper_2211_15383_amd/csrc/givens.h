@@ -58,30 +58,63 @@ __device__ __forceinline__ c128 lane_value(c128 v, int lane) {
                               __builtin_amdgcn_readlane(__double2loint(v.y), lane)));
 }
 
-// One wavefront: g <- R^-1 g over the first k columns (k <= 60), R the rotated Hessenberg
-// matrix (column c at H + c ld), row by row from the last, each row's terms subtracted in
-// the order of the columns; zero pivots give zero coefficients.  Lane c holds g_c, then y_c.
-__device__ __forceinline__ void givens_backsub(const c128* H, int ld, c128* g, int k) {
-  const int c = threadIdx.x & 63;
-  const c128* col = H + (c < k ? c : 0) * ld;
-  c128 mine = g[c < k ? c : 0];
-  c128 h = col[k - 1];
-  for (int i = k - 1; i >= 0; --i) {
-    const c128 hi = h;
-    if (i > 0) h = col[i - 1];
-    // lane l > i: R[i][l] y_l; zero beyond the last column, so that four at a time may overrun
-    const c128 term = c < k ? cprod<false>(hi, mine) : cmk(0.0, 0.0);
+// One wavefront: R^-1 g over the first k <= K columns, entry c in lane c (lanes from k on hold
+// nothing), R the rotated Hessenberg matrix (column c at H + c ld), row by row from the last, each
+// row's terms subtracted in the order of the columns; zero pivots give zero coefficients.
+// Lane c has row c: t[l] holds R[c][l] and, once y_l is known (one broadcast a row), the term
+// R[c][l] y_l; a row's subtractions are a chain in registers.  (With the terms in column lanes each
+// took four readlanes, 28 clocks for two: 1270 clocks a row at k = 24.  Parts are selected one by
+// one: as a whole the compiler selects between copies in scratch memory.)
+template <int K>
+__device__ __forceinline__ c128 givens_backsub(const c128* H, int ld, const c128* g, int k) {
+  const int c = threadIdx.x & 63, row = c < k ? c : 0;
+  c128 mine = g[row], t[K];
+#pragma unroll
+  for (int l = 0; l < K; ++l) t[l] = H[min(l, k - 1) * ld + row];
+  const c128 hd = H[row * ld + row];
+  const double dd = fma(hd.x, hd.x, hd.y * hd.y);
+#pragma unroll
+  for (int i = K - 1; i >= 0; --i) {  // rows from k on leave no term
     c128 acc = mine;
-    for (int l = i + 1; l < k; l += 4) {
-      const c128 t0 = lane_value(term, l), t1 = lane_value(term, l + 1), t2 = lane_value(term, l + 2),
-                 t3 = lane_value(term, l + 3);
-      acc = ((acc - t0) - t1) - t2;
-      acc = acc - t3;
-    }
-    const double dd = fma(hi.x, hi.x, hi.y * hi.y);
-    if (c == i)
-      mine = dd > 0.0 ? cmk(fma(acc.x, hi.x, acc.y * hi.y) / dd, fma(acc.y, hi.x, -(acc.x * hi.y)) / dd)
-                      : cmk(0.0, 0.0);
+#pragma unroll
+    for (int l = i + 1; l < K; ++l) acc = acc - t[l];
+    const double nx = fma(acc.x, hd.x, acc.y * hd.y) / dd, ny = fma(acc.y, hd.x, -(acc.x * hd.y)) / dd;
+    c128 y;
+    y.x = dd > 0.0 ? nx : 0.0;
+    y.y = dd > 0.0 ? ny : 0.0;
+    mine.x = c == i ? y.x : mine.x;
+    mine.y = c == i ? y.y : mine.y;
+    const c128 term = cprod<false>(t[i], lane_value(y, i));
+    t[i].x = i < k ? term.x : 0.0;
+    t[i].y = i < k ? term.y : 0.0;
   }
-  if (c < k) g[c] = mine;
+  return mine;
+}
+
+// The same for any k <= 64 with the terms in the place of R (LDS), for a kernel that lacks the
+// registers.
+__device__ __forceinline__ c128 givens_backsub_lds(c128* H, int ld, const c128* g, int k) {
+  const int c = threadIdx.x & 63, row = c < k ? c : 0;
+  c128* hr = H + row;
+  c128 mine = g[row];
+  const c128 hd = hr[row * ld];
+  const double dd = fma(hd.x, hd.x, hd.y * hd.y);
+  for (int i = k - 1; i >= 0; --i) {
+    const c128 h = hr[i * ld];
+    c128 acc = mine;
+    int l = i + 1;
+    for (; l + 4 <= k; l += 4) {
+      const c128 t0 = hr[l * ld], t1 = hr[(l + 1) * ld], t2 = hr[(l + 2) * ld], t3 = hr[(l + 3) * ld];
+      acc = (((acc - t0) - t1) - t2) - t3;
+    }
+    for (; l < k; ++l) acc = acc - hr[l * ld];
+    const double nx = fma(acc.x, hd.x, acc.y * hd.y) / dd, ny = fma(acc.y, hd.x, -(acc.x * hd.y)) / dd;
+    c128 y;
+    y.x = dd > 0.0 ? nx : 0.0;
+    y.y = dd > 0.0 ? ny : 0.0;
+    mine.x = c == i ? y.x : mine.x;
+    mine.y = c == i ? y.y : mine.y;
+    if (c < i) hr[i * ld] = cprod<false>(h, lane_value(y, i));
+  }
+  return mine;
 }
