@@ -116,6 +116,37 @@ def test_coarsest_gmres(shape, prec, k):
             assert np.linalg.norm(x[r] - ref) <= tol * np.linalg.norm(ref), (shape, prec, k, r)
 
 
+@pytest.mark.parametrize("m", [1, 9, 16, 17, 25, 31])
+@pytest.mark.parametrize("prec", ["mixed", "fp64"])
+@pytest.mark.parametrize("shape", ["16x8", "132x16"])
+def test_iteration_counts(shape, prec, m):
+    """Back substitutions with room for 8, 16, 24 and 32 columns, and the one in LDS of the
+    one-launch kernel beyond 8; bounds as above."""
+    import torch
+
+    from paper_2211_15383_amd import dmlmc
+
+    (Lx, Lt), agg, ntv = SHAPES[shape]
+    rng = np.random.default_rng(31)
+
+    def cn(*s):
+        return rng.standard_normal(s) + 1j * rng.standard_normal(s)
+
+    H = dmlmc.Hierarchy(dmlmc.Context(0), rng.normal(0.0, 0.3, (2, Lt, Lx)), 0.1, [agg], [ntv],
+                        import_tv=[cn(2 * Lx * Lt, ntv)])
+    lx, lt, _ = H.level_info(2)
+    A = H.export(2, Dc=True)["Dc"]
+    H.solver_params(coarsest_iters=m)
+    mixed = prec == "mixed"
+    bd = torch.as_tensor(cn(2, H.n(2)), device="cuda").to(torch.complex64 if mixed else torch.complex128)
+    x = H.apply(dmlmc.OP_VCYCLE, 2, bd, torch.empty_like(bd),
+                prec=dmlmc.MIXED if mixed else dmlmc.FP64).cpu().numpy()
+    b = bd.cpu().numpy().astype(np.complex128)
+    for r in range(2):
+        ref = _gmres(lambda v: _blocks_apply(A, lx, lt, v), b[r], m)
+        assert np.linalg.norm(x[r] - ref) <= (2e-4 if mixed else 1e-11) * np.linalg.norm(ref), (shape, prec, m, r)
+
+
 @pytest.mark.parametrize("nrhs", [1, 3, 8, 17, 33])
 @pytest.mark.parametrize("shape", ["8x2", "16x8", "8x12", "60x10", "64x16", "50x24", "132x16", "rows8", "rows12", "rows24",
                                    "2079x16"])
