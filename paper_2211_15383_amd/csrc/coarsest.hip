@@ -43,7 +43,13 @@ constexpr int CS_WAVES = CS_THREADS / 64;
 constexpr int CS_COLS = 16;    // FP32 operator columns whose loads a thread has in flight (half in FP64)
 constexpr int CS_PAD = 8;      // coefficients of zero past the last basis vector
 constexpr int CS_MAX_M = 31;
-constexpr int CS_MAX_K = SMALL_LEVEL_N / 4;  // deflation vectors
+// Bytes of deflation vectors that a workgroup goes through by itself: twice per right-hand side,
+// at one CU's rate of 10 us a MB.  More of them take the two launches of small_deflate, about 8 us
+// and as much again for 512 vectors.  Complex FP32, n = 2048, 8 steps, one right-hand side: 512
+// vectors (8.4 MB) 383 us inside and 164 in launches of their own, 256 vectors 262 and 154; n =
+// 1024, 256 vectors (2.1 MB) 143 and 103; about equal at 512 KB.
+constexpr int64_t CS_DEFL_BYTES = 512 * 1024;
+constexpr int CS_MAX_K = 128;  // vectors that these bytes can be: k <= n / 4, k n <= 65536
 constexpr size_t CS_LDS = 160 * 1024;  // per workgroup
 
 // Krylov basis of a right-hand side: vectors 0 .. kl-1 in LDS, the others in global memory
@@ -75,10 +81,10 @@ struct SmallArgs {
   const void* b;
   void* x;
   const void* W;        // deflation vectors [k][n] (Gamma5 X), or NULL
-  const double* lam;
+  const double* lam;    // (k = 0 where b is deflated already)
   int kl;               // basis vectors 0 .. kl-1 are kept in LDS
   void* basis;          // the others: [nrhs][m + 1 - kl][n]
-  c128* e0;             // [nrhs][n], the deflation space's part of the solution
+  c128* e0;             // [nrhs][n], the deflation space's part of the solution, or NULL
 };
 
 // LDS of fixed size: constant addresses (with run-time offsets for all of them the kernel
@@ -304,6 +310,64 @@ __device__ __forceinline__ c128 small_dot(const Cx<R>* v, const Cx<R>* __restric
   return cmk(wave::sum(re), wave::sum(im));
 }
 
+// The exact solve on the deflation space: c = W^H b, r = b - W c and e0 = X Lambda^-1 c with
+// X = Gamma5 W.  Coefficient i by a wavefront (w: b in LDS) ...
+template <typename R>
+__device__ __forceinline__ void defl_coefficient(const Cx<R>* W, const double* lam, const Cx<R>* __restrict__ w, int n,
+                                                 int i, c128* __restrict__ c, c128* __restrict__ cl) {
+  const double li = 1.0 / lam[i];
+  const c128 d = small_dot(W + (int64_t)i * n, w, n);
+  if ((threadIdx.x & 63) == 0) {
+    c[i] = d;
+    cl[i] = li * d;
+  }
+}
+
+// ... and entry p of r (v: entry p of b) and of e0
+template <typename R>
+__device__ __forceinline__ void defl_entry(const Cx<R>* W, int n, int k, int d, int p, const c128* c, const c128* cl,
+                                           c128& v, c128& e0) {
+  c128 e = cmk(0.0, 0.0);
+#pragma unroll 8
+  for (int i = 0; i < k; ++i) {
+    const Cx<R> wi = W[(int64_t)i * n + p];
+    const c128 wd = cmk((double)wi.x, (double)wi.y);
+    v = v - c[i] * wd;
+    cfma(e, cl[i], wd);
+  }
+  e0 = p % d < d / 2 ? e : cmk(-e.x, -e.y);
+}
+
+// The same over many workgroups: coefficients c[r][2][k], 16 to a workgroup, then r and e0, 256
+// entries to a workgroup (in the order above, so the results are the same bits)
+template <typename R>
+__global__ __launch_bounds__(CS_THREADS) void defl_coefficients_kernel(const Cx<R>* __restrict__ W,
+                                                                       const double* __restrict__ lam,
+                                                                       const Cx<R>* __restrict__ b, int n, int k,
+                                                                       c128* __restrict__ c) {
+  __shared__ __align__(32) Cx<R> w[SMALL_LEVEL_N];
+  const int r = blockIdx.x, i = blockIdx.y * CS_WAVES + (threadIdx.x >> 6);
+  for (int p = threadIdx.x; p < n; p += CS_THREADS) w[p] = b[(int64_t)r * n + p];
+  __syncthreads();
+  c128* cr = c + (int64_t)r * 2 * k;
+  if (i < k) defl_coefficient(W, lam, w, n, i, cr, cr + k);
+}
+
+template <typename R>
+__global__ __launch_bounds__(256) void defl_residual_kernel(const Cx<R>* __restrict__ W, const c128* __restrict__ c,
+                                                            const Cx<R>* __restrict__ b, int n, int k, int d,
+                                                            Cx<R>* __restrict__ res, c128* __restrict__ e0) {
+  __shared__ c128 cs[SMALL_LEVEL_N / 2];
+  const int r = blockIdx.x, p = blockIdx.y * 256 + threadIdx.x;
+  for (int q = threadIdx.x; q < 2 * k; q += 256) cs[q] = c[(int64_t)r * 2 * k + q];
+  __syncthreads();
+  if (p >= n) return;
+  const int64_t o = (int64_t)r * n + p;
+  c128 v = ccast<double>(b[o]);
+  defl_entry(W, n, k, d, p, cs, cs + k, v, e0[o]);
+  res[o] = ccast<R>(v);
+}
+
 // red[i] = <v_i, w> for i < nb, a wavefront per basis vector, zero for the CS_PAD entries after
 // them; the caller synchronises
 __device__ __forceinline__ void small_dots64(const Basis<double>& V, int nb, const c128* __restrict__ w,
@@ -464,36 +528,19 @@ __global__ __launch_bounds__(CS_THREADS) void coarsest_small_kernel(SmallArgs a)
   }
   constexpr bool F32 = sizeof(R) == 4;
 
-  // the exact solve on the deflation space: c = W^H b, r = b - W c and e0 = X Lambda^-1 c with
-  // X = Gamma5 W, one pass over W for both
+  // the exact solve on the deflation space (defl_coefficient, defl_entry), one pass over W for
+  // the residual and e0
   const Cx<R>* W = static_cast<const Cx<R>*>(a.W);
   for (int p = tid; p < n; p += CS_THREADS) w[p] = b[p];
   __syncthreads();
   if (a.k > 0) {
-    for (int i = tid >> 6; i < a.k; i += CS_WAVES) {
-      const double li = 1.0 / a.lam[i];
-      const c128 d = small_dot(W + (int64_t)i * n, w, n);
-      if ((tid & 63) == 0) {
-        S.defl[0][i] = d;
-        S.defl[1][i] = li * d;
-      }
-    }
+    for (int i = tid >> 6; i < a.k; i += CS_WAVES) defl_coefficient(W, a.lam, w, n, i, S.defl[0], S.defl[1]);
     __syncthreads();
   }
   double nrm = 0.0;
   for (int p = tid; p < n; p += CS_THREADS) {
     c128 v = cmk((double)w[p].x, (double)w[p].y);
-    if (a.k > 0) {
-      c128 e = cmk(0.0, 0.0);
-#pragma unroll 8
-      for (int i = 0; i < a.k; ++i) {
-        const Cx<R> wi = W[(int64_t)i * n + p];
-        const c128 wd = cmk((double)wi.x, (double)wi.y);
-        v = v - S.defl[0][i] * wd;
-        cfma(e, S.defl[1][i], wd);
-      }
-      a.e0[(int64_t)r * n + p] = p % a.d < a.d / 2 ? e : cmk(-e.x, -e.y);
-    }
+    if (a.k > 0) defl_entry(W, n, a.k, a.d, p, S.defl[0], S.defl[1], v, a.e0[(int64_t)r * n + p]);
     const Cx<R> u0 = ccast<R>(v);
     if (F32)
       store(0, p, u0);
@@ -603,7 +650,7 @@ __global__ __launch_bounds__(CS_THREADS) void coarsest_small_kernel(SmallArgs a)
   for (int p = tid; p < n; p += CS_THREADS) {
     c128 xp = cmk(0.0, 0.0);
     BASIS_LOOP(V, 0, m, "unroll 8", { xp = xp + cprod<false>(S.cf[i], cmk((double)v[p].x, (double)v[p].y)); })
-    if (a.k > 0) xp = xp + a.e0[(int64_t)r * n + p];
+    if (a.e0) xp = xp + a.e0[(int64_t)r * n + p];
     x[p] = ccast<R>(xp);
   }
 }
@@ -617,14 +664,13 @@ struct SmallPlan {
 };
 
 template <typename R>
-SmallPlan small_plan(const Level& L, int m, int k) {
+SmallPlan small_plan(const Level& L, int m) {
   SmallPlan p;
   if (L.fine || m < 1 || m > CS_MAX_M || L.n() > SMALL_LEVEL_N) return p;
   const int n = (int)L.n(), d = L.dofs;
   // as many threads to a row as leave each two columns of every direction
   if (sizeof(R) == 8)
     while (2 * p.P * n <= CS_THREADS && 4 * p.P <= d && d % (2 * p.P) == 0) p.P *= 2;
-  if (k > CS_MAX_K) return p;
   const size_t room = CS_LDS - sizeof(SmallShared);
   auto bytes = [&](int kl, bool blocks) { return small_dynamic<R>(n, d, p.P, kl, blocks); };
   if (bytes(0, false) > room) return p;
@@ -655,21 +701,41 @@ void small_launch(dmlmc_ctx* ctx, const SmallArgs& a, size_t shm) {
 }  // namespace
 
 template <typename R>
-bool coarsest_small_ok(const Level& L, int m, int k) {
-  return small_plan<R>(L, m, k).ok;
+bool coarsest_small_ok(const Level& L, int m) {
+  return small_plan<R>(L, m).ok;
+}
+
+template <typename R>
+bool small_deflates_inside(const Level& L, int k) {
+  return k * L.n() * (int64_t)sizeof(Cx<R>) <= CS_DEFL_BYTES;
+}
+
+template <typename R>
+void small_deflate(dmlmc_ctx* ctx, const Level& L, const dmlmc_defl* D, const Cx<R>* b, int nrhs, c128* c, Cx<R>* r,
+                   c128* e0) {
+  const int n = (int)L.n(), k = D->k;
+  REQUIRE(n <= SMALL_LEVEL_N && 4 * k <= n && D->n == n, "level not laid out for the deflation of small levels");
+  const Cx<R>* W = std::is_same<R, float>::value ? (const Cx<R>*)D->W32.p : (const Cx<R>*)D->W64.p;
+  KTimer kt(ctx, "defl_gemm", 24.0 * n * k * nrhs);
+  hipLaunchKernelGGL((defl_coefficients_kernel<R>), dim3(nrhs, (unsigned)ceil_div(k, CS_WAVES)), dim3(CS_THREADS), 0,
+                     ctx->stream, W, D->lam_dev.as<double>(), b, n, k, c);
+  LAUNCH_CHECK();
+  hipLaunchKernelGGL((defl_residual_kernel<R>), dim3(nrhs, (unsigned)ceil_div(n, 256)), dim3(256), 0, ctx->stream, W, c,
+                     b, n, k, L.dofs, r, e0);
+  LAUNCH_CHECK();
 }
 
 template <typename R>
 size_t coarsest_small_scratch(const Level& L, int m, int k, int nrhs) {
-  return small_scratch_bytes<R>(small_plan<R>(L, m, k), m, L.n(), nrhs) + (k > 0 ? sizeof(c128) * nrhs * L.n() : 0);
+  return small_scratch_bytes<R>(small_plan<R>(L, m), m, L.n(), nrhs) + (k > 0 ? sizeof(c128) * nrhs * L.n() : 0);
 }
 
 template <typename R>
 void coarsest_small(dmlmc_ctx* ctx, const Level& L, const dmlmc_defl* D, const Cx<R>* b, Cx<R>* x, int nrhs, int m,
-                    void* scratch) {
+                    void* scratch, c128* e0) {
   constexpr bool F32 = std::is_same<R, float>::value;
   const int k = D ? D->k : 0;
-  const SmallPlan p = small_plan<R>(L, m, k);
+  const SmallPlan p = small_plan<R>(L, m);
   SmallArgs a;
   a.n = (int)L.n();
   a.d = L.dofs;
@@ -686,8 +752,9 @@ void coarsest_small(dmlmc_ctx* ctx, const Level& L, const dmlmc_defl* D, const C
   a.lam = D ? D->lam_dev.as<double>() : nullptr;
   a.kl = p.kl;
   a.basis = scratch;
-  a.e0 = reinterpret_cast<c128*>(static_cast<char*>(scratch) + small_scratch_bytes<R>(p, m, L.n(), nrhs));
-  REQUIRE(p.ok && a.A != nullptr && (scratch != nullptr || (p.kl == m + 1 && k == 0)),
+  a.e0 = D ? reinterpret_cast<c128*>(static_cast<char*>(scratch) + small_scratch_bytes<R>(p, m, L.n(), nrhs)) : e0;
+  REQUIRE(p.ok && a.A != nullptr && (scratch != nullptr || (p.kl == m + 1 && k == 0)) &&
+              (D == nullptr || small_deflates_inside<R>(L, k)),
           "level not laid out for the one-launch coarsest solve");
   // the operator's blocks once per step and right-hand side
   KTimer kt(ctx, "coarsest", (double)nrhs * m * 5 * L.dofs * L.n() * sizeof(Cx<R>));
@@ -703,10 +770,13 @@ void coarsest_small(dmlmc_ctx* ctx, const Level& L, const dmlmc_defl* D, const C
   }
 }
 
-#define INST(R)                                                                                              \
-  template bool coarsest_small_ok<R>(const Level&, int, int);                                                \
-  template size_t coarsest_small_scratch<R>(const Level&, int, int, int);                                    \
-  template void coarsest_small<R>(dmlmc_ctx*, const Level&, const dmlmc_defl*, const Cx<R>*, Cx<R>*, int, int, void*);
+#define INST(R)                                                                                                      \
+  template bool coarsest_small_ok<R>(const Level&, int);                                                             \
+  template bool small_deflates_inside<R>(const Level&, int);                                                         \
+  template void small_deflate<R>(dmlmc_ctx*, const Level&, const dmlmc_defl*, const Cx<R>*, int, c128*, Cx<R>*, c128*); \
+  template size_t coarsest_small_scratch<R>(const Level&, int, int, int);                                            \
+  template void coarsest_small<R>(dmlmc_ctx*, const Level&, const dmlmc_defl*, const Cx<R>*, Cx<R>*, int, int, void*, \
+                                  c128*);
 INST(float)
 INST(double)
 #undef INST

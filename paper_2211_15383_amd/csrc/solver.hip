@@ -302,24 +302,32 @@ void coarsest_gmres(dmlmc_hier* H, int l, const Cx<R>* b_in, Cx<R>* x, int nrhs)
   const dmlmc_defl* D = H->coarse_defl;
   const bool use_defl = D != nullptr && D->level == l;
   const int m = std::max(1, use_defl ? H->coarsest_iters_defl : H->coarsest_iters);
-  // up to 2048 entries (SMALL_LEVEL_N) every step runs in one launch, a workgroup per RHS
-  if (coarsest_small_ok<R>(L, m, use_defl ? D->k : 0)) {
-    const size_t bytes = coarsest_small_scratch<R>(L, m, use_defl ? D->k : 0, nrhs);
-    void* scratch = bytes ? hier_buf(H, f32 ? "cg_V32" : "cg_V64", l, bytes) : nullptr;
-    coarsest_small<R>(ctx, L, use_defl ? D : nullptr, b_in, x, nrhs, m, scratch);
-    return;
-  }
   const Cx<R>* b = b_in;
   c128* e0 = nullptr;
-  if (use_defl) {
-    c128* b64 = (c128*)hier_buf(H, "cd_b", l, sizeof(c128) * (size_t)nrhs * n);
-    c128* r64 = (c128*)hier_buf(H, "cd_r", l, sizeof(c128) * (size_t)nrhs * n);
+  // up to 2048 entries (SMALL_LEVEL_N) every step runs in one launch, a workgroup per RHS
+  const bool one_launch = coarsest_small_ok<R>(L, m);
+  const bool inside = one_launch && use_defl && small_deflates_inside<R>(L, D->k);
+  if (use_defl && !inside) {
     e0 = (c128*)hier_buf(H, "cd_e0", l, sizeof(c128) * (size_t)nrhs * n);
     Cx<R>* rR = (Cx<R>*)hier_buf(H, f32 ? "cd_r32" : "cd_r64", l, sizeof(Cx<R>) * (size_t)nrhs * n);
-    launch_cast<double, R>(ctx, b_in, b64, n, nrhs, n, n);
-    defl_coarse_split(H, D, b64, nrhs, r64, e0, f32 ? DMLMC_MIXED : DMLMC_FP64);
-    launch_cast<R, double>(ctx, r64, rR, n, nrhs, n, n);
+    if (!L.fine && n <= SMALL_LEVEL_N) {
+      c128* c = (c128*)hier_buf(H, "cd_c", l, sizeof(c128) * (size_t)2 * D->k * nrhs);
+      small_deflate<R>(ctx, L, D, b_in, nrhs, c, rR, e0);
+    } else {
+      c128* b64 = (c128*)hier_buf(H, "cd_b", l, sizeof(c128) * (size_t)nrhs * n);
+      c128* r64 = (c128*)hier_buf(H, "cd_r", l, sizeof(c128) * (size_t)nrhs * n);
+      launch_cast<double, R>(ctx, b_in, b64, n, nrhs, n, n);
+      defl_coarse_split(H, D, b64, nrhs, r64, e0, f32 ? DMLMC_MIXED : DMLMC_FP64);
+      launch_cast<R, double>(ctx, r64, rR, n, nrhs, n, n);
+    }
     b = rR;
+  }
+  if (one_launch) {
+    const int k = inside ? D->k : 0;
+    const size_t bytes = coarsest_small_scratch<R>(L, m, k, nrhs);
+    void* scratch = bytes ? hier_buf(H, f32 ? "cg_V32" : "cg_V64", l, bytes) : nullptr;
+    coarsest_small<R>(ctx, L, inside ? D : nullptr, b, x, nrhs, m, scratch, e0);
+    return;
   }
   Cx<R>* V = (Cx<R>*)hier_buf(H, f32 ? "cg_V32" : "cg_V64", l, sizeof(Cx<R>) * (size_t)(m + 1) * nrhs * n);
   Cx<R>* wr = (Cx<R>*)hier_buf(H, f32 ? "cg_wr32" : "cg_wr64", l, sizeof(Cx<R>) * (size_t)nrhs * n);

@@ -215,6 +215,44 @@ def test_coarse_gauss_seidel(Lx, Lt, ntv, nrhs):
         assert np.linalg.norm(out.T - y) <= tol * np.linalg.norm(y), (prec, nrhs)
 
 
+@pytest.mark.parametrize("shape,k,m", [("16x8", 32, 24), ("64x16", 32, 8), ("64x16", 64, 8), ("64x16", 65, 24),
+                                       ("64x16", 256, 8), ("60x10", 109, 8), ("60x10", 110, 8), ("50x24", 300, 8),
+                                       ("128x16", 17, 24), ("128x16", 512, 8)])
+@pytest.mark.parametrize("prec", ["mixed", "fp64"])
+def test_deflation_of_many_vectors(shape, prec, k, m):
+    """Deflation inside the one-launch solve (up to 512 KB of vectors, more of them than its 16
+    wavefronts) and in launches of its own beyond; bounds as above (the k terms are FP64 sums)."""
+    import torch
+
+    from paper_2211_15383_amd import dmlmc
+
+    (Lx, Lt), agg, ntv = SHAPES[shape]
+    rng = np.random.default_rng(37)
+
+    def cn(*s):
+        return rng.standard_normal(s) + 1j * rng.standard_normal(s)
+
+    H = dmlmc.Hierarchy(dmlmc.Context(0), rng.normal(0.0, 0.3, (2, Lt, Lx)), 0.1, [agg], [ntv],
+                        import_tv=[cn(2 * Lx * Lt, ntv)])
+    lx, lt, d = H.level_info(2)
+    n = H.n(2)
+    A = H.export(2, Dc=True)["Dc"]
+    H.solver_params(coarsest_iters_defl=m)
+    X = np.linalg.qr(cn(n, k))[0]
+    lam = np.linspace(0.3, 2.0, k) * (-1.0) ** np.arange(k)
+    defl = dmlmc.Deflation(H, 2, k, import_X=X, import_lambda=lam)  # (the hierarchy keeps no reference)
+    H.set_deflation(defl)
+    W = np.tile(np.repeat([1.0, -1.0], d // 2), n // d)[:, None] * X
+    mixed = prec == "mixed"
+    bd = torch.as_tensor(cn(2, n), device="cuda").to(torch.complex64 if mixed else torch.complex128)
+    x = H.apply(dmlmc.OP_VCYCLE, 2, bd, torch.empty_like(bd),
+                prec=dmlmc.MIXED if mixed else dmlmc.FP64).cpu().numpy()
+    for r, b in enumerate(bd.cpu().numpy().astype(np.complex128)):
+        c = W.conj().T @ b
+        ref = X @ (c / lam) + _gmres(lambda v: _blocks_apply(A, lx, lt, v), b - W @ c, m)
+        assert np.linalg.norm(x[r] - ref) <= (2e-4 if mixed else 1e-11) * np.linalg.norm(ref), (shape, prec, k, r)
+
+
 def test_block_larger_than_the_readback_buffer():
     """8200 right-hand sides: their norms (8 bytes each) exceed the pinned staging buffer."""
     import torch
