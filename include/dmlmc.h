@@ -467,8 +467,9 @@ dmlmc_status dmlmc_set_verbose(dmlmc_ctx *ctx, int level);
  * When enabled, the library brackets every launch of the named kernel classes with HIP
  * events on the context stream and accumulates their durations.  Classes:
  * "wilson", "coarse", "sap", "coarse_gs", "restrict", "prolong", "gs_dots", "gs_update",
- * "gs_fused" (the single-workgroup Arnoldi step of small levels), "coarsest" (the one-launch
- * GMRES of coarsest levels up to 2048 entries), "defl_gemm",
+ * "gs_fused" (the Arnoldi step of vectors up to 16384 entries, two to four launches as one timed
+ * unit), "coarsest" (the one-launch GMRES of coarsest levels up to 2048 entries, where that is
+ * the faster form), "defl_gemm",
  * "coarse_direct" (the FP32 explicit-inverse coarsest solve) and "coarse_direct16" (its
  * FP16 form: RHS scaling, product and reduction as one timed unit).
  * dmlmc_timing_get returns (launches, total milliseconds, work summed over launches) for

@@ -3,9 +3,9 @@
 
 #include "common.h"
 
-// Whether coarsest_small runs the m-step GMRES of level L in precision R.
+// Whether coarsest_small runs the m-step GMRES of level L on nrhs right-hand sides in precision R.
 template <typename R>
-bool coarsest_small_ok(const Level& L, int m);
+bool coarsest_small_ok(const Level& L, int m, int nrhs);
 // Whether it takes in a deflation of k vectors too; small_deflate comes before it otherwise.
 template <typename R>
 bool small_deflates_inside(const Level& L, int k);

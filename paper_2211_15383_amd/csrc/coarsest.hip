@@ -1,8 +1,8 @@
 // Fixed-count GMRES of a small coarsest level, every step of it in one launch.
 //
 // A V-cycle ends in m steps of GMRES on the coarsest operator (after the exact solve on the
-// deflation space when one is attached).  As separate launches that is 2 to 6 launches a step
-// and a dozen around them, 2 to 20 us each on vectors of a few KB: launch latency and idle
+// deflation space when one is attached).  As separate launches that is 3 or 4 launches a step
+// and a dozen around them, 2 to 6 us each on vectors of a few KB: launch latency and idle
 // CUs.  Here one workgroup owns one right-hand side: the Krylov vector, the operator's result,
 // the Hessenberg matrix and (where it fits) the basis stay in LDS, and the operator's blocks
 // are streamed from L2, which is what bounds a step (64 bytes per clock and CU).
@@ -19,17 +19,18 @@
 //     joins the next step's operator, whose streaming hides them; one wavefront ends with the
 //     back substitution.
 //
-// The complex-FP32 form without a deflation performs the operations of the separate
-// launches (gram.hip's one-workgroup step, the coarse stencils, the coefficient kernels) in
-// their order, fused multiply-adds included, so its results are theirs to the last bit: the
-// test vectors of a hierarchy come out of solves with it, and a deflation's FP32 vectors
-// magnify a last-bit change of the coarse operators to 1e-8 in the coarsest samples.
+// The complex-FP32 form performs the operations of the separate launches (the split Gram-Schmidt
+// step, the coarse stencils, the coefficient kernels) in their order, fused multiply-adds
+// included, so its results are theirs to the last bit: the test vectors of a hierarchy come out of
+// solves with it, and a deflation's FP32 vectors magnify a last-bit change of the coarse
+// operators to 1e-8 in the coarsest samples.
 //
-// Measured (MI355X) against the separate launches: 8 steps with 32 deflation vectors, n = 1024,
-// 32 right-hand sides 228 -> 82 us (a step 18.5 kclk: operator 11.7, of which 10.2 at 64 bytes
-// per clock, dots 3.3, update 1.8); 24 steps, n = 600 with 10 dofs, 5 right-hand sides 920 -> 165 us
-// (operator 6.3 kclk, dots 6.8, update 4.1); complex FP64, 8 steps, n = 128 with 16 deflation
-// vectors 41 us (operator 3.4 kclk; 61 us and 8.5 kclk with the contraction in LDS partial sums).
+// Measured (MI355X, whole calls) against the separate launches: 8 steps with 32 deflation vectors, n =
+// 1024, 32 right-hand sides 171 -> 94 us (82 in the kernel, a step 18.5 kclk: operator 11.7, of which
+// 10.2 at 64 bytes per clock, dots 3.3, update 1.8); 24 steps, n = 600 with 10 dofs, 4 right-hand sides
+// 421 -> 177 us (165 in the kernel: operator 6.3 kclk a step, dots 6.8, update 4.1); complex FP64, 8
+// steps, n = 128 with 32 deflation vectors 187 -> 65 us.  Where a step streams more, the separate
+// launches are the faster form (one_launch_mb).
 #include <algorithm>
 
 #include "coarsest.h"
@@ -700,9 +701,38 @@ void small_launch(dmlmc_ctx* ctx, const SmallArgs& a, size_t shm) {
 
 }  // namespace
 
+// Whether one launch is the faster form, from the megabytes a workgroup streams per step (blocks and
+// basis vectors outside LDS, at about 10 us each) against what the separate launches take per step:
+// 12 to 17 us with the matrix-core stencil (16 dofs; FP64 from 8 right-hand sides on), more with the
+// scalar one, and more with many right-hand sides, of which the one launch has 256 at a time.
+// Measured (us, one launch / separate, no deflation) around the lines:
+//   FP32, 16 dofs, 24 steps, 1 RHS: n = 1024 (0.7 MB a step) 262 / 342, 1536 (1.1) 353 / 305, 2048 (1.6)
+//     441 / 306; 32 RHS, 2048: 4 steps (1.3) 75 / 84, 24 steps 454 / 359; 128 RHS: 498 / 737
+//   FP32, 24 dofs, n = 1536, 24 steps (1.6): 1 RHS 494 / 444, 2 RHS 500 / 566; 32 dofs, 2048 (2.9) 705 / 635
+//   FP64, 16 dofs, 1 RHS: n = 1024, 8 steps (1.4) 148 / 152, 24 steps (1.9) 504 / 429; 2048, 24 steps (4.3)
+//     934 / 380, 32 RHS 1103 / 544, 128 RHS 1428 / 1164, 512 RHS 3914 / 3788
+//   FP64, 24 dofs: n = 960, 24 steps (2.4), 2 RHS 647 / 663; 1536, 8 steps (3.4), 32 RHS 293 / 246
+// In complex FP32 both forms give the same bits.
+double one_launch_mb(bool f32, int d, int nrhs) {
+  constexpr double any = 1e9;
+  if (f32) {
+    if (nrhs >= 64) return any;
+    if (d == 16) return nrhs < 32 ? 1.05 : 1.4;
+    return nrhs > 1 ? 2.8 : d < 16 ? 0.75 : 1.55;
+  }
+  if (d > 16) return nrhs == 1 ? 2.1 : nrhs < 128 ? 2.8 : nrhs < 512 ? 4.1 : any;
+  if (nrhs < 64) return nrhs == 1 ? 1.36 : 1.6;
+  return d == 16 || nrhs < 128 ? (nrhs < 4096 ? 2.05 : any) : nrhs < 512 ? 4.1 : any;
+}
+
 template <typename R>
-bool coarsest_small_ok(const Level& L, int m) {
-  return small_plan<R>(L, m).ok;
+bool coarsest_small_ok(const Level& L, int m, int nrhs) {
+  constexpr bool F32 = std::is_same<R, float>::value;
+  const SmallPlan p = small_plan<R>(L, m);
+  if (!p.ok) return false;
+  const double vec = 1e-6 * L.n() * sizeof(Cx<R>), outside = std::max(0, m - p.kl);
+  const double mb = (p.blocks ? 0.0 : vec * 5 * L.dofs * m) + vec * (F32 ? 2 : 4) * outside * (outside + 1) / 2;
+  return mb <= m * one_launch_mb(F32, L.dofs, nrhs);
 }
 
 template <typename R>
@@ -771,7 +801,7 @@ void coarsest_small(dmlmc_ctx* ctx, const Level& L, const dmlmc_defl* D, const C
 }
 
 #define INST(R)                                                                                                      \
-  template bool coarsest_small_ok<R>(const Level&, int);                                                             \
+  template bool coarsest_small_ok<R>(const Level&, int, int);                                                        \
   template bool small_deflates_inside<R>(const Level&, int);                                                         \
   template void small_deflate<R>(dmlmc_ctx*, const Level&, const dmlmc_defl*, const Cx<R>*, int, c128*, Cx<R>*, c128*); \
   template size_t coarsest_small_scratch<R>(const Level&, int, int, int);                                            \

@@ -247,7 +247,7 @@ struct Level {
   int rows_per_block() const { return ax * at * (dofs / 2); }
 };
 
-// Vector length up to which a coarsest solve runs in one launch (coarsest.hip)
+// Vector length up to which a coarsest solve can run in one launch (coarsest.hip)
 constexpr int64_t SMALL_LEVEL_N = 2048;
 
 struct Workspace;  // per-level scratch for V-cycles and solves (solver.hip)

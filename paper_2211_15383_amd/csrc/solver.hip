@@ -304,13 +304,14 @@ void coarsest_gmres(dmlmc_hier* H, int l, const Cx<R>* b_in, Cx<R>* x, int nrhs)
   const int m = std::max(1, use_defl ? H->coarsest_iters_defl : H->coarsest_iters);
   const Cx<R>* b = b_in;
   c128* e0 = nullptr;
-  // up to 2048 entries (SMALL_LEVEL_N) every step runs in one launch, a workgroup per RHS
-  const bool one_launch = coarsest_small_ok<R>(L, m);
+  // on small levels every step runs in one launch, a workgroup per RHS, where that is the faster
+  const bool one_launch = coarsest_small_ok<R>(L, m, nrhs);
+  const bool small = !L.fine && n <= SMALL_LEVEL_N;
   const bool inside = one_launch && use_defl && small_deflates_inside<R>(L, D->k);
   if (use_defl && !inside) {
     e0 = (c128*)hier_buf(H, "cd_e0", l, sizeof(c128) * (size_t)nrhs * n);
     Cx<R>* rR = (Cx<R>*)hier_buf(H, f32 ? "cd_r32" : "cd_r64", l, sizeof(Cx<R>) * (size_t)nrhs * n);
-    if (!L.fine && n <= SMALL_LEVEL_N) {
+    if (small) {
       c128* c = (c128*)hier_buf(H, "cd_c", l, sizeof(c128) * (size_t)2 * D->k * nrhs);
       small_deflate<R>(ctx, L, D, b_in, nrhs, c, rR, e0);
     } else {
@@ -359,6 +360,11 @@ void coarsest_gmres(dmlmc_hier* H, int l, const Cx<R>* b_in, Cx<R>* x, int nrhs)
       arnoldi_step(ctx, V64, w, j, n, nrhs, k);
     }
     krylov_solution(ctx, k, m, nrhs);
+  }
+  if (use_defl && small) {  // the sum in FP64, as in the one-launch form
+    launch_combine<R, double>(ctx, V, m, k, e0, n, nrhs, true);
+    launch_cast<R, double>(ctx, e0, x, n, nrhs, n, n);
+    return;
   }
   launch_combine<R, R>(ctx, V, m, k, x, n, nrhs, false);
   if (use_defl) launch_add_cast_to<R>(ctx, e0, x, n, nrhs);

@@ -253,6 +253,63 @@ def test_deflation_of_many_vectors(shape, prec, k, m):
         assert np.linalg.norm(x[r] - ref) <= (2e-4 if mixed else 1e-11) * np.linalg.norm(ref), (shape, prec, k, r)
 
 
+@pytest.mark.parametrize("k", [0, 4, 65])
+@pytest.mark.parametrize("Lx,Lt,ntv,few", [(64, 64, 4, 1), (64, 40, 5, 1), (56, 48, 6, 1), (48, 48, 7, 1), (64, 32, 8, 3),
+                                           (40, 32, 12, 1), (32, 32, 16, 2)])
+def test_one_launch_and_separate_launches_agree(Lx, Lt, ntv, few, k):
+    """Levels of 1600 to 2048 entries, 8 to 32 dofs, 24 steps: a few right-hand sides take the
+    separate launches, a block of 64 the one launch, and in complex FP32 both give the same bits
+    (set-ups depend on the order of the sums), inside and outside deflations included."""
+    import torch
+
+    from paper_2211_15383_amd import dmlmc
+
+    rng = np.random.default_rng(41)
+
+    def cn(*s):
+        return rng.standard_normal(s) + 1j * rng.standard_normal(s)
+
+    ctx = dmlmc.Context(0)
+    H = dmlmc.Hierarchy(ctx, rng.normal(0.0, 0.3, (2, Lt, Lx)), 0.1, [(4, 4)], [ntv], import_tv=[cn(2 * Lx * Lt, ntv)])
+    n = H.n(2)
+    H.solver_params(coarsest_iters=24, coarsest_iters_defl=24)
+    if k:
+        X = np.linalg.qr(cn(n, k))[0]
+        defl = dmlmc.Deflation(H, 2, k, import_X=X, import_lambda=np.linspace(0.3, 2.0, k))
+        H.set_deflation(defl)
+    b = torch.as_tensor(cn(64, n), device="cuda").to(torch.complex64)
+    ctx.timing(True)
+    out = {}
+    for name, x in (("few", b[:few]), ("block", b)):
+        ctx.timing_reset()
+        out[name] = H.apply(dmlmc.OP_VCYCLE, 2, x, torch.empty_like(x), prec=dmlmc.MIXED)
+        assert ctx.timing_get("coarsest")[0] == (1 if name == "block" else 0)
+    assert torch.equal(torch.view_as_real(out["few"]), torch.view_as_real(out["block"][:few]))
+
+
+def test_fp64_basis_outside_lds():
+    """1600 entries in complex FP64: a block of 64 takes the one launch, no basis vector of which
+    fits into LDS, one vector the separate launches; both to 1e-11 as above, so 2e-11 apart."""
+    import torch
+
+    from paper_2211_15383_amd import dmlmc
+
+    rng = np.random.default_rng(43)
+    ctx = dmlmc.Context(0)
+    tv = rng.standard_normal((2 * 64 * 40, 5)) + 1j * rng.standard_normal((2 * 64 * 40, 5))
+    H = dmlmc.Hierarchy(ctx, rng.normal(0.0, 0.3, (2, 40, 64)), 0.1, [(4, 4)], [5], import_tv=[tv])
+    H.solver_params(coarsest_iters=8)
+    n = H.n(2)
+    b = torch.as_tensor(rng.standard_normal((64, n)) + 1j * rng.standard_normal((64, n)), device="cuda")
+    ctx.timing(True)
+    x = H.apply(dmlmc.OP_VCYCLE, 2, b, torch.empty_like(b))
+    assert ctx.timing_get("coarsest")[0] == 1
+    for r in (0, 63):
+        y = H.apply(dmlmc.OP_VCYCLE, 2, b[r:r + 1], torch.empty_like(b[:1]))
+        assert float((x[r] - y[0]).norm() / y[0].norm()) <= 2e-11
+    assert ctx.timing_get("coarsest")[0] == 1
+
+
 def test_block_larger_than_the_readback_buffer():
     """8200 right-hand sides: their norms (8 bytes each) exceed the pinned staging buffer."""
     import torch
