@@ -379,8 +379,14 @@ __global__ __launch_bounds__(256) void sap_kernel(const Cx<R>* __restrict__ U, C
 
 // Red/black point-block Gauss-Seidel on a coarse level: for every site of colour
 // `color`, x_s <- x_s + A_ss^-1 (b_s - (D x)_s).  Thread per (site, row); the residual of
-// a site is exchanged through LDS.
-template <typename R, int D>
+// a site is exchanged through LDS.  Forms of the same sums (gs_plan):
+//   GS_AHEAD       D dofs, straight-line, the next direction's entries on their way
+//   GS_DIRECTIONS  D dofs, straight-line, one direction's entries at a time (fewer registers)
+//   GS_CHUNKS      any dofs, CHUNK entries at a time
+//   GS_PLAIN       any dofs, entry by entry
+enum GsForm { GS_PLAIN, GS_CHUNKS, GS_DIRECTIONS, GS_AHEAD };
+
+template <typename R, int D, int FORM>
 __global__ __launch_bounds__(256) void coarse_gs_kernel(const Cx<R>* __restrict__ A, const Cx<R>* __restrict__ Ainv,
                                                         Cx<R>* __restrict__ x, const Cx<R>* __restrict__ b, int Lx,
                                                         int Lt, int dofs, int spb, int nrhs, int rb, int color,
@@ -413,10 +419,14 @@ __global__ __launch_bounds__(256) void coarse_gs_kernel(const Cx<R>* __restrict_
   for (int r = r0; r < r1; ++r) {
     const Cx<R>* xr = x + r * ld;
     Cx<R> acc = cmk((R)0, (R)0);
-    Cx<R> ai[D ? D : 1];
+    Cx<R> ai[FORM == GS_AHEAD ? D : 1];
+    auto subtract = [&](Cx<R> a, Cx<R> v) {
+      acc.x -= a.x * v.x - a.y * v.y;
+      acc.y -= a.x * v.y + a.y * v.x;
+    };
     if (active) {
       acc = b[r * ld + s * d + i];
-      if constexpr (D > 0) {
+      if constexpr (FORM == GS_AHEAD) {
         Cx<R> a[2][D], v[2][D];
         auto load = [&](int dir) {
 #pragma unroll
@@ -436,10 +446,27 @@ __global__ __launch_bounds__(256) void coarse_gs_kernel(const Cx<R>* __restrict_
           }
           __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
+          for (int j = 0; j < D; ++j) subtract(a[dir & 1][j], v[dir & 1][j]);
+        }
+      } else if constexpr (FORM == GS_DIRECTIONS) {
+#pragma unroll 1
+        for (int dir = 0; dir < 5; ++dir) {
+          const int64_t site = dir == 0 ? s : dir == 1 ? nb.xp : dir == 2 ? nb.xm : dir == 3 ? nb.tp : nb.tm;
+          Cx<R> a[D], v[D];
+#pragma unroll
           for (int j = 0; j < D; ++j) {
-            acc.x -= a[dir & 1][j].x * v[dir & 1][j].x - a[dir & 1][j].y * v[dir & 1][j].y;
-            acc.y -= a[dir & 1][j].x * v[dir & 1][j].y + a[dir & 1][j].y * v[dir & 1][j].x;
+            a[j] = Ab[(dir * D + j) * D + i];
+            v[j] = xr[site * D + j];
           }
+          __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+          for (int j = 0; j < D; ++j) subtract(a[j], v[j]);
+        }
+      } else if constexpr (FORM == GS_PLAIN) {
+        for (int dir = 0; dir < 5; ++dir) {
+          const Cx<R>* Ad = Ab + dir * d * d + i;
+          const Cx<R>* xd = xr + sites[dir] * d;
+          for (int j = 0; j < d; ++j) subtract(Ad[j * d], xd[j]);
         }
       } else {
 #pragma unroll
@@ -456,12 +483,8 @@ __global__ __launch_bounds__(256) void coarse_gs_kernel(const Cx<R>* __restrict_
               }
             }
 #pragma unroll
-            for (int j = 0; j < CHUNK; ++j) {
-              if (j0 + j < d) {
-                acc.x -= a[j].x * v[j].x - a[j].y * v[j].y;
-                acc.y -= a[j].x * v[j].y + a[j].y * v[j].x;
-              }
-            }
+            for (int j = 0; j < CHUNK; ++j)
+              if (j0 + j < d) subtract(a[j], v[j]);
           }
         }
       }
@@ -471,7 +494,7 @@ __global__ __launch_bounds__(256) void coarse_gs_kernel(const Cx<R>* __restrict_
     __syncthreads();
     if (active) {
       Cx<R> e = cmk((R)0, (R)0);
-      if constexpr (D > 0) {
+      if constexpr (FORM == GS_AHEAD) {
 #pragma unroll
         for (int j = 0; j < D; ++j) cfma(e, ai[j], res[ls * D + j]);
       } else {
@@ -2064,6 +2087,42 @@ void launch_sap(dmlmc_ctx* ctx, const Level& L, Cx<R>* x, const Cx<R>* b, int nr
   LAUNCH_CHECK();
 }
 
+namespace {
+struct GsPlan {
+  GsForm form;
+  int threads;
+};
+
+// Form and workgroup of the scalar Gauss-Seidel sweep.  A launch of few wavefronts waits for its
+// loads, which are then all out before they are used, in workgroups of 64 threads on more CUs; one of
+// many is bound by the caches: fewer loads in flight, and 256 threads sharing neighbours and
+// blocks, fetch less from beyond them.  Measured in us a launch as plain loops / as chosen here /
+// (where that is neither) prefetching:
+//   up to 2048 wavefronts: 128 sites, one RHS, FP64, 8 dofs 8.5 / 3.9, 16 dofs 13.6 / 5.5; 4096 sites, 5 RHS, FP64,
+//     10 dofs 23.2 / 18.2, 12 dofs 27.7 / 25.0
+//   2 to 6 dofs: 4096 sites, 32 RHS, 2 dofs FP64 7.1 / 6.3 / 9.5, 6 dofs FP32 31.8 / 18.8 / 23.4, FP64 43.2 / 36.2 / 42.5
+//   8 dofs FP64: 4096 sites, 32 RHS 34.5 / 25.2; 16384 sites, 16 RHS 71.5 / 71.8 / 122
+//   10 and 12 dofs FP64: 4096 sites, 32 RHS 72.0 / 72.1 / 105 and 102 / 103 / 137
+//   14 and 16 dofs FP64: 4096 sites, 32 RHS 127 / 89 / 187 (in chunks) and 120 / 122 / 137; 16384 sites, 16 RHS
+//     293 / 295 / 368 (in chunks) and 381 / 383 / 460
+//   more dofs: 32, 4096 sites FP64 (403 MB of blocks) 32 RHS 603 / 606 / 863 (in chunks), 2 RHS 87 / 52; 24, 5 RHS 115 / 76
+template <typename R>
+GsPlan gs_plan(int d, int64_t V, int64_t nsites, int nrhs, int rb) {
+  constexpr bool F64 = std::is_same<R, double>::value;
+  const int64_t groups = ceil_div(nrhs, rb), waves = ceil_div(nsites * d, 64) * groups;
+  const double blocks = (double)V * 6 * d * d * sizeof(Cx<R>);
+  if (d > 24 && waves >= 8192 && blocks >= 128e6) return {GS_PLAIN, 256};
+  if (d > 16) return {GS_CHUNKS, ceil_div(nsites * d, 256) * groups >= 1024 ? 256 : 64};
+  if (waves < (d <= 6 ? 2048 : 2200)) return {GS_AHEAD, 64};
+  if (F64 && d >= 6 && V >= 16384) return {GS_PLAIN, 256};
+  if (d <= 6) return {GS_DIRECTIONS, 256};
+  if (d == 8) return {GS_AHEAD, 256};
+  if (F64 && d >= 14) return {GS_DIRECTIONS, 64};
+  if (F64 && blocks >= 4e6 && waves * d * d >= 400000) return {GS_PLAIN, 256};
+  return {GS_AHEAD, d <= 12 && waves >= 8192 ? 256 : 64};
+}
+}  // namespace
+
 template <typename R>
 void launch_coarse_gs(dmlmc_ctx* ctx, const Level& L, Cx<R>* x, const Cx<R>* b, int nrhs, int color, bool half,
                       int64_t ld) {
@@ -2111,21 +2170,37 @@ void launch_coarse_gs(dmlmc_ctx* ctx, const Level& L, Cx<R>* x, const Cx<R>* b, 
   }
   KTimer kt(ctx, "coarse_gs",
             (double)nrhs * (V / 2) * d * 4 * sizeof(Cx<R>) + (double)(V / 2) * 6 * d * d * sizeof(Cx<R>));
-  // workgroups of 64 threads until 256-thread ones would be 2048, as in the stencil
-  const int spb = std::max(1, (ceil_div(nsites * d, 256) * ceil_div(nrhs, rb) >= 2048 ? 256 : 64) / d);
+  const GsPlan g = gs_plan<R>(d, V, nsites, nrhs, rb);
+  const int spb = std::max(1, g.threads / d);
   dim3 grid((unsigned)ceil_div(nsites, spb), (unsigned)ceil_div(nrhs, rb));
   dim3 block((unsigned)(spb * d));
   size_t shm = (size_t)spb * d * sizeof(Cx<R>);
-#define GS_DOFS(D)                                                                                                  \
-  hipLaunchKernelGGL((coarse_gs_kernel<R, D>), grid, block, shm, ctx->stream, A, Ai, x, b, L.Lx, L.Lt, d, spb, nrhs, \
+#define GS_LAUNCH(D, FORM)                                                                                               \
+  hipLaunchKernelGGL((coarse_gs_kernel<R, D, FORM>), grid, block, shm, ctx->stream, A, Ai, x, b, L.Lx, L.Lt, d, spb, nrhs, \
                      rb, color, even, ld)
-  switch (d) {
-    case 8: GS_DOFS(8); break;
-    case 10: GS_DOFS(10); break;
-    case 12: GS_DOFS(12); break;
-    case 16: GS_DOFS(16); break;
-    default: GS_DOFS(0);
+#define GS_DOFS(D)                                \
+  case D:                                         \
+    if (g.form == GS_AHEAD)                       \
+      GS_LAUNCH(D, GS_AHEAD);                     \
+    else                                          \
+      GS_LAUNCH(D, GS_DIRECTIONS);                \
+    break
+  if (g.form == GS_PLAIN) {
+    GS_LAUNCH(0, GS_PLAIN);
+  } else {
+    switch (d) {
+      GS_DOFS(2);
+      GS_DOFS(4);
+      GS_DOFS(6);
+      GS_DOFS(8);
+      GS_DOFS(10);
+      GS_DOFS(12);
+      GS_DOFS(14);
+      GS_DOFS(16);
+      default: GS_LAUNCH(0, GS_CHUNKS);
+    }
   }
+#undef GS_LAUNCH
 #undef GS_DOFS
   LAUNCH_CHECK();
 }

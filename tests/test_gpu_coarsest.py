@@ -253,6 +253,47 @@ def test_deflation_of_many_vectors(shape, prec, k, m):
         assert np.linalg.norm(x[r] - ref) <= (2e-4 if mixed else 1e-11) * np.linalg.norm(ref), (shape, prec, k, r)
 
 
+@pytest.mark.parametrize("Lx,Lt,ntv,nrhs", [
+    (16, 16, 1, 3), (16, 24, 2, 3), (24, 16, 7, 3), (16, 16, 9, 2),  # 2, 4 and 14 dofs prefetching, 18 in chunks
+    (64, 64, 2, 257), (64, 64, 3, 257),  # 4 and 6 dofs by directions, 257 right-hand sides
+    (64, 64, 4, 160),                    # 8 dofs prefetching, 256 threads
+    (32, 32, 7, 321), (32, 32, 8, 300),  # 14 and 16 dofs, FP64 by directions
+    (128, 128, 5, 65), (128, 128, 6, 48),  # 10 and 12 dofs, FP64 entry by entry
+    (512, 512, 4, 3),                    # 16384 sites, FP64 entry by entry
+    (160, 160, 16, 21),                  # 32 dofs, blocks of 157 MB (FP64) entry by entry
+])
+def test_coarse_gauss_seidel_forms(Lx, Lt, ntv, nrhs):
+    """The forms of the sweep by dofs, sites and right-hand sides; bounds as above."""
+    import torch
+
+    from paper_2211_15383_amd import dmlmc
+
+    rng = np.random.default_rng(47)
+
+    def cn(*s):
+        return rng.standard_normal(s) + 1j * rng.standard_normal(s)
+
+    H = dmlmc.Hierarchy(dmlmc.Context(0), rng.normal(0.0, 0.3, (2, Lt, Lx)), 0.3, [(4, 4), (2, 2)], [ntv, 1],
+                        import_tv=[cn(2 * Lx * Lt, ntv), cn(Lx * Lt // 16 * 2 * ntv, 1)])
+    H.solver_params(smoother_half=0)
+    lx, lt, d = H.level_info(2)
+    A = H.export(2, Dc=True)["Dc"]
+    Ainv = np.linalg.inv(A[:, 0])
+    t, x = np.divmod(np.arange(lx * lt), lx)
+    b = cn(nrhs, H.n(2))
+    for prec, dt, tol in ((dmlmc.FP64, torch.complex128, 1e-12), (dmlmc.MIXED, torch.complex64, 1e-4)):
+        bd = torch.as_tensor(b, device="cuda").to(dt)
+        out = H.apply(dmlmc.OP_SMOOTH, 2, bd, torch.zeros_like(bd), prec=prec, arg=1).cpu().numpy()
+        bh = bd.cpu().numpy().astype(np.complex128).T
+        y = np.zeros_like(bh)
+        for color in (0, 1):
+            r = (bh - _blocks_apply(A, lx, lt, y)).reshape(lx * lt, d, nrhs)
+            on = (x + t) % 2 == color
+            y.reshape(lx * lt, d, nrhs)[on] += (Ainv @ r)[on]
+        err = np.linalg.norm(out.T - y, axis=0) / np.linalg.norm(y, axis=0)
+        assert err.max() <= tol, (prec, err.max())
+
+
 @pytest.mark.parametrize("k", [0, 4, 65])
 @pytest.mark.parametrize("Lx,Lt,ntv,few", [(64, 64, 4, 1), (64, 40, 5, 1), (56, 48, 6, 1), (48, 48, 7, 1), (64, 32, 8, 3),
                                            (40, 32, 12, 1), (32, 32, 16, 2)])
