@@ -145,28 +145,30 @@ __global__ __launch_bounds__(256) void wilson_kernel(const Cx<R>* __restrict__ U
 // The scalar kernels below ask for CHUNK block (or interpolation) entries and their vector
 // entries before the first product, so that a thread waits for memory once per chunk; the
 // products keep their order.  A uniform branch around each of them costs more than the load
-// and the product together, so the usual dofs are template arguments (D; 0: any), right-hand
-// sides past the last repeat it, and a thread with one right-hand side has the next
-// direction's entries on their way during this one's products.
+// and the product together, so all dofs up to 16 (eight test vectors) are template arguments (D),
+// more go by whole chunks (0), right-hand sides past the last repeat it, and a thread with one
+// right-hand side has the next direction's entries on their way during this one's products.
 constexpr int CHUNK = 8;
 
 // Coarse block stencil: y_s = sum_dir A[s][dir] x_{s+dir}; blocks column-major
 // (A[s][dir][j * d + i] = row i, column j).  Thread per (site, row), RB right-hand sides
 // per thread so that every block entry is loaded once per RB vectors.  Measured at 256 sites,
 // 16 dofs, FP64, one RHS: 17 us with a load and its product at a time on 16 workgroups, 7.6 with
-// 16 at a time on 64, 3.7 straight-line.
+// 16 at a time on 64, 3.7 straight-line; at 4096 sites, FP32, 16 RHS, a load and product at a time / by
+// chunks with a branch per entry / as here: 14 dofs 65 / 46 / 33, 24 dofs 160 / 137 / 91; at 16384 sites, 2
+// RHS, 24 dofs 142 / 192 / 104 (with groups of four right-hand sides the first two).  D = -1: any dofs,
+// entry by entry.
 template <typename R, int RB, bool G5, typename RO, int D>
 __global__ __launch_bounds__(256) void coarse_kernel(const Cx<R>* __restrict__ A, const Cx<R>* __restrict__ in,
                                                      Cx<RO>* __restrict__ out, int Lx, int Lt, int dofs, int spb,
                                                      int nrhs, int64_t ldx, int64_t ldy,
                                                      const Cx<R>* __restrict__ sub) {
-  const int d = D ? D : dofs;
+  const int d = D > 0 ? D : dofs;
   const int64_t V = (int64_t)Lx * Lt;
   const int i = threadIdx.x % d;
   const int64_t s = (int64_t)blockIdx.x * spb + threadIdx.x / d;
   if (threadIdx.x >= spb * d || s >= V) return;
   const Nbr nb = neighbours(s, Lx, Lt);
-  const int64_t sites[5] = {s, nb.xp, nb.xm, nb.tp, nb.tm};
   const int r0 = blockIdx.y * RB;
   const int nr = min(RB, nrhs - r0);
   Cx<R> acc[RB];
@@ -218,7 +220,10 @@ __global__ __launch_bounds__(256) void coarse_kernel(const Cx<R>* __restrict__ A
         products(0);
       }
     }
-  } else {
+  } else if constexpr (D == 0 && RB == 4 && sizeof(R) == 8) {
+    // (a branch per entry all the same: 5 to 15 % faster than the form below, which is up to 1.7
+    // times faster in FP32 and with fewer right-hand sides)
+    const int64_t sites[5] = {s, nb.xp, nb.xm, nb.tp, nb.tm};
 #pragma unroll
     for (int dir = 0; dir < 5; ++dir) {
       for (int j0 = 0; j0 < d; j0 += CHUNK) {
@@ -238,6 +243,35 @@ __global__ __launch_bounds__(256) void coarse_kernel(const Cx<R>* __restrict__ A
             for (int q = 0; q < RB; ++q) cfma(acc[q], a[j], x[q][j]);
           }
         }
+      }
+    }
+  } else {
+    constexpr int CH = D == 0 ? CHUNK : 1;
+#pragma unroll 1
+    for (int dir = 0; dir < 5; ++dir) {
+      const int64_t site = dir == 0 ? s : dir == 1 ? nb.xp : dir == 2 ? nb.xm : dir == 3 ? nb.tp : nb.tm;
+      const Cx<R>* Ad = Ab + dir * d * d;
+      const int64_t xo = site * d;
+      int j0 = 0;
+      for (; D == 0 && j0 + CH <= d; j0 += CH) {
+        Cx<R> a[CH], x[RB][CH];
+#pragma unroll
+        for (int j = 0; j < CH; ++j) {
+          a[j] = Ad[(j0 + j) * d];
+#pragma unroll
+          for (int q = 0; q < RB; ++q) x[q][j] = xq[q][xo + j0 + j];
+        }
+        __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+        for (int j = 0; j < CH; ++j) {
+#pragma unroll
+          for (int q = 0; q < RB; ++q) cfma(acc[q], a[j], x[q][j]);
+        }
+      }
+      for (; j0 < d; ++j0) {
+        const Cx<R> a = Ad[j0 * d];
+#pragma unroll
+        for (int q = 0; q < RB; ++q) cfma(acc[q], a, xq[q][xo + j0]);
       }
     }
   }
@@ -1918,7 +1952,17 @@ static void launch_coarse_scalar(dmlmc_ctx* ctx, const Level& L, const Cx<R>* A,
     case 10: COARSE_DOFS(10); break;
     case 12: COARSE_DOFS(12); break;
     case 16: COARSE_DOFS(16); break;
-    default: COARSE_DOFS(0);
+  // Entry by entry where FP64 blocks a little beyond the 256 MB last-level cache are read by several
+  // groups (32 dofs, 4096 sites, 335 MB, 32 RHS: 528 us, in chunks 644; at 16384 sites, 1.3 GB, 2914 and 2626)
+  constexpr bool F64 = std::is_same<R, double>::value;
+  const double blocks = (double)V * 5 * d * d * sizeof(Cx<R>);
+  const bool plain = d > 24 && nrhs >= 16 && blocks > 256e6 && blocks < 1e9;
+    default:
+      if (F64 && RB == 4 && plain) {
+        COARSE_DOFS(-1);
+      } else {
+        COARSE_DOFS(0);
+      }
   }
 #undef COARSE_DOFS
   LAUNCH_CHECK();
@@ -1926,9 +1970,19 @@ static void launch_coarse_scalar(dmlmc_ctx* ctx, const Level& L, const Cx<R>* A,
 
 template <typename R>
 void launch_coarse(dmlmc_ctx* ctx, const Level& L, const Cx<R>* x, Cx<R>* y, int nrhs, int64_t ldx, int64_t ldy,
+    case 2: COARSE_DOFS(2); break;
+    case 4: COARSE_DOFS(4); break;
+    case 6: COARSE_DOFS(6); break;
                    bool gamma5_left, const Cx<R>* sub) {
   const int d = L.dofs;
   const int64_t V = L.sites();
+    case 14:
+      if (F64 && RB == 4) {
+        COARSE_DOFS(0);
+      } else {
+        COARSE_DOFS(14);
+      }
+      break;
   const Cx<R>* A = std::is_same<R, float>::value ? (const Cx<R>*)L.A32.p : (const Cx<R>*)L.A64.p;
   REQUIRE(!(sub && gamma5_left), "the residual form has no Gamma5");
   KTimer kt(ctx, "coarse",
@@ -2004,6 +2058,8 @@ void apply_op(dmlmc_ctx* ctx, const Level& L, const Cx<R>* x, Cx<R>* y, int nrhs
   else
     launch_coarse<R>(ctx, L, x, y, nrhs, ld, ld, gamma5_left, nullptr);
 }
+  else if (nrhs == 2)
+    launch_coarse_scalar<R, 2, R>(ctx, L, A, x, y, nrhs, ldx, ldy, gamma5_left, sub);
 
 template <typename R>
 void apply_residual(dmlmc_ctx* ctx, const Level& L, const Cx<R>* x, const Cx<R>* b, Cx<R>* r, int nrhs) {
@@ -2058,6 +2114,8 @@ void launch_sap(dmlmc_ctx* ctx, const Level& L, Cx<R>* x, const Cx<R>* b, int nr
   const Cx<R>* U = std::is_same<R, float>::value ? (const Cx<R>*)L.U32.p : (const Cx<R>*)L.U64.p;
   const int64_t V = L.sites();
   // 4 RHS per thread (more workgroups in flight) unless tuned
+  else if (nrhs == 2)
+    launch_coarse_scalar<double, 2, float>(ctx, L, L.A64.as<c128>(), x, r, nrhs, ldx, ldr, false, b);
   const int rb = L.kv[KV_SAP_RB] > 0 ? std::min(L.kv[KV_SAP_RB], nrhs) : std::min(4, rhs_block_for(V, nrhs));
   // algorithmic bytes of one colour: x of every site (the colour's own and its halo) read
   // once, b read and x written on the colour's sites (two vector passes), and the links

@@ -253,6 +253,55 @@ def test_deflation_of_many_vectors(shape, prec, k, m):
         assert np.linalg.norm(x[r] - ref) <= (2e-4 if mixed else 1e-11) * np.linalg.norm(ref), (shape, prec, k, r)
 
 
+@pytest.mark.parametrize("Lx,Lt,agg,ntv,nrhs", [
+    (16, 16, (4, 4), 2, 1), (16, 16, (4, 4), 2, 2), (16, 16, (4, 4), 2, 5), (24, 16, (4, 4), 7, 1), (24, 16, (4, 4), 7, 2),
+    (24, 16, (4, 4), 7, 6), (16, 16, (4, 4), 9, 1), (16, 16, (4, 4), 9, 2), (16, 16, (4, 4), 9, 5),  # 4, 14, 18 dofs
+    (16, 16, (4, 4), 1, 2), (16, 16, (4, 4), 3, 2), (16, 16, (4, 4), 8, 2), (16, 16, (2, 2), 4, 7),
+    (16, 16, (4, 4), 16, 3), (16, 16, (4, 4), 11, 6),  # 32 and 22 dofs: remainders of the chunks of 0 and 6
+    (256, 256, (4, 4), 6, 30), (256, 256, (4, 4), 7, 16),  # restriction by half chunks in FP64
+    (256, 256, (4, 4), 16, 16),  # blocks of 335 MB in FP64, entry by entry
+])
+def test_coarse_operator_and_transfers_by_dofs(Lx, Lt, agg, ntv, nrhs):
+    """D, P^H and P for any number of test vectors, incomplete groups of four right-hand sides
+    included; the references on three of them."""
+    import torch
+
+    from paper_2211_15383_amd import dmlmc
+
+    rng = np.random.default_rng(53)
+
+    def cn(*s):
+        return rng.standard_normal(s) + 1j * rng.standard_normal(s)
+
+    (ax, at), lx, lt = agg, Lx // agg[0], Lt // agg[1]
+    # test vectors orthonormal on each (aggregate, chirality) block: the blocks of P
+    B = np.linalg.qr(cn(lt * lx * 2, ax * at, ntv))[0]
+    tv = B.reshape(lt, lx, 2, at, ax, ntv).transpose(0, 3, 1, 4, 2, 5).reshape(-1, ntv)
+    H = dmlmc.Hierarchy(dmlmc.Context(0), rng.normal(0.0, 0.3, (2, Lt, Lx)), 0.1, [agg], [ntv],
+                        import_tv=[np.ascontiguousarray(tv)])
+    A = H.export(2, Dc=True)["Dc"]
+    xf, xc = cn(nrhs, H.n(1)), cn(nrhs, H.n(2))
+    rows = sorted({0, nrhs // 2, nrhs - 1})
+
+    def aggregated(x):
+        return x.reshape(-1, lt, at, lx, ax, 2).transpose(0, 1, 3, 5, 2, 4).reshape(-1, lt * lx * 2, ax * at)
+
+    for prec, dt, tol in ((dmlmc.FP64, torch.complex128, 1e-13), (dmlmc.MIXED, torch.complex64, 1e-6)):
+        f, c = (torch.as_tensor(v, device="cuda").to(dt) for v in (xf, xc))
+        hf, hc = (t[rows].cpu().numpy().astype(np.complex128) for t in (f, c))
+        for op, lv, src, shape, ref in (
+                (dmlmc.OP_D, 2, c, c.shape, _blocks_apply(A, lx, lt, hc.T).T),
+                (dmlmc.OP_RESTRICT, 1, f, c.shape, np.einsum("bri,qbr->qbi", B.conj(), aggregated(hf)).reshape(len(rows), -1)),
+                (dmlmc.OP_PROLONG, 1, c, f.shape, np.einsum("bri,qbi->qbr", B, hc.reshape(len(rows), -1, ntv)))):
+            out = H.apply(op, lv, src, torch.full(shape, float("nan"), dtype=dt, device="cuda"), prec=prec)
+            assert torch.isfinite(torch.view_as_real(out)).all()
+            out = out[rows].cpu().numpy()
+            if op == dmlmc.OP_PROLONG:
+                out = aggregated(out)
+            err = [np.linalg.norm(o - r) / np.linalg.norm(r) for o, r in zip(out, ref)]
+            assert max(err) <= tol, (prec, op, err)
+
+
 @pytest.mark.parametrize("Lx,Lt,ntv,nrhs", [
     (16, 16, 1, 3), (16, 24, 2, 3), (24, 16, 7, 3), (16, 16, 9, 2),  # 2, 4 and 14 dofs prefetching, 18 in chunks
     (64, 64, 2, 257), (64, 64, 3, 257),  # 4 and 6 dofs by directions, 257 right-hand sides
