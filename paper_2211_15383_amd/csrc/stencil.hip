@@ -1940,6 +1940,11 @@ static void launch_coarse_scalar(dmlmc_ctx* ctx, const Level& L, const Cx<R>* A,
   const int threads = ceil_div(V * d, 256) * ceil_div(nrhs, RB) >= 2048 ? 256 : 64;
   const int spb = std::max(1, threads / d);
   const dim3 grid((unsigned)ceil_div(V, spb), (unsigned)ceil_div(nrhs, RB)), block((unsigned)(spb * d));
+  // Entry by entry where FP64 blocks a little beyond the 256 MB last-level cache are read by several
+  // groups (32 dofs, 4096 sites, 335 MB, 32 RHS: 528 us, in chunks 644; at 16384 sites, 1.3 GB, 2914 and 2626)
+  constexpr bool F64 = std::is_same<R, double>::value;
+  const double blocks = (double)V * 5 * d * d * sizeof(Cx<R>);
+  const bool plain = d > 24 && nrhs >= 16 && blocks > 256e6 && blocks < 1e9;
 #define COARSE_DOFS(D)                                                                                                 \
   if (gamma5_left)                                                                                                    \
     hipLaunchKernelGGL((coarse_kernel<R, RB, true, RO, D>), grid, block, 0, ctx->stream, A, x, y, L.Lx, L.Lt, d, spb,  \
@@ -1948,15 +1953,20 @@ static void launch_coarse_scalar(dmlmc_ctx* ctx, const Level& L, const Cx<R>* A,
     hipLaunchKernelGGL((coarse_kernel<R, RB, false, RO, D>), grid, block, 0, ctx->stream, A, x, y, L.Lx, L.Lt, d, spb, \
                        nrhs, ldx, ldy, sub)
   switch (d) {
+    case 2: COARSE_DOFS(2); break;
+    case 4: COARSE_DOFS(4); break;
+    case 6: COARSE_DOFS(6); break;
     case 8: COARSE_DOFS(8); break;
     case 10: COARSE_DOFS(10); break;
     case 12: COARSE_DOFS(12); break;
+    case 14:
+      if (F64 && RB == 4) {
+        COARSE_DOFS(0);
+      } else {
+        COARSE_DOFS(14);
+      }
+      break;
     case 16: COARSE_DOFS(16); break;
-  // Entry by entry where FP64 blocks a little beyond the 256 MB last-level cache are read by several
-  // groups (32 dofs, 4096 sites, 335 MB, 32 RHS: 528 us, in chunks 644; at 16384 sites, 1.3 GB, 2914 and 2626)
-  constexpr bool F64 = std::is_same<R, double>::value;
-  const double blocks = (double)V * 5 * d * d * sizeof(Cx<R>);
-  const bool plain = d > 24 && nrhs >= 16 && blocks > 256e6 && blocks < 1e9;
     default:
       if (F64 && RB == 4 && plain) {
         COARSE_DOFS(-1);
@@ -1970,19 +1980,9 @@ static void launch_coarse_scalar(dmlmc_ctx* ctx, const Level& L, const Cx<R>* A,
 
 template <typename R>
 void launch_coarse(dmlmc_ctx* ctx, const Level& L, const Cx<R>* x, Cx<R>* y, int nrhs, int64_t ldx, int64_t ldy,
-    case 2: COARSE_DOFS(2); break;
-    case 4: COARSE_DOFS(4); break;
-    case 6: COARSE_DOFS(6); break;
                    bool gamma5_left, const Cx<R>* sub) {
   const int d = L.dofs;
   const int64_t V = L.sites();
-    case 14:
-      if (F64 && RB == 4) {
-        COARSE_DOFS(0);
-      } else {
-        COARSE_DOFS(14);
-      }
-      break;
   const Cx<R>* A = std::is_same<R, float>::value ? (const Cx<R>*)L.A32.p : (const Cx<R>*)L.A64.p;
   REQUIRE(!(sub && gamma5_left), "the residual form has no Gamma5");
   KTimer kt(ctx, "coarse",
@@ -2046,6 +2046,8 @@ void launch_coarse(dmlmc_ctx* ctx, const Level& L, const Cx<R>* x, Cx<R>* y, int
   }
   if (nrhs == 1)
     launch_coarse_scalar<R, 1, R>(ctx, L, A, x, y, nrhs, ldx, ldy, gamma5_left, sub);
+  else if (nrhs == 2)
+    launch_coarse_scalar<R, 2, R>(ctx, L, A, x, y, nrhs, ldx, ldy, gamma5_left, sub);
   else
     launch_coarse_scalar<R, 4, R>(ctx, L, A, x, y, nrhs, ldx, ldy, gamma5_left, sub);
 }
@@ -2058,8 +2060,6 @@ void apply_op(dmlmc_ctx* ctx, const Level& L, const Cx<R>* x, Cx<R>* y, int nrhs
   else
     launch_coarse<R>(ctx, L, x, y, nrhs, ld, ld, gamma5_left, nullptr);
 }
-  else if (nrhs == 2)
-    launch_coarse_scalar<R, 2, R>(ctx, L, A, x, y, nrhs, ldx, ldy, gamma5_left, sub);
 
 template <typename R>
 void apply_residual(dmlmc_ctx* ctx, const Level& L, const Cx<R>* x, const Cx<R>* b, Cx<R>* r, int nrhs) {
@@ -2102,6 +2102,8 @@ void apply_residual_to32(dmlmc_ctx* ctx, const Level& L, const c128* x, const c1
   }
   if (nrhs == 1)
     launch_coarse_scalar<double, 1, float>(ctx, L, L.A64.as<c128>(), x, r, nrhs, ldx, ldr, false, b);
+  else if (nrhs == 2)
+    launch_coarse_scalar<double, 2, float>(ctx, L, L.A64.as<c128>(), x, r, nrhs, ldx, ldr, false, b);
   else
     launch_coarse_scalar<double, 4, float>(ctx, L, L.A64.as<c128>(), x, r, nrhs, ldx, ldr, false, b);
 }
@@ -2114,8 +2116,6 @@ void launch_sap(dmlmc_ctx* ctx, const Level& L, Cx<R>* x, const Cx<R>* b, int nr
   const Cx<R>* U = std::is_same<R, float>::value ? (const Cx<R>*)L.U32.p : (const Cx<R>*)L.U64.p;
   const int64_t V = L.sites();
   // 4 RHS per thread (more workgroups in flight) unless tuned
-  else if (nrhs == 2)
-    launch_coarse_scalar<double, 2, float>(ctx, L, L.A64.as<c128>(), x, r, nrhs, ldx, ldr, false, b);
   const int rb = L.kv[KV_SAP_RB] > 0 ? std::min(L.kv[KV_SAP_RB], nrhs) : std::min(4, rhs_block_for(V, nrhs));
   // algorithmic bytes of one colour: x of every site (the colour's own and its halo) read
   // once, b read and x written on the colour's sites (two vector passes), and the links
