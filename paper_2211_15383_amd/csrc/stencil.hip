@@ -546,7 +546,7 @@ __global__ __launch_bounds__(256) void coarse_gs_kernel(const Cx<R>* __restrict_
 // local site * h + dof within chirality, local site = lx + ax * lt, h = d_f / 2.
 // Thread per (coarse dof, group of RB right-hand sides): each P entry is loaded once per
 // RB vectors.
-template <typename R, int RB>
+template <typename R, int RB, int CHUNK>
 __global__ __launch_bounds__(256) void restrict_kernel(const Cx<R>* __restrict__ P, const Cx<R>* __restrict__ xf,
                                                        Cx<R>* __restrict__ yc, int Lxf, int Ltf, int df, int ax,
                                                        int at, int N, int nrhs, int64_t ldf, int64_t ldc) {
@@ -2307,16 +2307,25 @@ void launch_restrict(dmlmc_ctx* ctx, const Level& L, const Cx<R>* xf, Cx<R>* yc,
     LAUNCH_CHECK();
     return;
   }
-  // 64-thread workgroups until 256-thread ones would be 1024, one RHS per thread for one RHS
-  const int RB = nrhs == 1 ? 1 : 4;
+  // 64-thread workgroups until 256-thread ones would be 1024; RHS per thread up to four.  Large FP64
+  // launches of six test vectors and more go by half chunks, as fewer registers keep more wavefronts
+  // (32 RHS from 256^2: 8 test vectors 37.2 -> 34.1 us, 16 64.8 -> 58.4; with up to 5 onto 128^2 sites 116 -> 122)
+  const int RB = nrhs < 3 ? nrhs : 4;
   const int wg = ceil_div(threads, 256) * ceil_div(nrhs, RB) >= 1024 ? 256 : 64;
   const dim3 grid((unsigned)ceil_div(threads, wg), (unsigned)ceil_div(nrhs, RB));
+#define RESTRICT(RB, CH)                                                                                             \
+  hipLaunchKernelGGL((restrict_kernel<R, RB, CH>), grid, dim3(wg), 0, ctx->stream, P, xf, yc, L.Lx, L.Lt, L.dofs, L.ax, \
+                     L.at, L.N, nrhs, ldf, ldc)
+  const bool half = std::is_same<R, double>::value && wg == 256 && L.N >= 6;
   if (RB == 1)
-    hipLaunchKernelGGL((restrict_kernel<R, 1>), grid, dim3(wg), 0, ctx->stream, P, xf, yc, L.Lx, L.Lt, L.dofs, L.ax,
-                       L.at, L.N, nrhs, ldf, ldc);
+    RESTRICT(1, CHUNK);
+  else if (RB == 2)
+    RESTRICT(2, CHUNK);
+  else if (half)
+    RESTRICT(4, CHUNK / 2);
   else
-    hipLaunchKernelGGL((restrict_kernel<R, 4>), grid, dim3(wg), 0, ctx->stream, P, xf, yc, L.Lx, L.Lt, L.dofs, L.ax,
-                       L.at, L.N, nrhs, ldf, ldc);
+    RESTRICT(4, CHUNK);
+#undef RESTRICT
   LAUNCH_CHECK();
 }
 
