@@ -630,13 +630,18 @@ __global__ __launch_bounds__(256) void restrict_kernel(const Cx<R>* __restrict__
     if (q < nr) yc[(int64_t)(r0 + q) * ldc + cs * 2 * N + c * N + k] = acc[q];
 }
 
-// Prolongation x_f (+)= P e_c; thread per (fine dof, group of RB right-hand sides).  A thread's
-// interpolation row is one request (FP64, 256^2 onto the fine level, 16 RHS: 105 -> 34 us).
+// Prolongation x_f (+)= P e_c; thread per (fine dof, group of RB right-hand sides, those of an
+// incomplete group one by one).  NT test vectors, or any number (0) by chunks; a thread's chunk of an
+// interpolation row is one request (FP64, 256^2 onto the fine level, 16 RHS: 105 -> 34 us).  With a
+// chunk of eight and a branch per entry for all but eight test vectors, and incomplete groups
+// filled up with their last right-hand side: 512^2, one test vector, FP64, 32 RHS 85 us against 65; 4 test
+// vectors, FP32, one RHS 11.2 against 6.6; 16^2, 16 test vectors, one RHS 10.1 against 6.2.
 template <typename R, int RB, int NT>
 __global__ __launch_bounds__(256) void prolong_kernel(const Cx<R>* __restrict__ P, const Cx<R>* __restrict__ ec,
                                                       Cx<R>* __restrict__ xf, int Lxf, int Ltf, int df, int ax, int at,
                                                       int ntv, int nrhs, int add, int64_t ldf, int64_t ldc) {
   const int N = NT ? NT : ntv;
+  constexpr int CH = NT ? NT : CHUNK;
   const int64_t nf = (int64_t)Lxf * Ltf * df;
   const int64_t tid = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
   if (tid >= nf) return;
@@ -650,35 +655,42 @@ __global__ __launch_bounds__(256) void prolong_kernel(const Cx<R>* __restrict__ 
   const int row = ((x - X * ax) + ax * (t - T * at)) * h + j;
   const int rows = ax * at * h;
   const Cx<R>* Pr = P + ((cs * 2 + c) * (int64_t)rows + row) * N;
-  const int r0 = blockIdx.y * RB;
-  const int nr = min(RB, nrhs - r0);
   const Cx<R>* er = ec + cs * 2 * N + c * N;
-  Cx<R> acc[RB];
+  auto group = [&](int r0, auto count) {
+    constexpr int B = decltype(count)::value;
+    Cx<R> acc[B];
 #pragma unroll
-  for (int q = 0; q < RB; ++q)
-    acc[q] = (add && q < nr) ? xf[(int64_t)(r0 + q) * ldf + tid] : cmk((R)0, (R)0);
-  for (int k0 = 0; k0 < N; k0 += CHUNK) {
-    Cx<R> pv[CHUNK], e[RB][CHUNK];
+    for (int q = 0; q < B; ++q) acc[q] = add ? xf[(int64_t)(r0 + q) * ldf + tid] : cmk((R)0, (R)0);
+    int k0 = 0;
+    for (; k0 + CH <= N; k0 += CH) {
+      Cx<R> pv[CH], e[B][CH];
 #pragma unroll
-    for (int k = 0; k < CHUNK; ++k) {
-      if (NT == CHUNK || k0 + k < N) {
+      for (int k = 0; k < CH; ++k) {
         pv[k] = Pr[k0 + k];
 #pragma unroll
-        for (int q = 0; q < RB; ++q) e[q][k] = er[min(r0 + q, nrhs - 1) * ldc + k0 + k];
+        for (int q = 0; q < B; ++q) e[q][k] = er[(r0 + q) * ldc + k0 + k];
+      }
+      __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+      for (int k = 0; k < CH; ++k) {
+#pragma unroll
+        for (int q = 0; q < B; ++q) cfma(acc[q], pv[k], e[q][k]);
       }
     }
-    __builtin_amdgcn_sched_barrier(0);
+    for (; !NT && k0 < N; ++k0) {
+      const Cx<R> p = Pr[k0];
 #pragma unroll
-    for (int k = 0; k < CHUNK; ++k) {
-      if (NT == CHUNK || k0 + k < N) {
-#pragma unroll
-        for (int q = 0; q < RB; ++q) cfma(acc[q], pv[k], e[q][k]);
-      }
+      for (int q = 0; q < B; ++q) cfma(acc[q], p, er[(r0 + q) * ldc + k0]);
     }
+#pragma unroll
+    for (int q = 0; q < B; ++q) xf[(int64_t)(r0 + q) * ldf + tid] = acc[q];
+  };
+  const int r0 = blockIdx.y * RB, r1 = min(r0 + RB, nrhs);
+  if (r1 - r0 == RB) {
+    group(r0, std::integral_constant<int, RB>());
+  } else {
+    for (int r = r0; r < r1; ++r) group(r, std::integral_constant<int, 1>());
   }
-#pragma unroll
-  for (int q = 0; q < RB; ++q)
-    if (q < nr) xf[(int64_t)(r0 + q) * ldf + tid] = acc[q];
 }
 
 // The same for eight test vectors on levels that fill the chip: thread per fine dof, every
@@ -2393,8 +2405,6 @@ void launch_prolong(dmlmc_ctx* ctx, const Level& L, const Cx<R>* ec, Cx<R>* xf, 
     LAUNCH_CHECK();
     return;
   }
-  constexpr int RB = 4;
-  dim3 grid((unsigned)ceil_div(nf, 256), (unsigned)ceil_div(nrhs, RB));
   if (L.N == 8 && ceil_div(nf, 256) >= 256) {
     // about 1024 workgroups, a pair of right-hand sides each at least (as many more re-read P:
     // 1024^2, 16 RHS 331 us with one workgroup a row block, 382 with four)
@@ -2405,12 +2415,22 @@ void launch_prolong(dmlmc_ctx* ctx, const Level& L, const Cx<R>* ec, Cx<R>* xf, 
     LAUNCH_CHECK();
     return;
   }
-  if (L.N == CHUNK)
-    hipLaunchKernelGGL((prolong_kernel<R, RB, CHUNK>), grid, dim3(256), 0, ctx->stream, P, ec, xf, L.Lx, L.Lt, L.dofs,
-                       L.ax, L.at, L.N, nrhs, add ? 1 : 0, ldf, ldc);
-  else
-    hipLaunchKernelGGL((prolong_kernel<R, RB, 0>), grid, dim3(256), 0, ctx->stream, P, ec, xf, L.Lx, L.Lt, L.dofs, L.ax,
-                       L.at, L.N, nrhs, add ? 1 : 0, ldf, ldc);
+  const dim3 grid((unsigned)ceil_div(nf, 256), (unsigned)ceil_div(nrhs, 4));
+#define PROLONG(NT)                                                                                                 \
+  hipLaunchKernelGGL((prolong_kernel<R, 4, NT>), grid, dim3(256), 0, ctx->stream, P, ec, xf, L.Lx, L.Lt, L.dofs, L.ax, \
+                     L.at, L.N, nrhs, add ? 1 : 0, ldf, ldc)
+  switch (L.N) {
+    case 1: PROLONG(1); break;
+    case 2: PROLONG(2); break;
+    case 3: PROLONG(3); break;
+    case 4: PROLONG(4); break;
+    case 5: PROLONG(5); break;
+    case 6: PROLONG(6); break;
+    case 7: PROLONG(7); break;
+    case 8: PROLONG(8); break;
+    default: PROLONG(0);
+  }
+#undef PROLONG
   LAUNCH_CHECK();
 }
 
