@@ -1862,18 +1862,23 @@ struct WilsonGrid {
 // Tiles where at most an eighth of their threads lies outside the lattice, from 2^15 sites
 // (linear -> tiles, 32 RHS: 1024^2 253 -> 234 us in FP32 and 598 -> 567 in FP64, 400 x 300
 // 38.6 -> 37.0; with a quarter outside, 200 x 180, 18.6 -> 19.5; 128^2 20.0 -> 20.2).
-// Right-hand sides per thread: 8 while input and output (`bytes` an entry pair) fit into
-// the 256 MB last-level cache, as links are then re-read least (1024^2, 4 RHS: 37.9 us, with
-// 2 39.7); beyond it 2, since few streams at a time keep the neighbours' rows in the L2s
-// (768 x 600, 32 RHS: 87.1 -> 79.5 us; 512^2 57.0 -> 53.9).
+// Right-hand sides per thread: up to 8, as links are then re-read least, while input and output
+// (`bytes` an entry pair) fit into the 256 MB last-level cache (1024^2, FP32, 4 RHS: 37.9 us, with 2 39.7)
+// or each of them does (1024^2, FP64, 5 RHS 60.8 us, with 2 70.7; FP32, 12 RHS 64.7 and 72.4; 400 x 300, 128
+// RHS 79.9 and 88.3).  Beyond that 2, since few streams at a time keep the neighbours' rows in the L2s
+// (1024^2, FP32, 16 RHS 110 us, with 8 116), and with 16 RHS and whole tiles of rows of up to 16 KB already
+// from the cache's size on (512^2, 32 RHS 41.2 and 44.8; 768 x 600 67.3 and 74.8, but FP64, 16 RHS 92.5 and 82.3).
 WilsonGrid wilson_grid(const Level& L, int nrhs, size_t bytes) {
   const int64_t V = L.sites(), tx = ceil_div(L.Lx, TILE_X), tt = ceil_div(L.Lt, TILE_T);
   const bool tiles = V >= 32768 && 8 * (tx * tt * TILE_X * TILE_T) <= 9 * V;
+  const double total = (double)nrhs * L.n() * bytes;
   WilsonGrid g;
   g.blocks = (unsigned)(tiles ? tx * tt : ceil_div(V, 256));
   g.tiles_x = tiles ? (int)tx : 0;
-  const int most = tiles && (double)nrhs * L.n() * bytes > 256e6 ? 2 : 8;
+  const bool rows = nrhs >= 16 && L.Lx % TILE_X == 0 && L.Lx * bytes <= 16384;
+  const int most = tiles && (total > 512e6 || (total > 256e6 && rows)) ? 2 : 8;
   g.rb = L.kv[KV_WILSON_RB] > 0 ? std::min(L.kv[KV_WILSON_RB], nrhs) : std::min(most, rhs_block_for(V, nrhs));
+
   return g;
 }
 }  // namespace

@@ -41,3 +41,22 @@ def test_stencil_tiles(gpu, Lx, Lt, nrhs, precs):
         assert rel_err(to_host(y), ref) < tol, name
         H.apply(dm.OP_GAMMA5_D, 1, xd, y, prec)
         assert rel_err(to_host(y), g5[:, None] * ref) < tol, name
+
+
+@pytest.mark.parametrize("Lx,Lt,nrhs,name", [
+    (400, 300, 33, "fp64"),   # 253 MB, just within the cache
+    (400, 300, 65, "fp64"),   # beyond it, ragged tiles: 8 right-hand sides per thread
+    (256, 132, 119, "fp64"),  # beyond it, whole tiles: 2
+    (1024, 64, 130, "fp64"),  # 545 MB, both vectors beyond it: 2
+])
+def test_stencil_right_hand_sides_per_thread(gpu, Lx, Lt, nrhs, name):
+    torch, dm, ctx = gpu
+    theta = link_angles(Lx, Lt, 0.5, Lx * 1000 + Lt)
+    H = dm.Hierarchy(ctx, theta, -0.07, [], [])
+    D = ow.dirac_operator(theta, -0.07)
+    xd = torch.randn((nrhs, H.n(1)), dtype=torch.complex128, device="cuda",
+                     generator=torch.Generator("cuda").manual_seed(2))
+    y = H.apply(dm.OP_D, 1, xd, torch.full_like(xd, float("nan")), dm.FP64)
+    for r in (0, nrhs // 2, nrhs - 2, nrhs - 1):
+        ref = D @ xd[r].cpu().numpy()
+        assert np.linalg.norm(y[r].cpu().numpy() - ref) < 1e-13 * np.linalg.norm(ref), r
