@@ -1870,7 +1870,8 @@ struct WilsonGrid {
 // from the cache's size on (512^2, 32 RHS 41.2 and 44.8; 768 x 600 67.3 and 74.8, but FP64, 16 RHS 92.5 and 82.3).
 WilsonGrid wilson_grid(const Level& L, int nrhs, size_t bytes) {
   const int64_t V = L.sites(), tx = ceil_div(L.Lx, TILE_X), tt = ceil_div(L.Lt, TILE_T);
-  const bool tiles = V >= 32768 && 8 * (tx * tt * TILE_X * TILE_T) <= 9 * V;
+  // (a launch has fewer than 2^32 threads in x and 65536 workgroups in y)
+  const bool tiles = V >= 32768 && 8 * (tx * tt * TILE_X * TILE_T) <= 9 * V && tx * tt < (1 << 24);
   const double total = (double)nrhs * L.n() * bytes;
   WilsonGrid g;
   g.blocks = (unsigned)(tiles ? tx * tt : ceil_div(V, 256));
@@ -1878,7 +1879,7 @@ WilsonGrid wilson_grid(const Level& L, int nrhs, size_t bytes) {
   const bool rows = nrhs >= 16 && L.Lx % TILE_X == 0 && L.Lx * bytes <= 16384;
   const int most = tiles && (total > 512e6 || (total > 256e6 && rows)) ? 2 : 8;
   g.rb = L.kv[KV_WILSON_RB] > 0 ? std::min(L.kv[KV_WILSON_RB], nrhs) : std::min(most, rhs_block_for(V, nrhs));
-
+  g.rb = std::max(g.rb, (int)ceil_div(nrhs, 65535));
   return g;
 }
 }  // namespace

@@ -43,6 +43,19 @@ def test_stencil_tiles(gpu, Lx, Lt, nrhs, precs):
         assert rel_err(to_host(y), g5[:, None] * ref) < tol, name
 
 
+def test_stencil_of_more_right_hand_sides_than_workgroup_rows(gpu):
+    """70000 right-hand sides with one asked for per thread: the launch has at most 65535 rows of
+    workgroups.  The first, middle and last rows are those of small blocks."""
+    torch, dm, ctx = gpu
+    H = dm.Hierarchy(ctx, link_angles(8, 8, 0.5, 3), -0.07, [], [])
+    H.set_kernel_variant(1, dm.KV_WILSON_RB, 1)
+    x = torch.randn((70000, H.n(1)), dtype=torch.complex64, device="cuda", generator=torch.Generator("cuda").manual_seed(1))
+    y = H.apply(dm.OP_D, 1, x, torch.full_like(x, float("nan")), dm.MIXED)
+    for r in (0, 1, 34999, 65535, 65536, 69999):
+        ref = H.apply(dm.OP_D, 1, x[r:r + 1], torch.empty_like(x[:1]), dm.MIXED)
+        assert torch.equal(torch.view_as_real(y[r:r + 1]), torch.view_as_real(ref))
+
+
 @pytest.mark.parametrize("Lx,Lt,nrhs,name", [
     (400, 300, 33, "fp64"),   # 253 MB, just within the cache
     (400, 300, 65, "fp64"),   # beyond it, ragged tiles: 8 right-hand sides per thread
