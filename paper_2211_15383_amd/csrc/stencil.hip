@@ -1868,7 +1868,8 @@ struct WilsonGrid {
 // RHS 79.9 and 88.3).  Beyond that 2, since few streams at a time keep the neighbours' rows in the L2s
 // (1024^2, FP32, 16 RHS 110 us, with 8 116), and with 16 RHS and whole tiles of rows of up to 16 KB already
 // from the cache's size on (512^2, 32 RHS 41.2 and 44.8; 768 x 600 67.3 and 74.8, but FP64, 16 RHS 92.5 and 82.3).
-WilsonGrid wilson_grid(const Level& L, int nrhs, size_t bytes) {
+// `variant` (0: none) is a choice made by hand or by the tuner.
+WilsonGrid wilson_grid(const Level& L, int nrhs, size_t bytes, int variant) {
   const int64_t V = L.sites(), tx = ceil_div(L.Lx, TILE_X), tt = ceil_div(L.Lt, TILE_T);
   // (a launch has fewer than 2^32 threads in x and 65536 workgroups in y)
   const bool tiles = V >= 32768 && 8 * (tx * tt * TILE_X * TILE_T) <= 9 * V && tx * tt < (1 << 24);
@@ -1878,7 +1879,7 @@ WilsonGrid wilson_grid(const Level& L, int nrhs, size_t bytes) {
   g.tiles_x = tiles ? (int)tx : 0;
   const bool rows = nrhs >= 16 && L.Lx % TILE_X == 0 && L.Lx * bytes <= 16384;
   const int most = tiles && (total > 512e6 || (total > 256e6 && rows)) ? 2 : 8;
-  g.rb = L.kv[KV_WILSON_RB] > 0 ? std::min(L.kv[KV_WILSON_RB], nrhs) : std::min(most, rhs_block_for(V, nrhs));
+  g.rb = variant > 0 ? std::min(variant, nrhs) : std::min(most, rhs_block_for(V, nrhs));
   g.rb = std::max(g.rb, (int)ceil_div(nrhs, 65535));
   return g;
 }
@@ -1888,7 +1889,7 @@ template <typename R>
 void launch_wilson(dmlmc_ctx* ctx, const Level& L, const Cx<R>* x, Cx<R>* y, int nrhs, int64_t ldx, int64_t ldy,
                    bool gamma5_left, const Cx<R>* sub) {
   const int64_t V = L.sites();
-  const WilsonGrid g = wilson_grid(L, nrhs, 2 * sizeof(Cx<R>));
+  const WilsonGrid g = wilson_grid(L, nrhs, 2 * sizeof(Cx<R>), L.kv[KV_WILSON_RB]);
   const dim3 grid(g.blocks, (unsigned)ceil_div(nrhs, g.rb));
   const Cx<R>* U = std::is_same<R, float>::value ? (const Cx<R>*)L.U32.p : (const Cx<R>*)L.U64.p;
   REQUIRE(!(sub && gamma5_left), "the residual form has no Gamma5");
@@ -2097,7 +2098,8 @@ void apply_residual_to32(dmlmc_ctx* ctx, const Level& L, const c128* x, const c1
   // reads x and b (FP64), writes r (complex FP32)
   const double vec_bytes = (double)nrhs * L.n() * (2 * sizeof(c128) + sizeof(c64));
   if (L.fine) {
-    const WilsonGrid g = wilson_grid(L, nrhs, 2 * sizeof(c128));
+    // (the variant is timed on the complex-FP32 stencil and does not reach this form)
+    const WilsonGrid g = wilson_grid(L, nrhs, 2 * sizeof(c128), 0);
     const dim3 grid(g.blocks, (unsigned)ceil_div(nrhs, g.rb));
     KTimer kt(ctx, "wilson", vec_bytes + (double)V * 2 * sizeof(c128));
     hipLaunchKernelGGL((wilson_kernel<double, false, float>), grid, dim3(256), 0, ctx->stream, L.U64.as<c128>(), x,
