@@ -162,6 +162,39 @@ __device__ __forceinline__ c64 row_of_pairs(const float4* As, const c64* __restr
   return acc;
 }
 
+// The same for any number of column pairs, CS_COLS / 2 of them at a time, then those that are left
+__device__ __forceinline__ c64 row_in_chunks(const float4* As, const c64* __restrict__ u, const int (&nb)[5], int d) {
+  constexpr int CH = CS_COLS / 2;
+  const int pairs = d / 2;
+  c64 acc = cmk(0.f, 0.f);
+#pragma unroll 1
+  for (int dir = 0; dir < 5; ++dir) {
+    const int site = dir == 0 ? nb[0] : dir == 1 ? nb[1] : dir == 2 ? nb[2] : dir == 3 ? nb[3] : nb[4];
+    const float4* ud = reinterpret_cast<const float4*>(u + site * d);
+    const float4* Ad = As + dir * pairs * d;
+    int q0 = 0;
+#pragma unroll 1
+    for (; q0 + CH <= pairs; q0 += CH) {
+      float4 m[CH];
+#pragma unroll
+      for (int q = 0; q < CH; ++q) m[q] = Ad[(q0 + q) * d];
+#pragma unroll
+      for (int q = 0; q < CH; ++q) {
+        const float4 v = ud[q0 + q];
+        cfma(acc, cmk(m[q].x, m[q].y), cmk(v.x, v.y));
+        cfma(acc, cmk(m[q].z, m[q].w), cmk(v.z, v.w));
+      }
+    }
+#pragma unroll 1
+    for (; q0 < pairs; ++q0) {
+      const float4 m = Ad[q0 * d], v = ud[q0];
+      cfma(acc, cmk(m.x, m.y), cmk(v.x, v.y));
+      cfma(acc, cmk(m.z, m.w), cmk(v.z, v.w));
+    }
+  }
+  return acc;
+}
+
 // w = D u in complex FP32 (u, w in LDS; blocks by column pairs, in LDS or global memory), a
 // thread per row, in the order of the coarse stencils; ends with a barrier
 template <bool D16>
@@ -193,31 +226,16 @@ __device__ void small_op(const SmallArgs& a, const c64* A, const c64* __restrict
         for (int k = 0; k < 4; ++k) v4[k] = ud[2 * k + 1];
         mfma_order(acc, m1, v4);
       }
-    } else if (pairs == 4) {
-      acc = row_of_pairs<4>(As, u, nb);
-    } else if (pairs == 5) {
-      acc = row_of_pairs<5>(As, u, nb);
     } else {
-#pragma unroll 1
-      for (int dir = 0; dir < 5; ++dir) {
-        const float4* Ad = As + dir * d * pairs;
-        const int site = dir == 0 ? nb[0] : dir == 1 ? nb[1] : dir == 2 ? nb[2] : dir == 3 ? nb[3] : nb[4];
-        const float4* ud = reinterpret_cast<const float4*>(u + site * d);
-#pragma unroll 1
-        for (int q0 = 0; q0 < pairs; q0 += CS_COLS / 2) {
-          float4 m4[CS_COLS / 2];
-#pragma unroll
-          for (int q = 0; q < CS_COLS / 2; ++q)
-            if (q0 + q < pairs) m4[q] = Ad[(q0 + q) * d];
-#pragma unroll
-          for (int q = 0; q < CS_COLS / 2; ++q) {
-            if (q0 + q < pairs) {
-              const float4 v = ud[q0 + q];
-              cfma(acc, cmk(m4[q].x, m4[q].y), cmk(v.x, v.y));
-              cfma(acc, cmk(m4[q].z, m4[q].w), cmk(v.z, v.w));
-            }
-          }
-        }
+      switch (pairs) {
+        case 1: acc = row_of_pairs<1>(As, u, nb); break;
+        case 2: acc = row_of_pairs<2>(As, u, nb); break;
+        case 3: acc = row_of_pairs<3>(As, u, nb); break;
+        case 4: acc = row_of_pairs<4>(As, u, nb); break;
+        case 5: acc = row_of_pairs<5>(As, u, nb); break;
+        case 6: acc = row_of_pairs<6>(As, u, nb); break;
+        case 7: acc = row_of_pairs<7>(As, u, nb); break;
+        default: acc = row_in_chunks(As, u, nb, d);
       }
     }
     w[row] = acc;
