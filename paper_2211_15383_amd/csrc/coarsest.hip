@@ -92,7 +92,7 @@ struct SmallArgs {
 // spilled registers).  The deflation coefficients are used before the Hessenberg matrix is.
 struct SmallShared {
   union {
-    c128 H[(CS_MAX_M + 1) * (CS_MAX_M + 3)];  // three columns more for the back substitution
+    c128 H[(CS_MAX_M + 1) * CS_MAX_M];
     c128 defl[2][CS_MAX_K];  // W^H b and Lambda^-1 W^H b
   };
   double stage[CS_WAVES * 64];
@@ -456,30 +456,31 @@ __device__ __forceinline__ void small_dots32(const Basis<float>& V, int nb, cons
         const double s = wave::sum16(acc);
         if ((lane & 3) == 0) stage[(wv % nw) * 64 + 2 * c0 + (lane >> 2)] = s;
       }
-    } else
-    for (int c0 = 4 * (wv / nw); c0 < nb; c0 += 4 * groups) {
-      double acc[8];
-      float4 u[4];
-#pragma unroll
-      for (int i = 0; i < 4; ++i)
-        u[i] = make_float4(0.f, 0.f, 0.f, 0.f);
-      // kl is a multiple of four or past the last vector: a group is in one part of the basis
-      if (c0 < V.kl) {
+    } else {
+      for (int c0 = 4 * (wv / nw); c0 < nb; c0 += 4 * groups) {
+        double acc[8];
+        float4 u[4];
 #pragma unroll
         for (int i = 0; i < 4; ++i)
-          if (on && c0 + i < nb) u[i] = reinterpret_cast<const float4*>(V.lds + (c0 + i) * n)[t];
-      } else {
+          u[i] = make_float4(0.f, 0.f, 0.f, 0.f);
+        // kl is a multiple of four or past the last vector: a group is in one part of the basis
+        if (c0 < V.kl) {
 #pragma unroll
-        for (int i = 0; i < 4; ++i)
-          if (on && c0 + i < nb) u[i] = reinterpret_cast<const float4*>(V.mem_at(c0 + i))[t];
-      }
+          for (int i = 0; i < 4; ++i)
+            if (on && c0 + i < nb) u[i] = reinterpret_cast<const float4*>(V.lds + (c0 + i) * n)[t];
+        } else {
 #pragma unroll
-      for (int i = 0; i < 4; ++i) {  // products of two floats are exact in FP64
-        acc[2 * i] = (((double)u[i].x * bx0 + (double)u[i].y * by0) + (double)u[i].z * bx1) + (double)u[i].w * by1;
-        acc[2 * i + 1] = (((double)u[i].x * by0 - (double)u[i].y * bx0) + (double)u[i].z * by1) - (double)u[i].w * bx1;
+          for (int i = 0; i < 4; ++i)
+            if (on && c0 + i < nb) u[i] = reinterpret_cast<const float4*>(V.mem_at(c0 + i))[t];
+        }
+#pragma unroll
+        for (int i = 0; i < 4; ++i) {  // products of two floats are exact in FP64
+          acc[2 * i] = (((double)u[i].x * bx0 + (double)u[i].y * by0) + (double)u[i].z * bx1) + (double)u[i].w * by1;
+          acc[2 * i + 1] = (((double)u[i].x * by0 - (double)u[i].y * bx0) + (double)u[i].z * by1) - (double)u[i].w * bx1;
+        }
+        const double s = wave::sum8(acc);
+        if ((lane & 7) == 0) stage[(wv % nw) * 64 + 2 * c0 + (lane >> 3)] = s;
       }
-      const double s = wave::sum8(acc);
-      if ((lane & 7) == 0) stage[(wv % nw) * 64 + 2 * c0 + (lane >> 3)] = s;
     }
   }
   __syncthreads();
