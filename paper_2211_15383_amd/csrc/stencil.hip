@@ -29,8 +29,9 @@ __device__ __forceinline__ int wave_index() { return __builtin_amdgcn_readfirstl
 struct Nbr {
   int64_t xp, xm, tp, tm;
 };
-// Sites, aggregates and level sizes are below 2^32 (a hierarchy's links alone take 48 bytes a
-// site), so their divisions are 32 bits wide here and below.  With the wavefront's site on the
+// The sites, aggregates and entries divided here and below are numbers of a launch's threads or
+// wavefronts, and a launch has fewer than 2^32 threads in x (HIP refuses larger ones), so the
+// divisions are 32 bits wide.  With the wavefront's site on the
 // scalar unit and the transfers' entry numbers by quotient(): restriction onto 256 sites, 20
 // RHS, 10.5 -> 9.0 us, onto 4096 sites, 32 RHS, 14.3 -> 12.3; prolongation 8.5 -> 7.3; all
 // launches of a V-cycle at 256^2 538 -> 522 us.
