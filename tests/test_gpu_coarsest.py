@@ -400,6 +400,143 @@ def test_fp64_basis_outside_lds():
     assert ctx.timing_get("coarsest")[0] == 1
 
 
+@pytest.mark.parametrize("k", [0, 4])
+@pytest.mark.parametrize("prec", ["mixed", "fp64"])
+@pytest.mark.parametrize("shape", ["16x8", "64x16"])
+def test_nan_and_infinity_stay_in_their_right_hand_side(shape, prec, k):
+    """The one-launch solve of a block with a NaN and an infinite entry: those two come out not
+    finite, the others as without them."""
+    import torch
+
+    from paper_2211_15383_amd import dmlmc
+
+    (Lx, Lt), agg, ntv = SHAPES[shape]
+    rng = np.random.default_rng(59)
+
+    def cn(*s):
+        return rng.standard_normal(s) + 1j * rng.standard_normal(s)
+
+    H = dmlmc.Hierarchy(dmlmc.Context(0), rng.normal(0.0, 0.3, (2, Lt, Lx)), 0.1, [agg], [ntv],
+                        import_tv=[cn(2 * Lx * Lt, ntv)])
+    n = H.n(2)
+    H.solver_params(coarsest_iters=8)
+    if k:
+        defl = dmlmc.Deflation(H, 2, k, import_X=np.linalg.qr(cn(n, k))[0], import_lambda=np.linspace(0.3, 2.0, k))
+        H.set_deflation(defl)
+    p, dt = (dmlmc.MIXED, torch.complex64) if prec == "mixed" else (dmlmc.FP64, torch.complex128)
+    b = torch.as_tensor(cn(5, n), device="cuda").to(dt)
+    ref = H.apply(dmlmc.OP_VCYCLE, 2, b, torch.empty_like(b), prec=p)
+    b[1, n // 3] = float("nan")
+    b[3, n - 1] = float("inf")
+    x = H.apply(dmlmc.OP_VCYCLE, 2, b, torch.empty_like(b), prec=p)
+    finite = torch.isfinite(torch.view_as_real(x)).reshape(5, -1).all(1).tolist()
+    assert finite == [True, False, True, False, True]
+    assert torch.equal(torch.view_as_real(x[::2]), torch.view_as_real(ref[::2]))
+
+
+def _to_blocks(x, lx, lt, d, agg):
+    """[rows, n] of a level by (aggregate, chirality) blocks: [rows, blocks, entries of a block]."""
+    ax, at = agg
+    x = x.reshape(-1, lt // at, at, lx // ax, ax, 2, d // 2).transpose(0, 1, 3, 5, 2, 4, 6)
+    return x.reshape(x.shape[0], lx * lt // (ax * at) * 2, -1)
+
+
+def _from_blocks(x, lx, lt, d, agg):
+    ax, at = agg
+    x = x.reshape(-1, lt // at, lx // ax, 2, at, ax, d // 2).transpose(0, 1, 4, 2, 5, 3, 6)
+    return x.reshape(x.shape[0], -1)
+
+
+def _three_levels(rng, Lx, Lt, ntv, agg):
+    """A hierarchy of imported test vectors, those of the second level orthonormal on their blocks;
+    also the blocks."""
+    from paper_2211_15383_amd import dmlmc
+
+    def cn(*s):
+        return rng.standard_normal(s) + 1j * rng.standard_normal(s)
+
+    lx, lt, d = Lx // 4, Lt // 4, 2 * ntv[0]
+    B = np.linalg.qr(cn(lx * lt // (agg[0] * agg[1]) * 2, agg[0] * agg[1] * ntv[0], ntv[1]))[0]
+    tv2 = _from_blocks(B.transpose(2, 0, 1), lx, lt, d, agg).T
+    H = dmlmc.Hierarchy(dmlmc.Context(0), rng.normal(0.0, 0.3, (2, Lt, Lx)), 0.3, [(4, 4), agg], list(ntv),
+                        import_tv=[cn(2 * Lx * Lt, ntv[0]), np.ascontiguousarray(tv2)])
+    return H, B
+
+
+@pytest.mark.parametrize("Lx,Lt,ntv,agg,nrhs", [
+    (64, 64, (5, 4), (4, 4), 5),   # 4 test vectors, an incomplete group of right-hand sides
+    (64, 64, (4, 12), (4, 4), 3),  # 12: by chunks
+    (64, 64, (7, 8), (2, 4), 4),   # 8 in the straight-line form
+    (264, 264, (8, 8), (6, 6), 3),  # 8 by whole rows through LDS, a ragged last workgroup
+])
+def test_vcycle_with_presmoothing(Lx, Lt, ntv, agg, nrhs):
+    """A V-cycle of the second of three levels, whose prolongation adds to the smoothed vector."""
+    import torch
+
+    from paper_2211_15383_amd import dmlmc
+
+    rng = np.random.default_rng(61)
+    H, B = _three_levels(rng, Lx, Lt, ntv, agg)
+    m = 6
+    H.solver_params(nu_pre=1, nu_post_coarse=1, smoother_half=0, coarsest_iters=m)
+    lx, lt, d = H.level_info(2)
+    lx3, lt3, _ = H.level_info(3)
+    A, A3 = H.export(2, Dc=True)["Dc"], H.export(3, Dc=True)["Dc"]
+    Ainv = np.linalg.inv(A[:, 0])
+    t, x = np.divmod(np.arange(lx * lt), lx)
+    b = rng.standard_normal((nrhs, H.n(2))) + 1j * rng.standard_normal((nrhs, H.n(2)))
+
+    def sweep(y, bh):
+        for color in (0, 1):
+            r = (bh - _blocks_apply(A, lx, lt, y)).reshape(lx * lt, d, -1)
+            on = (x + t) % 2 == color
+            y.reshape(lx * lt, d, -1)[on] += (Ainv @ r)[on]
+
+    # bounds of the coarsest solve, which is the least accurate part
+    for prec, dt, tol in ((dmlmc.FP64, torch.complex128, 1e-11), (dmlmc.MIXED, torch.complex64, 2e-4)):
+        bd = torch.as_tensor(b, device="cuda").to(dt)
+        out = H.apply(dmlmc.OP_VCYCLE, 2, bd, torch.full_like(bd, float("nan")), prec=prec).cpu().numpy()
+        bh = bd.cpu().numpy().astype(np.complex128).T
+        y = np.zeros_like(bh)
+        sweep(y, bh)
+        r = _to_blocks((bh - _blocks_apply(A, lx, lt, y)).T, lx, lt, d, agg)
+        bc = (r[:, :, None, :] @ B.conj()[None]).reshape(nrhs, -1)
+        xc = np.stack([_gmres(lambda v: _blocks_apply(A3, lx3, lt3, v), v, m) for v in bc])
+        y += _from_blocks((B[None] @ xc.reshape(nrhs, -1, ntv[1], 1))[..., 0], lx, lt, d, agg).T
+        sweep(y, bh)
+        err = np.linalg.norm(out.T - y, axis=0) / np.linalg.norm(y, axis=0)
+        assert err.max() <= tol, (prec, err.max())
+
+
+@pytest.mark.parametrize("Lx,Lt,ntv,nrhs", [
+    (32, 32, 8, 9),     # 16 dofs, 64 sites: a wavefront per tile, through LDS
+    (128, 128, 8, 8), (128, 128, 8, 20),  # 1024 sites, padded work vectors, one tile and two
+    (256, 256, 8, 9),   # 4096 sites, one tile: straight from memory
+    (256, 256, 8, 17),  # two tiles: both in one wavefront
+    (128, 128, 8, 1), (128, 128, 8, 2), (128, 128, 8, 7),  # the scalar kernel
+    (64, 64, 5, 1), (64, 64, 5, 2), (64, 64, 7, 6), (64, 64, 12, 2), (64, 64, 12, 5), (128, 128, 4, 5),
+])
+def test_refinement_residual(Lx, Lt, ntv, nrhs):
+    """The relative residual that a solve of the second level reports is that of its solution (the
+    residual form of the FP64 stencils, stored in FP32 at padded strides by mixed solves)."""
+    import torch
+
+    from paper_2211_15383_amd import dmlmc
+
+    rng = np.random.default_rng(67)
+    H, _ = _three_levels(rng, Lx, Lt, (ntv, 2), (2, 2))
+    lx, lt, _ = H.level_info(2)
+    A = H.export(2, Dc=True)["Dc"]
+    b = torch.as_tensor(rng.standard_normal((nrhs, H.n(2))) + 1j * rng.standard_normal((nrhs, H.n(2))), device="cuda")
+    # FP64: residuals of size 0.1 from sums rounded at 1e-15; mixed: each entry rounded to FP32
+    for prec, tol in ((dmlmc.FP64, 1e-11), (dmlmc.MIXED, 1e-6)):
+        X, st = H.solve(2, b, prec=prec, rtol=0.2)
+        r = b.cpu().numpy() - _blocks_apply(A, lx, lt, X.cpu().numpy().T).T
+        rel = np.linalg.norm(r, axis=1) / np.linalg.norm(b.cpu().numpy(), axis=1)
+        assert st.converged and st.ir_steps >= 1 and rel.max() > 1e-4
+        assert abs(st.relres_max - rel.max()) <= tol * rel.max(), (prec, st.relres_max, rel.max())
+
+
 def test_block_larger_than_the_readback_buffer():
     """8200 right-hand sides: their norms (8 bytes each) exceed the pinned staging buffer."""
     import torch
