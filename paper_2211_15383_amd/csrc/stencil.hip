@@ -65,15 +65,20 @@ __device__ __forceinline__ void hops(Cx<R> ux, Cx<R> uxm, Cx<R> ut, Cx<R> utm, S
   a1 = a1 + mul_i(g);
 }
 
-// Workgroups are dispatched round-robin over the 8 XCDs (each with its own L2).  This
-// renumbering hands every XCD a contiguous range of logical workgroups, so neighbouring
-// sites (the stencils' re-reads) are fetched through the same L2.  It is a bijection on
-// [0, gridDim.x): the largest multiple of 8 is permuted, the tail keeps its numbers.
+// Workgroups are dispatched round-robin over the 8 XCDs (each with its own L2), row after row
+// of the grid.  This renumbering hands every XCD a contiguous range of logical workgroups, the
+// same one in every row (group of right-hand sides) whatever the number of workgroups in a
+// row, so neighbouring sites (the stencils' re-reads) and a site's links and blocks are fetched
+// through the same L2.  It is a bijection on [0, gridDim.x): the largest multiple of 8 is permuted,
+// the tail keeps its numbers.  Gauss-Seidel sweep in FP64 without and with it: 3224 sites of 8 dofs,
+// 100 RHS (51 workgroups a row, a site on a different XCD for every group) 151 -> 59 us; 1092 sites of 32
+// dofs, 34 RHS (69) 266 -> 113.
 __device__ __forceinline__ int64_t xcd_block() {
   const int64_t g = blockIdx.x, n = gridDim.x;
   const int64_t full = n & ~(int64_t)7;
   if (g >= full) return g;
-  return (g & 7) * (full >> 3) + (g >> 3);
+  const int64_t xcd = (g + blockIdx.y * n) & 7;
+  return xcd * (full >> 3) + (g >> 3);
 }
 
 // A workgroup of the fine stencil has tiles of TILE_X sites by TILE_T rows, a row per
@@ -432,7 +437,7 @@ __global__ __launch_bounds__(256) void coarse_gs_kernel(const Cx<R>* __restrict_
   const int64_t V = (int64_t)Lx * Lt;
   const int i = threadIdx.x % d;
   const int ls = threadIdx.x / d;
-  const int64_t k = (int64_t)blockIdx.x * spb + ls;
+  const int64_t k = xcd_block() * spb + ls;
   int64_t s;
   bool active;
   if (even_lx) {
@@ -2172,33 +2177,30 @@ struct GsPlan {
   int threads;
 };
 
-// Form and workgroup of the scalar Gauss-Seidel sweep.  A launch of few wavefronts waits for its
-// loads, which are then all out before they are used, in workgroups of 64 threads on more CUs; one of
-// many is bound by the caches: fewer loads in flight, and 256 threads sharing neighbours and
-// blocks, fetch less from beyond them.  Measured in us a launch as plain loops / as chosen here /
-// (where that is neither) prefetching:
-//   up to 2048 wavefronts: 128 sites, one RHS, FP64, 8 dofs 8.5 / 3.9, 16 dofs 13.6 / 5.5; 4096 sites, 5 RHS, FP64,
-//     10 dofs 23.2 / 18.2, 12 dofs 27.7 / 25.0
-//   2 to 6 dofs: 4096 sites, 32 RHS, 2 dofs FP64 7.1 / 6.3 / 9.5, 6 dofs FP32 31.8 / 18.8 / 23.4, FP64 43.2 / 36.2 / 42.5
-//   8 dofs FP64: 4096 sites, 32 RHS 34.5 / 25.2; 16384 sites, 16 RHS 71.5 / 71.8 / 122
-//   10 and 12 dofs FP64: 4096 sites, 32 RHS 72.0 / 72.1 / 105 and 102 / 103 / 137
-//   14 and 16 dofs FP64: 4096 sites, 32 RHS 127 / 89 / 187 (in chunks) and 120 / 122 / 137; 16384 sites, 16 RHS
-//     293 / 295 / 368 (in chunks) and 381 / 383 / 460
-//   more dofs: 32, 4096 sites FP64 (403 MB of blocks) 32 RHS 603 / 606 / 863 (in chunks), 2 RHS 87 / 52; 24, 5 RHS 115 / 76
+// Form and workgroup of the scalar Gauss-Seidel sweep.  With a direction's entries on their way before
+// the last one's products a launch waits once and not five times, and workgroups of 64 threads reach more
+// CUs.  Against that lie registers (FP64 from 12 dofs on: one direction at a time) and,
+// with blocks beyond what the caches keep, lines that loads far ahead push out before their other
+// entries are read: plain loops there.  More than 16 dofs go by chunks, whose blocks are shared better
+// in 256 threads once the chip is full.  Measured in us a launch as GS_PLAIN of 256 threads, GS_AHEAD
+// or GS_CHUNKS of 64, the same of 256, GS_DIRECTIONS of 64 (-: no such form), * the one chosen:
+//   8 dofs FP32, 132 sites, 34 RHS 8.5 / 4.5* / 5.2 / 5.5; FP64, 3224 sites, 34 RHS 32.6 / 22.6* / 22.7 / 23.4
+//   10 dofs FP64, 4356 sites, 34 RHS 63.7 / 48.8* / 47.8 / 48.7
+//   14 dofs FP64, 4096 sites, 34 RHS 111 / 113 / 114 / 94.7*; 16 dofs, 4356 sites 146 / 155 / 164 / 147*
+//   beyond 100 MB (125 MB) of blocks: FP64, 8 dofs, 16384 sites, 3 RHS 18.7* / 24.1 / 24.4 / 18.4; 10 dofs, 16 RHS
+//     135* / 187 / 187 / 187; 16 dofs, 7052 sites, 34 RHS 251* / 401 / 405 / 379
+//   24 dofs FP64, 132 sites, 3 RHS 20.5 / 13.0* / 18.0 / -; 1092 sites, 34 RHS 86.8 / 79.4 / 71.8* / -
+//   32 dofs FP64, 1092 sites, 34 RHS 160 / 108* / 113 / -; 4096 sites (403 MB), 34 RHS 714* / 867 / 874 / -
 template <typename R>
 GsPlan gs_plan(int d, int64_t V, int64_t nsites, int nrhs, int rb) {
   constexpr bool F64 = std::is_same<R, double>::value;
-  const int64_t groups = ceil_div(nrhs, rb), waves = ceil_div(nsites * d, 64) * groups;
-  const double blocks = (double)V * 6 * d * d * sizeof(Cx<R>);
-  if (d > 24 && waves >= 8192 && blocks >= 128e6) return {GS_PLAIN, 256};
-  if (d > 16) return {GS_CHUNKS, ceil_div(nsites * d, 256) * groups >= 1024 ? 256 : 64};
-  if (waves < (d <= 6 ? 2048 : 2200)) return {GS_AHEAD, 64};
-  if (F64 && d >= 6 && V >= 16384) return {GS_PLAIN, 256};
-  if (d <= 6) return {GS_DIRECTIONS, 256};
-  if (d == 8) return {GS_AHEAD, 256};
-  if (F64 && d >= 14) return {GS_DIRECTIONS, 64};
-  if (F64 && blocks >= 4e6 && waves * d * d >= 400000) return {GS_PLAIN, 256};
-  return {GS_AHEAD, d <= 12 && waves >= 8192 ? 256 : 64};
+  const int64_t waves = ceil_div(nsites * d, 64) * ceil_div(nrhs, rb);
+  const double entries = (double)V * d * d;  // of a direction
+  if (d > 24) return waves >= 5000 && entries >= 4e6 ? GsPlan{GS_PLAIN, 256} : GsPlan{GS_CHUNKS, 64};
+  if (d > 16) return {GS_CHUNKS, waves >= 2048 ? 256 : 64};
+  if (F64 && waves >= 2500 && entries >= (d <= 12 ? 1e6 : 1.3e6)) return {GS_PLAIN, 256};
+  if (F64 && d >= 12 && waves >= 1024) return {GS_DIRECTIONS, 64};
+  return {GS_AHEAD, 64};
 }
 }  // namespace
 
@@ -2257,12 +2259,15 @@ void launch_coarse_gs(dmlmc_ctx* ctx, const Level& L, Cx<R>* x, const Cx<R>* b, 
 #define GS_LAUNCH(D, FORM)                                                                                               \
   hipLaunchKernelGGL((coarse_gs_kernel<R, D, FORM>), grid, block, shm, ctx->stream, A, Ai, x, b, L.Lx, L.Lt, d, spb, nrhs, \
                      rb, color, even, ld)
-#define GS_DOFS(D)                                \
-  case D:                                         \
-    if (g.form == GS_AHEAD)                       \
-      GS_LAUNCH(D, GS_AHEAD);                     \
-    else                                          \
-      GS_LAUNCH(D, GS_DIRECTIONS);                \
+#define GS_DOFS(D)                                                                  \
+  case D:                                                                           \
+    if constexpr (std::is_same<R, double>::value && D >= 12) {                      \
+      if (g.form == GS_DIRECTIONS) {                                                \
+        GS_LAUNCH(D, GS_DIRECTIONS);                                                \
+        break;                                                                      \
+      }                                                                             \
+    }                                                                               \
+    GS_LAUNCH(D, GS_AHEAD);                                                         \
     break
   if (g.form == GS_PLAIN) {
     GS_LAUNCH(0, GS_PLAIN);

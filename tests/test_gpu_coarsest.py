@@ -304,12 +304,13 @@ def test_coarse_operator_and_transfers_by_dofs(Lx, Lt, agg, ntv, nrhs):
 
 @pytest.mark.parametrize("Lx,Lt,ntv,nrhs", [
     (16, 16, 1, 3), (16, 24, 2, 3), (24, 16, 7, 3), (16, 16, 9, 2),  # 2, 4 and 14 dofs prefetching, 18 in chunks
-    (64, 64, 2, 257), (64, 64, 3, 257),  # 4 and 6 dofs by directions, 257 right-hand sides
-    (64, 64, 4, 160),                    # 8 dofs prefetching, 256 threads
+    (64, 64, 2, 257), (64, 64, 3, 257), (64, 64, 4, 160),  # 4, 6 and 8 dofs, many groups of right-hand sides
     (32, 32, 7, 321), (32, 32, 8, 300),  # 14 and 16 dofs, FP64 by directions
-    (128, 128, 5, 65), (128, 128, 6, 48),  # 10 and 12 dofs, FP64 entry by entry
-    (512, 512, 4, 3),                    # 16384 sites, FP64 entry by entry
-    (160, 160, 16, 21),                  # 32 dofs, blocks of 157 MB (FP64) entry by entry
+    (128, 128, 5, 65), (128, 128, 6, 48),  # 10 and 12 dofs, FP64 of the latter by directions
+    (512, 512, 4, 3), (288, 288, 8, 5),  # FP64 entry by entry: 16384 sites of 8 dofs, 5184 of 16
+    (160, 160, 16, 21), (256, 256, 16, 6),  # 32 dofs in chunks of 64 threads and entry by entry
+    # rows of workgroups that are no multiple of 8 in number, several groups of right-hand sides
+    (88, 24, 4, 34), (120, 72, 12, 40), (168, 104, 7, 34), (208, 248, 4, 12),
 ])
 def test_coarse_gauss_seidel_forms(Lx, Lt, ntv, nrhs):
     """The forms of the sweep by dofs, sites and right-hand sides; bounds as above."""
