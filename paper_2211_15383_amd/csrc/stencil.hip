@@ -65,20 +65,28 @@ __device__ __forceinline__ void hops(Cx<R> ux, Cx<R> uxm, Cx<R> ut, Cx<R> utm, S
   a1 = a1 + mul_i(g);
 }
 
-// Workgroups are dispatched round-robin over the 8 XCDs (each with its own L2), row after row
-// of the grid.  This renumbering hands every XCD a contiguous range of logical workgroups, the
-// same one in every row (group of right-hand sides) whatever the number of workgroups in a
-// row, so neighbouring sites (the stencils' re-reads) and a site's links and blocks are fetched
-// through the same L2.  It is a bijection on [0, gridDim.x): the largest multiple of 8 is permuted,
-// the tail keeps its numbers.  Gauss-Seidel sweep in FP64 without and with it: 3224 sites of 8 dofs,
-// 100 RHS (51 workgroups a row, a site on a different XCD for every group) 151 -> 59 us; 1092 sites of 32
-// dofs, 34 RHS (69) 266 -> 113.
+// Workgroups are dispatched round-robin over the 8 XCDs (each with its own L2).  This
+// renumbering hands every XCD a contiguous range of logical workgroups, so neighbouring
+// sites (the stencils' re-reads) are fetched through the same L2.  It is a bijection on
+// [0, gridDim.x): the largest multiple of 8 is permuted, the tail keeps its numbers.
 __device__ __forceinline__ int64_t xcd_block() {
   const int64_t g = blockIdx.x, n = gridDim.x;
   const int64_t full = n & ~(int64_t)7;
   if (g >= full) return g;
-  const int64_t xcd = (g + blockIdx.y * n) & 7;
-  return xcd * (full >> 3) + (g >> 3);
+  return (g & 7) * (full >> 3) + (g >> 3);
+}
+
+// The same with every range on one XCD in all rows of the grid (groups of right-hand sides), also
+// where a row's workgroups are no multiple of 8 in number and the next one so begins on another
+// XCD: a site's blocks are read into one L2.  Gauss-Seidel sweep in FP64, without renumbering and
+// with it: 3224 sites of 8 dofs, 100 RHS (51 workgroups a row) 151 -> 59 us; 1092 sites of 32 dofs, 34 RHS
+// (69) 266 -> 113.  The fine stencils keep the shorter form, as most of their extents make such multiples:
+// 1024^2, FP32, 32 RHS 234.0 us against 235.3 with this one.
+__device__ __forceinline__ int64_t xcd_block_in_row() {
+  const int64_t g = blockIdx.x, n = gridDim.x;
+  const int64_t full = n & ~(int64_t)7;
+  if (g >= full) return g;
+  return ((g + blockIdx.y * n) & 7) * (full >> 3) + (g >> 3);
 }
 
 // A workgroup of the fine stencil has tiles of TILE_X sites by TILE_T rows, a row per
@@ -437,7 +445,7 @@ __global__ __launch_bounds__(256) void coarse_gs_kernel(const Cx<R>* __restrict_
   const int64_t V = (int64_t)Lx * Lt;
   const int i = threadIdx.x % d;
   const int ls = threadIdx.x / d;
-  const int64_t k = xcd_block() * spb + ls;
+  const int64_t k = xcd_block_in_row() * spb + ls;
   int64_t s;
   bool active;
   if (even_lx) {
