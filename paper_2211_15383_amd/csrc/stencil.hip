@@ -644,12 +644,13 @@ __global__ __launch_bounds__(256) void restrict_kernel(const Cx<R>* __restrict__
     if (q < nr) yc[(int64_t)(r0 + q) * ldc + cs * 2 * N + c * N + k] = acc[q];
 }
 
-// Prolongation x_f (+)= P e_c; thread per (fine dof, group of RB right-hand sides, those of an
-// incomplete group one by one).  NT test vectors, or any number (0) by chunks; a thread's chunk of an
-// interpolation row is one request (FP64, 256^2 onto the fine level, 16 RHS: 105 -> 34 us).  With a
-// chunk of eight and a branch per entry for all but eight test vectors, and incomplete groups
-// filled up with their last right-hand side: 512^2, one test vector, FP64, 32 RHS 85 us against 65; 4 test
-// vectors, FP32, one RHS 11.2 against 6.6; 16^2, 16 test vectors, one RHS 10.1 against 6.2.
+// Prolongation x_f (+)= P e_c; thread per (fine dof, group of up to RB right-hand sides).  NT test
+// vectors, or any number (0) by chunks; a thread's chunk of an interpolation row is one request
+// (FP64, 256^2 onto the fine level, 16 RHS: 105 -> 34 us).  With a chunk of eight and a branch per
+// entry for all but eight test vectors, and incomplete groups filled up with their last right-hand
+// side: 512^2, one test vector, FP64, 32 RHS 85 us against 65; 4 test vectors, FP32, one RHS 11.2 against 6.6;
+// 16^2, 16 test vectors, one RHS 10.1 against 6.2.  An incomplete group in code of its own size and not one
+// by one, which reads P again each time: 16 test vectors, FP64, 64^2, 3 RHS 13.4 -> 9.3, 264^2 31.2 -> 21.7.
 template <typename R, int RB, int NT>
 __global__ __launch_bounds__(256) void prolong_kernel(const Cx<R>* __restrict__ P, const Cx<R>* __restrict__ ec,
                                                       Cx<R>* __restrict__ xf, int Lxf, int Ltf, int df, int ax, int at,
@@ -699,11 +700,12 @@ __global__ __launch_bounds__(256) void prolong_kernel(const Cx<R>* __restrict__ 
 #pragma unroll
     for (int q = 0; q < B; ++q) xf[(int64_t)(r0 + q) * ldf + tid] = acc[q];
   };
-  const int r0 = blockIdx.y * RB, r1 = min(r0 + RB, nrhs);
-  if (r1 - r0 == RB) {
-    group(r0, std::integral_constant<int, RB>());
-  } else {
-    for (int r = r0; r < r1; ++r) group(r, std::integral_constant<int, 1>());
+  const int r0 = blockIdx.y * RB;
+  switch (min(nrhs - r0, RB)) {
+    case 1: group(r0, std::integral_constant<int, 1>()); break;
+    case 2: group(r0, std::integral_constant<int, 2>()); break;
+    case 3: group(r0, std::integral_constant<int, 3>()); break;
+    default: group(r0, std::integral_constant<int, RB>());
   }
 }
 
