@@ -65,26 +65,16 @@ __device__ __forceinline__ void hops(Cx<R> ux, Cx<R> uxm, Cx<R> ut, Cx<R> utm, S
   a1 = a1 + mul_i(g);
 }
 
-// Workgroups are dispatched round-robin over the 8 XCDs (each with its own L2).  This
-// renumbering hands every XCD a contiguous range of logical workgroups, so neighbouring
-// sites (the stencils' re-reads) are fetched through the same L2.  It is a bijection on
-// [0, gridDim.x): the largest multiple of 8 is permuted, the tail keeps its numbers.
+// Workgroups are dispatched round-robin over the 8 XCDs (each with its own L2), row after row
+// of the grid.  This renumbering hands every XCD a contiguous range of logical workgroups, the
+// same one in every row (group of right-hand sides) also where a row's workgroups are no multiple of
+// 8 in number and the next one so begins on another XCD: neighbouring sites (the stencils' re-reads)
+// and a site's links and blocks are fetched through one L2.  It is a bijection on [0, gridDim.x): the
+// largest multiple of 8 is permuted, the tail keeps its numbers.  Without regard to the row / with it:
+// Gauss-Seidel in FP64, 3224 sites of 8 dofs, 100 RHS (51 workgroups a row) 151 / 59 us, 1092 sites of 32 dofs, 34
+// RHS (69) 266 / 113; fine stencil in FP64, 400 x 300, 16 RHS (525) 32.5 / 25.7, 360 x 500, 5 RHS (750) 17.9 / 14.9.
 __device__ __forceinline__ int64_t xcd_block() {
-  const int64_t g = blockIdx.x, n = gridDim.x;
-  const int64_t full = n & ~(int64_t)7;
-  if (g >= full) return g;
-  return (g & 7) * (full >> 3) + (g >> 3);
-}
-
-// The same with every range on one XCD in all rows of the grid (groups of right-hand sides), also
-// where a row's workgroups are no multiple of 8 in number and the next one so begins on another
-// XCD: a site's blocks are read into one L2.  Gauss-Seidel sweep in FP64, without renumbering and
-// with it: 3224 sites of 8 dofs, 100 RHS (51 workgroups a row) 151 -> 59 us; 1092 sites of 32 dofs, 34 RHS
-// (69) 266 -> 113.  The fine stencils keep the shorter form, as most of their extents make such multiples:
-// 1024^2, FP32, 32 RHS 234.0 us against 235.3 with this one.
-__device__ __forceinline__ int64_t xcd_block_in_row() {
-  const int64_t g = blockIdx.x, n = gridDim.x;
-  const int64_t full = n & ~(int64_t)7;
+  const unsigned g = blockIdx.x, n = gridDim.x, full = n & ~7u;
   if (g >= full) return g;
   return ((g + blockIdx.y * n) & 7) * (full >> 3) + (g >> 3);
 }
@@ -445,7 +435,7 @@ __global__ __launch_bounds__(256) void coarse_gs_kernel(const Cx<R>* __restrict_
   const int64_t V = (int64_t)Lx * Lt;
   const int i = threadIdx.x % d;
   const int ls = threadIdx.x / d;
-  const int64_t k = xcd_block_in_row() * spb + ls;
+  const int64_t k = xcd_block() * spb + ls;
   int64_t s;
   bool active;
   if (even_lx) {
@@ -1879,11 +1869,12 @@ struct WilsonGrid {
 // (linear -> tiles, 32 RHS: 1024^2 253 -> 234 us in FP32 and 598 -> 567 in FP64, 400 x 300
 // 38.6 -> 37.0; with a quarter outside, 200 x 180, 18.6 -> 19.5; 128^2 20.0 -> 20.2).
 // Right-hand sides per thread: up to 8, as links are then re-read least, while input and output
-// (`bytes` an entry pair) fit into the 256 MB last-level cache (1024^2, FP32, 4 RHS: 37.9 us, with 2 39.7)
-// or each of them does (1024^2, FP64, 5 RHS 60.8 us, with 2 70.7; FP32, 12 RHS 64.7 and 72.4; 400 x 300, 128
-// RHS 79.9 and 88.3).  Beyond that 2, since few streams at a time keep the neighbours' rows in the L2s
-// (1024^2, FP32, 16 RHS 110 us, with 8 116), and with 16 RHS and whole tiles of rows of up to 16 KB already
-// from the cache's size on (512^2, 32 RHS 41.2 and 44.8; 768 x 600 67.3 and 74.8, but FP64, 16 RHS 92.5 and 82.3).
+// (`bytes` an entry pair) fit into the 256 MB last-level cache (1024^2, FP32, 4 RHS: 37.9 us, with 2 39.7).
+// From twice that on 2, since few streams at a time keep the neighbours' rows in the L2s (1024^2, FP32, 16 RHS
+// 110 us, with 8 116).  Between them 2 too for vectors of up to 20 MB, of which a pair stays in the L2s
+// while it is swept (344 x 328, FP64, 48 RHS 59.3 us, with 8 64.0; 360 x 500, FP64, 34 RHS 65.5 and 71.2; 512^2,
+// FP32, 32 RHS 41.2 and 44.8; 640 x 608, FP32, 34 RHS 61.5 and 67.4), and 8 for larger ones (768 x 600, FP64, 16 RHS
+// 82.8 us, with 2 96.1; 1024^2, FP64, 5 RHS 61.7 and 71.1, FP32, 12 RHS 65.3 and 72.4).
 // `variant` (0: none) is a choice made by hand or by the tuner.
 WilsonGrid wilson_grid(const Level& L, int nrhs, size_t bytes, int variant) {
   const int64_t V = L.sites(), tx = ceil_div(L.Lx, TILE_X), tt = ceil_div(L.Lt, TILE_T);
@@ -1893,8 +1884,8 @@ WilsonGrid wilson_grid(const Level& L, int nrhs, size_t bytes, int variant) {
   WilsonGrid g;
   g.blocks = (unsigned)(tiles ? tx * tt : ceil_div(V, 256));
   g.tiles_x = tiles ? (int)tx : 0;
-  const bool rows = nrhs >= 16 && L.Lx % TILE_X == 0 && L.Lx * bytes <= 16384;
-  const int most = tiles && (total > 512e6 || (total > 256e6 && rows)) ? 2 : 8;
+  const bool pairs = total > 512e6 || (total > 256e6 && (double)L.n() * bytes <= 20e6);
+  const int most = tiles && pairs ? 2 : 8;
   g.rb = variant > 0 ? std::min(variant, nrhs) : std::min(most, rhs_block_for(V, nrhs));
   g.rb = std::max(g.rb, (int)ceil_div(nrhs, 65535));
   return g;

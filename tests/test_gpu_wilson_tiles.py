@@ -58,8 +58,9 @@ def test_stencil_of_more_right_hand_sides_than_workgroup_rows(gpu):
 
 @pytest.mark.parametrize("Lx,Lt,nrhs,name", [
     (400, 300, 33, "fp64"),   # 253 MB, just within the cache
-    (400, 300, 65, "fp64"),   # beyond it, ragged tiles: 8 right-hand sides per thread
+    (400, 300, 65, "fp64"),   # beyond it, ragged tiles, rows of 525 workgroups: 2 right-hand sides per thread
     (256, 132, 119, "fp64"),  # beyond it, whole tiles: 2
+    (720, 512, 13, "fp64"),   # beyond it, vectors of 24 MB: 8
     (1024, 64, 130, "fp64"),  # 545 MB, both vectors beyond it: 2
 ])
 def test_stencil_right_hand_sides_per_thread(gpu, Lx, Lt, nrhs, name):
